@@ -39,6 +39,7 @@
 //    contiguously in the [k][block][receiver][slot] output layout.
 #include <hip/hip_fp16.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "afc_internal.h"
@@ -68,7 +69,7 @@ constexpr int kWavesMain = 16, kWavesBatched = 8;
 constexpr int kKStride = 16 * 16 + 4;        // float2 per k1 row
 constexpr int kSStride = 4 * kKStride + 2;   // float2 per spectrum
 constexpr int kSpectraPerPhase = 16;
-constexpr int kChunk = 768;                  // spectra per workgroup, a multiple of 16
+constexpr int kRunQ = 32;                    // a workgroup's run of spectra is a multiple of this
 constexpr int kTT = 18;                      // tap pairs per branch and part (t = 0..17, cyclic)
 
 // One workgroup: receivers [i0, i0+16) of one subband, spectra [s_begin, s_end).
@@ -345,7 +346,7 @@ template <int DT, bool kOne>
 __global__ __launch_bounds__(64 * kWavesMain) void ppf_kernel(const int16_t* __restrict__ x, const float* __restrict__ taps,
                                                        void* __restrict__ z, Tw64 tw, int64_t x_sb_stride,
                                                        int64_t z_sb_bytes, int N, int S, int Sb, int n_groups,
-                                                       int n_chunks, int total, int per_xcd, float gain) {
+                                                       int n_chunks, int total, int per_xcd, int run, float gain) {
     __shared__ float2 lds[kSpectraPerPhase * kSStride];
     __shared__ __attribute__((aligned(16))) unsigned ltp[2 * kP * kTT];
     // workgroups go round-robin over the 8 XCDs: give each XCD a contiguous
@@ -356,8 +357,8 @@ __global__ __launch_bounds__(64 * kWavesMain) void ppf_kernel(const int16_t* __r
     const int grp = w % n_groups;
     const int chunk = (w / n_groups) % n_chunks;
     const int sb = w / (n_groups * n_chunks);
-    const int s_begin = chunk * kChunk;
-    const int s_end = min(S, s_begin + kChunk);
+    const int s_begin = chunk * run;
+    const int s_end = min(S, s_begin + run);
     ppf_body<DT, kWavesMain, kOne>(x + sb * x_sb_stride, taps, reinterpret_cast<char*>(z) + sb * z_sb_bytes, tw, N, S, Sb,
                  grp * kNi, s_begin, s_end, gain, lds, ltp);
 }
@@ -368,7 +369,7 @@ __global__ __launch_bounds__(64 * kWavesBatched) void ppf_batched_kernel(const i
                                                               const float* __restrict__ taps, void* __restrict__ z,
                                                               Tw64 tw, const PpfItem* __restrict__ items,
                                                               int N, int n_groups, int n_chunks, int total,
-                                                              int per_xcd) {
+                                                              int per_xcd, int run) {
     __shared__ float2 lds[kSpectraPerPhase * kSStride];
     __shared__ __attribute__((aligned(16))) unsigned ltp[2 * kP * kTT];
     // XCD-aware order as in ppf_kernel: neighbouring receiver groups (which
@@ -379,9 +380,9 @@ __global__ __launch_bounds__(64 * kWavesBatched) void ppf_batched_kernel(const i
     const int chunk = (w / n_groups) % n_chunks;
     const int it = w / (n_groups * n_chunks);
     const PpfItem item = items[it];
-    const int s_begin = chunk * kChunk;
+    const int s_begin = chunk * run;
     if (s_begin >= item.S) return;                       // uniform over the workgroup
-    const int s_end = min(item.S, s_begin + kChunk);
+    const int s_end = min(item.S, s_begin + run);
     const int16_t* xs = x + item.x_off;
     void* zs = reinterpret_cast<char*>(z) + item.z_off;
     if (item.dt == AFC_F32)
@@ -392,12 +393,42 @@ __global__ __launch_bounds__(64 * kWavesBatched) void ppf_batched_kernel(const i
         ppf_body<AFC_I8, kWavesBatched, kOne>(xs, taps, zs, tw, N, item.S, item.Sb, grp * kNi, s_begin, s_end, item.gain, lds, ltp);
 }
 
+// Spectra per workgroup.  142 KB of LDS leave one workgroup per CU, so a
+// launch runs in rounds of workgroups over the CUs, each as long as its run:
+// phases of 16 spectra (~6 us of a full chip) plus about one more for the tap
+// tables and the run's first half-window.  The run is the multiple of 32 (two
+// phases, so that every spectrum keeps its parity and with it its bits) that
+// minimises rounds x (phases + 1); the longer one on ties.  Against the fixed
+// 768 spectra it replaced: 48 antennas x 1 subband x 1024 spectra 186 -> 15 us
+// (12 workgroups before, 192 now), 576 x 1 x 3051 to fp16 534 -> 423 us (a
+// second round with 32 workgroups before), 288 x 8 x 3051 1342 -> 1302 us;
+// 576 x 16 x 3051 still takes 768 (5154 us; 640 and 1024 within 0.4%).
+int ppf_run(int B, int n_groups, int S) {
+    int dev = 0, n_cu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu <= 0)
+        n_cu = 256;
+    const int64_t s_pad = ceil_div(S, kRunQ) * kRunQ;
+    int best = kRunQ;
+    int64_t best_cost = INT64_MAX;
+    for (int c = kRunQ; c <= std::min<int64_t>(s_pad, 4096); c += kRunQ) {
+        const int64_t rounds = ceil_div((int64_t)B * n_groups * ceil_div(S, c), n_cu);
+        const int64_t cost = rounds * (c / kSpectraPerPhase + 1);
+        if (cost <= best_cost) {
+            best_cost = cost;
+            best = c;
+        }
+    }
+    return best;
+}
+
 }  // namespace
 
 hipError_t launch_ppf(const PpfLaunch& a, hipStream_t stream) {
     static const Tw64 tw = make_twiddles();
     const int n_groups = (int)ceil_div(a.N, kNi);
-    const int n_chunks = (int)ceil_div(a.S, kChunk);
+    const int run = ppf_run(a.B, n_groups, a.S);
+    const int n_chunks = (int)ceil_div(a.S, run);
     const int total = (int)((int64_t)a.B * n_groups * n_chunks);
     const int per_xcd = (int)ceil_div(total, 8);
     const dim3 grid((unsigned)(per_xcd * 8));
@@ -407,10 +438,10 @@ hipError_t launch_ppf(const PpfLaunch& a, hipStream_t stream) {
 #define AFC_PPF_LAUNCH(DT)                                                                                       \
     if (one)                                                                                                     \
         hipLaunchKernelGGL((ppf_kernel<DT, true>), grid, dim3(64 * kWavesMain), 0, stream, a.x, a.taps, a.z, tw,  \
-                           a.x_sb_stride, z_sb_bytes, a.N, a.S, a.Sb, n_groups, n_chunks, total, per_xcd, a.gain); \
+                           a.x_sb_stride, z_sb_bytes, a.N, a.S, a.Sb, n_groups, n_chunks, total, per_xcd, run, a.gain); \
     else                                                                                                         \
         hipLaunchKernelGGL((ppf_kernel<DT, false>), grid, dim3(64 * kWavesMain), 0, stream, a.x, a.taps, a.z, tw, \
-                           a.x_sb_stride, z_sb_bytes, a.N, a.S, a.Sb, n_groups, n_chunks, total, per_xcd, a.gain);
+                           a.x_sb_stride, z_sb_bytes, a.N, a.S, a.Sb, n_groups, n_chunks, total, per_xcd, run, a.gain);
     switch (a.dt) {
         case AFC_F32: AFC_PPF_LAUNCH(AFC_F32) break;
         case AFC_F16: AFC_PPF_LAUNCH(AFC_F16) break;
@@ -424,7 +455,8 @@ hipError_t launch_ppf_batched(const int16_t* x, const float* taps, void* z_ws, c
                               int n_items, int N, int max_S, hipStream_t stream) {
     static const Tw64 tw = make_twiddles();
     const int n_groups = (int)ceil_div(N, kNi);
-    const int n_chunks = (int)ceil_div(max_S, kChunk);
+    const int run = 768;
+    const int n_chunks = (int)ceil_div(max_S, run);
     const int64_t total64 = (int64_t)n_items * n_groups * n_chunks;
     if (total64 > (1LL << 30)) return hipErrorInvalidValue;
     const int total = (int)total64;
@@ -435,10 +467,10 @@ hipError_t launch_ppf_batched(const int16_t* x, const float* taps, void* z_ws, c
     const bool one = (int64_t)kP * ceil_div(max_S, kSBlk) * N * kSBlk * 8 <= 0x7FFFFFFFLL;
     if (one)
         hipLaunchKernelGGL((ppf_batched_kernel<true>), grid, dim3(64 * kWavesBatched), 0, stream, x, taps, z_ws, tw,
-                           items_dev, N, n_groups, n_chunks, total, per_xcd);
+                           items_dev, N, n_groups, n_chunks, total, per_xcd, run);
     else
         hipLaunchKernelGGL((ppf_batched_kernel<false>), grid, dim3(64 * kWavesBatched), 0, stream, x, taps, z_ws, tw,
-                           items_dev, N, n_groups, n_chunks, total, per_xcd);
+                           items_dev, N, n_groups, n_chunks, total, per_xcd, run);
     return hipGetLastError();
 }
 

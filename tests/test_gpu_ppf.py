@@ -203,3 +203,18 @@ def test_output_above_2gib_per_subband(afc, dev, dtype):
             assert np.all(d <= 2.0 ** -11 * np.abs(comp(ref)) * 1.0001 + 2e-5 * sigma)
     del x, z
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("dtype,gain", [("f32", 1.0), ("f16", 1.0), ("i8", 0.05)])
+@pytest.mark.parametrize("S", [31, 33, 333])
+def test_run_length_does_not_change_results(afc, dev, dtype, gain, S):
+    """The host picks the spectra per workgroup from the launch size: one
+    subband of 75 antennas runs 32 spectra per workgroup, 24 of them longer
+    runs.  Runs start at multiples of two phases, so every spectrum's products
+    keep their order and the outputs are identical bit for bit."""
+    cfg = W.Config("runs", 75, 24, n_spectra=S, sigma_n=200.0, source_sigmas=(50.0,), seed=11)
+    x, _, z = _run(afc, dev, cfg, dtype, gain)
+    taps = torch.from_numpy(W.prototype_taps()).to(dev)
+    for sb in (0, 23):
+        z1 = afc.channelise(x[sb:sb + 1].contiguous(), taps, S, dtype, gain)
+        assert torch.equal(z1[0].view(torch.int8), z[sb].view(torch.int8)), sb
