@@ -290,7 +290,9 @@ def main():
         f32_xe = t32.ms("xengine")
         f32_tf = 8.0 * cmac / (f32_xe * 1e-3) / 1e12
         out["fp32"] = {"xengine_ms": round(f32_xe, 3), "xengine_tcmacs": round(cmac / (f32_xe * 1e-3) / 1e12, 3),
+                       # above 1: computed as six bf16 products of exact parts
                        "xengine_fp32_mfma_frac": round(f32_tf / PEAK_FP32_MFMA_TFLOPS, 4),
+                       "xengine_bf16_mfma_frac": round(6 * f32_tf / PEAK_FP16_TFLOPS, 4),
                        "ppf_ms": round(t32.ms("ppf"), 3),
                        "ppf_gbs": round((float(B) * L * N * 4 + float(B) * P * S * N * 8) / (t32.ms("ppf") * 1e-3) / 1e9, 1),
                        "real_time_factor": round(data_s / ((f32_xe + t32.ms("ppf")) * 1e-3), 2)}

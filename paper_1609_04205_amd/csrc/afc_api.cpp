@@ -585,14 +585,14 @@ namespace {
 // Time of one tile item in MFMA cycles (per SIMD), from the instruction
 // rates: an int8 16x16x64 and an fp16 16x16x32 MFMA take the same cycles,
 // the int8 one covering twice the spectra (4 and 8 cycles per spectrum for
-// the real and imaginary parts of a 32 x 32 area); fp32 32x32x2 blocks take
-// 128.  The waves of a tile run in parallel, so a diagonal tile takes the
-// time of its busiest wave: 9 of 16 blocks (128-wide), 3 of 4 (64-wide
-// int8 / fp16), all of it for fp32 (one block per wave either way).
+// the real and imaginary parts of a 32 x 32 area); fp32 takes six bf16
+// MFMAs of the fp16 cost.  The waves of a tile run in parallel, so a diagonal
+// tile takes the time of its busiest wave (fp32: SIMD): 9 of 16 blocks
+// (128-wide), 3 of 4 (64-wide int8 / fp16), all four rows (64-wide fp32).
 double tile_cost(int dt, int tile, int S, bool diag) {
-    const double diag_frac = dt == AFC_F32 ? 1.0 : tile == 128 ? 9.0 / 16.0 : 3.0 / 4.0;
+    const double diag_frac = tile == 128 ? 9.0 / 16.0 : dt == AFC_F32 ? 1.0 : 3.0 / 4.0;
     const double blocks = (tile / 32.0) * (tile / 32.0) * (diag ? diag_frac : 1.0);
-    const double per_spec = dt == AFC_I8 ? 4.0 : dt == AFC_F16 ? 8.0 : 128.0;   // cycles per 32x32 area-spectrum
+    const double per_spec = dt == AFC_I8 ? 4.0 : dt == AFC_F16 ? 8.0 : 48.0;    // cycles per 32x32 area-spectrum
     return blocks * per_spec * S + 2000.0;                                      // + fixed cost (epilogue)
 }
 
@@ -952,7 +952,9 @@ AFC_API int afc_plan_create(const afc_dims* d, const afc_dtype* dtype_per_sb, co
         }
     }
     if (any1) {
-        rc = upload_mode(p, 1, 64);
+        int n32 = 0;
+        for (int b = 0; b < B; ++b) n32 += p->dt[b] == AFC_F32;
+        rc = upload_mode(p, 1, xengine_f32_tile(p->N, n32));
         if (rc != AFC_OK) {
             afc_plan_destroy(p);
             return rc;

@@ -102,15 +102,16 @@ struct XcdRanges {
 };
 // One workgroup per work item (workgroup ids go round-robin over the 8
 // XCDs); mode 0: int8 / fp16 subbands with tile-wide tiles (128 or 64),
-// mode 1: fp32 subbands (64).  Returns the grid size through n_wg_out.
+// mode 1: fp32 subbands (128 or 64).
 hipError_t launch_xengine_list(const void* z_ws, void* vis, int32_t* weights, const uint8_t* flags,
                                const XSubband* sbs_dev, const XWork* work_dev, const XcdRanges& ranges,
                                int N, int Na, int mode, int tile, hipStream_t stream);
 int xengine_list_grid(const XcdRanges& ranges);
+// tile width of the fp32 correlator for N receivers and its subband count
+int xengine_f32_tile(int N, int n_subbands);
 // Fill `bytes` (a multiple of 4) of device memory with hashed bytes that are
 // valid int8 samples and finite fp16 values (bit 6 of every byte clear).
 hipError_t launch_fill_scratch(void* p, size_t bytes, hipStream_t stream);
-int xengine_tile(afc_dtype dt);
 
 // ---------------------------------------------------------------- validity
 // spectrum validity bits [B][ceil(S/32)][Na] from packet flags [B][n_pk][Na]

@@ -20,23 +20,24 @@
 // 2w, 2w+1 against the eight row blocks (128 x 32 outputs); a diagonal tile
 // gives wave w the column blocks w and 7-w, nine blocks on or below the
 // diagonal each.  64-wide tiles: four row blocks x column block w off the
-// diagonal, ten blocks split 3/3/2/2 on it.  fp32: 32 x 32 blocks, 2 x 2
-// waves of one quarter each, the wave above the diagonal idle on a diagonal
-// tile.  Tiles wholly above the diagonal are never launched.
+// diagonal, ten blocks split 3/3/2/2 on it.  Tiles wholly above the diagonal
+// are never launched.
 // int8 / fp16: the row panel of a tile streams through LDS in stages of one
 // MFMA k-step (direct global-to-LDS loads of the block layout
 // [block][receiver][8 spectra], XOR-swizzled 16-byte chunks so that the MFMA
 // operand reads are bank-conflict free); off the diagonal each wave loads
-// its own column blocks straight into registers.  fp32 stages both panels
-// through registers into LDS.
+// its own column blocks straight into registers.  fp32: 16 x 16 blocks as
+// well, on samples split into three bf16 parts (see xtile_split).
 //
 // Sample types (gfx950 MFMA):
 //   int8  v_mfma_i32_16x16x64_i8  (32 spectra per k-step), exact int32 sums
 //   fp16  v_mfma_f32_16x16x32_f16 (16 spectra per k-step), fp32 sums
-//   fp32  v_mfma_f32_32x32x2_f32  ( 2 spectra per k-step), fp32 sums, summed
-//         in two levels (blocks of 64 spectra into a second accumulator) to
-//         keep the rounding error of 3051-term sums near 1e-7 relative
+//   fp32  v_mfma_f32_16x16x32_bf16 (16 spectra per k-step and product of
+//         parts), fp32 sums, summed in two levels (64 spectra into a second
+//         accumulator) to keep the rounding error of 3051-term sums near 1e-7
+//         relative; v_mfma_f32_32x32x2_f32 for samples out of the parts' range
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 #include <utility>
 
@@ -95,14 +96,23 @@ constexpr int dma_depth() { return DT == AFC_I8 ? AFC_I8_DMA_DEPTH : AFC_F16_DMA
 // buffer being refilled
 template <int DT>
 constexpr int dma_buffers() { return dma_depth<DT>() + 2; }
+// both panels of a 64-wide tile on the fp32 matrix cores, two buffers
+template <int TILE>
+constexpr int lds_f32_bytes() { return 2 * 2 * stage_blocks<AFC_F32, TILE>() * TILE * XT<AFC_F32>::RB; }
 template <int DT, int TILE>
 constexpr int lds_bytes() {
+    // fp32: the 64-wide tiles computed at a time on the fp32 matrix cores (the
+    // bf16 split's two buffers of two panels are smaller)
+    if (DT == AFC_F32) return (TILE / 64) * lds_f32_bytes<64>();
     // 128-wide int8 / fp16 tiles stage only the row panel (their column
     // operands are loaded into registers, or, on the diagonal, are the row
     // panel); the others stage both
-    constexpr int panels = uses_dma<DT>() && TILE == 128 ? 1 : 2;
-    return (uses_dma<DT>() ? dma_buffers<DT>() : 2) * panels * stage_blocks<DT, TILE>() * TILE * XT<DT>::RB;
+    constexpr int panels = TILE == 128 ? 1 : 2;
+    return dma_buffers<DT>() * panels * stage_blocks<DT, TILE>() * TILE * XT<DT>::RB;
 }
+// threads of a tile's workgroup
+template <int DT, int TILE>
+constexpr int tile_threads() { return DT == AFC_F32 ? 4 * TILE : kThreads; }
 
 // Workgroup barrier for the DMA pipeline: no memory fence (which would wait
 // for every outstanding global-to-LDS load) and no wait for the wave's LDS
@@ -193,6 +203,38 @@ __device__ __forceinline__ int jswap_f16(int w) {
     const unsigned u = (unsigned)w;
     return (int)(((u >> 16) | (u << 16)) ^ 0x00008000u);
 }
+
+// Store of the 2 x 2 polarisation block of a baseline by a lane pair.  The
+// values are those of rows I, I + 1 (the two polarisations of antenna I / 2)
+// and receiver Jc, which the lane and the one at (lane xor 1) hold for the two
+// receivers of one antenna: the pair swaps one value, so that the even lane
+// owns (p, q) = (0, 0), (0, 1) and the odd lane (1, 0), (1, 1), and each
+// stores 16 contiguous bytes.
+template <class E>
+struct StorePair {
+    char* vis_ch;
+    int32_t* w_sb;
+    int N, S;
+    bool write_weights, odd;
+    __device__ __forceinline__ void operator()(E r0, E i0v, E r1, E i1v, int I, int Jc, bool flagged) const {
+        // the even lane sends its p = 1 values, the odd lane its p = 0 values
+        const E yr = pair_swap(odd ? r0 : r1), yi = pair_swap(odd ? i0v : i1v);
+        E o0 = odd ? yr : r0, o1 = odd ? yi : i0v, o2 = odd ? r1 : yr, o3 = odd ? i1v : yi;
+        const int a = I >> 1, b = Jc >> 1;
+        if (Jc >= N || I >= N || a < b) return;
+        if (a == b) {             // inputs equal for (0, 0) and (1, 1)
+            if (odd) o3 = E(0);
+            else o1 = E(0);
+        }
+        if (flagged) o0 = o1 = o2 = o3 = E(0);
+        const int64_t bl = (int64_t)a * (a + 1) / 2 + b;
+        // written once and not read again by this kernel: a streaming
+        // (non-temporal) store
+        typedef E ev4 __attribute__((ext_vector_type(4)));
+        __builtin_nontemporal_store(ev4{o0, o1, o2, o3}, reinterpret_cast<ev4*>(vis_ch) + bl * 2 + (odd ? 1 : 0));
+        if (write_weights && !odd) w_sb[bl] = flagged ? 0 : S;
+    }
+};
 
 // Zero the spectra >= valid (1..8) of a 16-byte chunk of plane q.
 template <int DT>
@@ -606,31 +648,10 @@ __device__ __forceinline__ void xtile_mm16(const char* __restrict__ z, char* __r
 
     // ---- epilogue: 2 x 2 polarisation blocks of antennas a >= b.  Rows
     // 4 (lane / 16) + {0, 1} and {2, 3} of a lane are the two polarisations
-    // of two antennas, lanes lc, lc ^ 1 the two of one antenna b: a lane pair
-    // holds the four values of a baseline, swaps one value so that the even
-    // lane owns (p, q) = (0, 0), (0, 1) and the odd lane (1, 0), (1, 1), and
-    // each lane stores 16 contiguous bytes.
+    // of two antennas, lanes lc, lc ^ 1 the two of one antenna b.
     using E = std::conditional_t<DT == AFC_I8, int, float>;
     const bool odd = (lc & 1) != 0;
-    // rows I, I + 1 (the two polarisations of antenna I / 2) of receiver Jc
-    auto store_pair = [&](E r0, E i0v, E r1, E i1v, int I, int Jc, bool flagged) {
-        // the even lane sends its p = 1 values, the odd lane its p = 0 values
-        const E yr = pair_swap(odd ? r0 : r1), yi = pair_swap(odd ? i0v : i1v);
-        E o0 = odd ? yr : r0, o1 = odd ? yi : i0v, o2 = odd ? r1 : yr, o3 = odd ? i1v : yi;
-        const int a = I >> 1, b = Jc >> 1;
-        if (Jc >= N || I >= N || a < b) return;
-        if (a == b) {             // inputs equal for (0, 0) and (1, 1)
-            if (odd) o3 = E(0);
-            else o1 = E(0);
-        }
-        if (flagged) o0 = o1 = o2 = o3 = E(0);
-        const int64_t bl = (int64_t)a * (a + 1) / 2 + b;
-        // written once and not read again by this kernel: a streaming
-        // (non-temporal) store
-        typedef E ev4 __attribute__((ext_vector_type(4)));
-        __builtin_nontemporal_store(ev4{o0, o1, o2, o3}, reinterpret_cast<ev4*>(vis_ch) + bl * 2 + (odd ? 1 : 0));
-        if (write_weights && !odd) w_sb[bl] = flagged ? 0 : S;
-    };
+    const StorePair<E> store_pair{vis_ch, w_sb, N, S, write_weights, odd};
     auto flag_of = [&](int rcv) { return fl_sb[min(rcv, N - 1) >> 1] != 0; };
     auto to_u = [](E v) -> unsigned {
         if constexpr (DT == AFC_I8) return (unsigned)v;
@@ -762,14 +783,292 @@ __device__ __forceinline__ void xtile_mm16(const char* __restrict__ z, char* __r
     }
 }
 
-// One fp32 tile of one (subband, channel): 2 x 2 waves of one 32 x 32 block
-// each, samples staged through registers.  `z` points at channel ch of
-// subband sb.
+// ---------------------------------------------------------------------------
+// fp32 tiles on the bf16 matrix cores.
+//
+// Every float32 sample is the exact sum of three bf16 parts, h + m + l (8
+// significant bits each, rounded to nearest), and a product of two samples
+// the sum of nine products of parts, each exact in float32.  Six of them are
+// formed (16x16x32 MFMAs, float32 sums, the small ones first); the dropped
+// m l, l m and l l are below 2^-25 of the product, less than the rounding of
+// one float32 multiply.  The bf16 rate is 16 times the fp32 matrix rate, so
+// the six take 3/8 of the time of the fp32 MFMAs.
+// Bound by the matrix cores' power: 1152 receivers x 2 subbands x 3051 spectra
+// take 10.4 ms, 1.2 PFLOP/s of bf16 MFMA (a large bf16 product reaches 1.26 on
+// the same card), against 17.9 ms on the fp32 MFMAs; converting while the
+// SIMD's other wave multiplies is worth 2% of it.
+//
+// 128-wide tiles: 8 waves, wave (rh, cg) takes the row blocks 4 rh .. 4 rh + 3
+// of two column blocks, 2 cg and 2 cg + 1, or on a diagonal tile cg and 7 - cg,
+// so that the waves of one SIMD (cg, both rh) share 9 blocks of the lower
+// triangle.  64-wide tiles: 4 waves, wave cg the four row blocks of column
+// block cg.  A step is 16 spectra: each thread loads 32 bytes (4 spectra of a
+// receiver) of the row panel and of the column panel, splits them and writes
+// the parts to LDS (plane, receiver, four 16-byte K chunks, swizzled as in
+// swz()) while the previous step is multiplied from the other buffer.  Sums
+// are kept in two levels: the MFMA accumulators take kSplitInner steps and are
+// then added to an outer sum.
+template <int TILE>
+constexpr int split_plane() { return TILE * 64; }        // bytes of one part of a panel: TILE receivers x 16 spectra
+template <int TILE>
+constexpr int split_panel() { return 3 * split_plane<TILE>(); }
+constexpr int kSplitInner = 4;
+
+typedef __bf16 v8b __attribute__((ext_vector_type(8)));
+typedef __bf16 v2b __attribute__((ext_vector_type(2)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+
+// bf16 parts of two floats, packed: x = h + m + l exactly (|x| in range)
+__device__ __forceinline__ void split2(float x, float y, unsigned& h, unsigned& m, unsigned& l) {
+    h = __builtin_bit_cast(unsigned, __builtin_convertvector(v2f{x, y}, v2b));
+    const float x1 = x - __uint_as_float(h << 16), y1 = y - __uint_as_float(h & 0xFFFF0000u);
+    m = __builtin_bit_cast(unsigned, __builtin_convertvector(v2f{x1, y1}, v2b));
+    const float x2 = x1 - __uint_as_float(m << 16), y2 = y1 - __uint_as_float(m & 0xFFFF0000u);
+    l = __builtin_bit_cast(unsigned, __builtin_convertvector(v2f{x2, y2}, v2b));
+}
+
+// The split holds for samples that are 0 or 2^-50 <= |x| < 2^50: no part is
+// subnormal, no part rounds to infinity and no product of parts leaves the
+// normal range.  mx and mn collect the largest magnitude and the smallest
+// nonzero one (twice the bits, minus one: zero is the largest value).
+constexpr float kSplitMax = 0x1p50f;
+constexpr unsigned kSplitMin = 2u * ((127u - 50u) << 23) - 1u;
+__device__ __forceinline__ void split_range(float x, float y, float& mx, unsigned& mn) {
+    mx = fmaxf(fmaxf(fabsf(x), fabsf(y)), mx);
+    mn = min(min(2u * __float_as_uint(x) - 1u, 2u * __float_as_uint(y) - 1u), mn);
+}
+
+// kFull: an off-diagonal tile with all rows and columns below N (no block of
+// it is skipped).  False if a sample is out of the split's range; the tile is
+// then not stored.
+template <int TILE, bool kFull>
+__device__ __forceinline__ bool xtile_split(const char* __restrict__ z, char* __restrict__ vis_ch,
+                                            int32_t* __restrict__ w_sb, const uint8_t* __restrict__ fl_sb,
+                                            int N, int S, int ti, int tj, bool write_weights, char* lds) {
+    constexpr int RB = 64, NC = TILE == 128 ? 2 : 1;
+    constexpr int kSplitPlane = split_plane<TILE>(), kSplitPanel = split_panel<TILE>();
+    const int tid = threadIdx.x, lane = tid & 63, lc = lane & 15, lg = lane >> 4;
+    const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int cg = wid & 3, rh = wid >> 2;               // rh = 0 in 64-wide tiles
+    const int i0 = ti * TILE, j0 = tj * TILE;
+    const bool diag = !kFull && ti == tj;
+    const int nb = (S + kSBlk - 1) / kSBlk;
+    const int tail_valid = S - (nb - 1) * kSBlk;
+    const int full_blocks = tail_valid < kSBlk ? nb - 1 : nb;
+    const int n_k = (nb + 1) / 2;
+    const int bn[2] = {diag || NC == 1 ? cg : 2 * cg, diag ? 7 - cg : 2 * cg + 1};
+    // blocks this wave computes: those with a row and a column below N, on or
+    // below the diagonal
+    bool on[4][NC];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int x = 0; x < NC; ++x)
+            on[i][x] = kFull || (i0 + (4 * rh + i) * 16 < N && j0 + bn[x] * 16 < N && (!diag || 4 * rh + i >= bn[x]));
+
+    // staging: 4 spectra (sh) of one receiver of block sb of the step, in
+    // either panel; rows beyond N repeat row N - 1 (they only feed outputs
+    // that are never stored), blocks beyond the data the last block
+    const int sh = tid & 1, srow = (tid >> 1) & (TILE - 1), sb = tid / (2 * TILE);
+    const unsigned src_a = (unsigned)min(i0 + srow, N - 1) * RB + sh * 32;
+    const unsigned src_b = (unsigned)min(j0 + srow, N - 1) * RB + sh * 32;
+    const unsigned dst = (unsigned)srow * 64 + (unsigned)((((sb * 2 + sh) ^ (srow >> 2)) & 3) * 16);
+    constexpr int kDepth = 2;                            // steps of loads in flight beyond the one being staged
+    float4 raws[kDepth][2][2];
+    auto load = [&](int k, auto slot_tag) {
+        float4 (&raw)[2][2] = raws[decltype(slot_tag)::value];
+        const unsigned off = (unsigned)min(2 * k + sb, nb - 1) * (unsigned)(N * RB);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            raw[0][e] = *reinterpret_cast<const float4*>(z + (src_a + off + 16 * e));
+            if (!diag) raw[1][e] = *reinterpret_cast<const float4*>(z + (src_b + off + 16 * e));
+        }
+    };
+    float mx = 0.0f;
+    unsigned mn = 0xFFFFFFFFu;
+    auto stage = [&](int k, auto slot_tag) {
+        float4 (&raw)[2][2] = raws[decltype(slot_tag)::value];
+        if (2 * k + 2 > full_blocks) {                   // uniform: zero the spectra >= S
+            const int first = (2 * k + sb) * kSBlk + sh * 4;
+#pragma unroll
+            for (int pn = 0; pn < 2; ++pn)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    float4& v = raw[pn][e];
+                    if (first + 2 * e >= S) v.x = v.y = 0.0f;
+                    if (first + 2 * e + 1 >= S) v.z = v.w = 0.0f;
+                }
+        }
+        char* base = lds + (k & 1) * 2 * kSplitPanel + dst;
+#pragma unroll
+        for (int pn = 0; pn < 2; ++pn) {
+            if (pn == 1 && diag) break;
+            uint4 h, m, l;
+            const float4 u = raw[pn][0], v = raw[pn][1];
+            split2(u.x, u.y, h.x, m.x, l.x);
+            split2(u.z, u.w, h.y, m.y, l.y);
+            split2(v.x, v.y, h.z, m.z, l.z);
+            split2(v.z, v.w, h.w, m.w, l.w);
+            split_range(u.x, u.y, mx, mn);
+            split_range(u.z, u.w, mx, mn);
+            split_range(v.x, v.y, mx, mn);
+            split_range(v.z, v.w, mx, mn);
+            char* p = base + pn * kSplitPanel;
+            *reinterpret_cast<uint4*>(p) = h;
+            *reinterpret_cast<uint4*>(p + kSplitPlane) = m;
+            *reinterpret_cast<uint4*>(p + 2 * kSplitPlane) = l;
+        }
+    };
+    v4f accR[4][NC], accI[4][NC], outR[4][NC], outI[4][NC];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int x = 0; x < NC; ++x) accR[i][x] = accI[i][x] = outR[i][x] = outI[i][x] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    auto rd = [&](const char* panel, int part, int row) -> uint4 {
+        return *reinterpret_cast<const uint4*>(panel + part * kSplitPlane + row * 64 + (((lg ^ (row >> 2)) & 3) * 16));
+    };
+    auto jsw = [](uint4 u) {
+        return make_uint4((unsigned)jswap_f16((int)u.x), (unsigned)jswap_f16((int)u.y), (unsigned)jswap_f16((int)u.z),
+                          (unsigned)jswap_f16((int)u.w));
+    };
+    auto mm = [](v4f& acc, uint4 a, uint4 b) {
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8b, a), __builtin_bit_cast(v8b, b), acc, 0, 0, 0);
+    };
+    uint4 b[NC][3], bj[NC][3];
+    auto columns = [&](int k) {
+        const char* pa = lds + (k & 1) * 2 * kSplitPanel;
+        const char* pb = diag ? pa : pa + kSplitPanel;
+#pragma unroll
+        for (int x = 0; x < NC; ++x)
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                b[x][p] = rd(pb, p, bn[x] * 16 + lc);
+                bj[x][p] = jsw(b[x][p]);
+            }
+    };
+    auto rows = [&](int k, auto first_tag, auto last_tag) {
+        const char* pa = lds + (k & 1) * 2 * kSplitPanel;
+        // (row part, column part), smallest products first
+        constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+        for (int i = decltype(first_tag)::value; i < decltype(last_tag)::value; ++i) {
+            uint4 a[3];
+#pragma unroll
+            for (int p = 0; p < 3; ++p) a[p] = rd(pa, p, (4 * rh + i) * 16 + lc);
+            if constexpr (kFull) {
+#pragma unroll
+                for (int q = 0; q < 6; ++q)
+#pragma unroll
+                    for (int x = 0; x < NC; ++x) {
+                        mm(accR[i][x], a[PA[q]], b[x][PB[q]]);
+                        mm(accI[i][x], a[PA[q]], bj[x][PB[q]]);
+                    }
+            } else {
+#pragma unroll
+                for (int x = 0; x < NC; ++x)
+                    if (on[i][x]) {
+#pragma unroll
+                        for (int q = 0; q < 6; ++q) {
+                            mm(accR[i][x], a[PA[q]], b[x][PB[q]]);
+                            mm(accI[i][x], a[PA[q]], bj[x][PB[q]]);
+                        }
+                    }
+            }
+        }
+    };
+    auto fold = [&]() {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int x = 0; x < NC; ++x) {
+                outR[i][x] += accR[i][x];
+                outI[i][x] += accI[i][x];
+                accR[i][x] = accI[i][x] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+            }
+    };
+    // a sample out of range stops the tile: the wave that meets one raises the
+    // workgroup's flag before the barrier of the step that folds, and every
+    // wave reads it after that barrier (no wave writes it before it is read)
+    int* const bad = reinterpret_cast<int*>(lds + 4 * kSplitPanel);
+    auto raise = [&]() {
+        if (__any(!(mx < kSplitMax) || mn < kSplitMin) && lane == 0) *bad = 1;
+    };
+    if (tid == 0) *bad = 0;
+    using S0 = std::integral_constant<int, 0>;
+    using S1 = std::integral_constant<int, kDepth - 1>;
+    load(0, S0{});
+    stage(0, S0{});
+    load(1, S1{});
+    load(2, S0{});
+    lds_barrier();
+    int inner = 0;
+    // multiply step k; step k + 1 (in register slot `slot`) goes to the other
+    // buffer.  The two waves of a SIMD stage at different times, so that one
+    // multiplies while the other converts.
+    auto step = [&](int k, auto slot_tag) {
+        const bool more = k + 1 < n_k;
+        if ((!kFull || rh == 0) && more) {
+            stage(k + 1, slot_tag);
+            load(k + 1 + kDepth, slot_tag);
+        }
+        columns(k);
+        rows(k, std::integral_constant<int, 0>{}, std::integral_constant<int, 2>{});
+        if (kFull && rh == 1 && more) {
+            stage(k + 1, slot_tag);
+            load(k + 1 + kDepth, slot_tag);
+        }
+        rows(k, std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
+        if (++inner == kSplitInner) {
+            inner = 0;
+            fold();
+            raise();
+        }
+        lds_barrier();
+    };
+    for (int k = 0; k < n_k; k += 2) {
+        if (inner == 0 && __builtin_amdgcn_readfirstlane(*bad)) return false;
+        step(k, S1{});
+        if (k + 1 < n_k) step(k + 1, S0{});
+    }
+    fold();
+    raise();
+    lds_barrier();
+    if (__builtin_amdgcn_readfirstlane(*bad)) return false;
+
+    const StorePair<float> st{vis_ch, w_sb, N, S, write_weights, (lc & 1) != 0};
+    auto flag_of = [&](int rcv) { return fl_sb && fl_sb[min(rcv, N - 1) >> 1] != 0; };
+    bool fr[4][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) fr[i][h] = flag_of(i0 + (4 * rh + i) * 16 + 4 * lg + 2 * h);
+#pragma unroll
+    for (int x = 0; x < NC; ++x) {
+        const int Jc = j0 + bn[x] * 16 + lc;
+        const bool fc = flag_of(Jc);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (!on[i][x]) continue;
+#pragma unroll
+            for (int r = 0; r < 4; r += 2)
+                st(outR[i][x][r], outI[i][x][r], outR[i][x][r + 1], outI[i][x][r + 1],
+                   i0 + (4 * rh + i) * 16 + 4 * lg + r, Jc, fc || fr[i][r >> 1]);
+        }
+    }
+    return true;
+}
+
+// One fp32 tile on the fp32 matrix cores: 2 x 2 waves of one 32 x 32 block
+// each (threads tid 0..255), samples staged through registers.  The tiles
+// whose samples the bf16 split cannot hold take it (infinities, magnitudes
+// outside 2^-50 .. 2^50); sums in two levels of 64 spectra.  `z` points at
+// channel ch of subband sb; off: the tile is only stepped through (its
+// barriers), neither multiplied nor stored.
 template <int DT, int TILE>
 __device__ __forceinline__ void xtile_f32(const char* __restrict__ z, char* __restrict__ vis_ch,
                                       int32_t* __restrict__ w_sb, const uint8_t* __restrict__ fl_sb,
                                       int N, int Na, int S, int ti, int tj, bool write_weights,
-                                      char* lds_raw) {
+                                      char* lds_raw, int tid, bool off) {
     using Tr = XT<DT>;
     constexpr int RB = Tr::RB, PLANES = Tr::PLANES, kStg = stage_blocks<DT, TILE>();
     constexpr int WT = TILE / 2, MB = WT / 32;
@@ -780,12 +1079,12 @@ __device__ __forceinline__ void xtile_f32(const char* __restrict__ z, char* __re
     static_assert(DT == AFC_F32, "fp32 only");
     using acc_t = typename Tr::acc_t;
 
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int lane = tid & 63;
     const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wr = wid >> 1, wc = wid & 1;
     const int i0 = ti * TILE, j0 = tj * TILE;
     const bool diag = ti == tj;
-    const bool wave_on = !(diag && wr < wc);
+    const bool wave_on = !off && !(diag && wr < wc);
     const int nb = (S + kSBlk - 1) / kSBlk;
     const int tail_valid = S - (nb - 1) * kSBlk;             // spectra in the last block
     const int n_stages = (nb + kStg - 1) / kStg;
@@ -1012,7 +1311,29 @@ __device__ __forceinline__ void xtile(const char* __restrict__ z, char* __restri
                                       int32_t* __restrict__ w_sb, const uint8_t* __restrict__ fl_sb,
                                       int N, int Na, int S, int ti, int tj, bool write_weights, char* lds_raw) {
     if constexpr (DT == AFC_F32) {
-        xtile_f32<DT, TILE>(z, vis_ch, w_sb, fl_sb, N, Na, S, ti, tj, write_weights, lds_raw);
+        static_assert(4 * split_panel<TILE>() + 16 <= lds_bytes<DT, TILE>(), "two buffers of two panels and the flag");
+        const bool full = ti != tj && (ti + 1) * TILE <= N;
+        // (one spectrum: the fp32 products round less often than the split's
+        // six parts, 3.1e-8 against 3.4e-8 of the result)
+        if (S > 1 && (full ? xtile_split<TILE, true>(z, vis_ch, w_sb, fl_sb, N, S, ti, tj, write_weights, lds_raw)
+                           : xtile_split<TILE, false>(z, vis_ch, w_sb, fl_sb, N, S, ti, tj, write_weights, lds_raw)))
+            return;
+        __syncthreads();
+        if constexpr (TILE == 64) {
+            xtile_f32<DT, 64>(z, vis_ch, w_sb, fl_sb, N, Na, S, ti, tj, write_weights, lds_raw, threadIdx.x, false);
+        } else {
+            // the 64-wide quarters, two at a time: waves 0-3 the left ones,
+            // waves 4-7 the right ones (above the diagonal on a diagonal
+            // tile's top: stepped through)
+            const int half = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+#pragma unroll 1
+            for (int r = 0; r < 2; ++r) {
+                const int qi = 2 * ti + r, qj = 2 * tj + half;
+                const bool off = qi < qj || qi * 64 >= N || qj * 64 >= N;
+                xtile_f32<DT, 64>(z, vis_ch, w_sb, fl_sb, N, Na, S, qi, qj, write_weights,
+                                  lds_raw + half * lds_f32_bytes<64>(), threadIdx.x & 255, off);
+            }
+        }
     } else {
         const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         auto run = [&](auto job, const int (&am)[8], const int (&bn)[2]) {
@@ -1051,7 +1372,7 @@ __device__ __forceinline__ void xtile(const char* __restrict__ z, char* __restri
 }
 
 template <int DT, int TILE>
-__global__ __launch_bounds__(kThreads, 2) void xengine_kernel(XArgs a) {
+__global__ __launch_bounds__((tile_threads<DT, TILE>()), 2) void xengine_kernel(XArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[lds_bytes<DT, TILE>()];
     // XCD-aware order: consecutive workgroup ids go round-robin over the 8
     // XCDs; give each XCD a contiguous range of work so that the tiles of one
@@ -1078,12 +1399,12 @@ __global__ __launch_bounds__(kThreads, 2) void xengine_kernel(XArgs a) {
 // Batched form: one workgroup per work item of a host-built list; each item
 // is one tile of one channel of one subband with its own sample type and
 // integration length.  MODE 0 serves int8 and fp16 subbands (mixed in one
-// launch) with TILE-wide tiles, MODE 1 fp32 subbands (64).  Workgroup ids go
+// launch), MODE 1 fp32 subbands, with TILE-wide tiles.  Workgroup ids go
 // round-robin over the 8 XCDs and the list holds each XCD's items (whole
 // channels, cost-balanced across XCDs) contiguously, so that the hardware
 // dispatcher keeps the tiles in flight on an XCD a window of few channels.
 template <int MODE, int TILE, int WPC>
-__global__ __launch_bounds__(kThreads, WPC) void xengine_list_kernel(
+__global__ __launch_bounds__((MODE == 1 ? tile_threads<AFC_F32, TILE>() : kThreads), WPC) void xengine_list_kernel(
     const char* __restrict__ z_ws, char* __restrict__ vis, int32_t* __restrict__ weights,
     const uint8_t* __restrict__ flags, const XSubband* __restrict__ sbs, const XWork* __restrict__ work,
     XcdRanges r, int N, int Na) {
@@ -1138,7 +1459,29 @@ hipError_t launch_fill_scratch(void* p, size_t bytes, hipStream_t stream) {
     return hipGetLastError();
 }
 
-int xengine_tile(afc_dtype dt) { return dt == AFC_F32 ? 64 : 128; }
+// fp32 tile width.  128-wide tiles convert and read each sample for twice as
+// many products, but run one workgroup per CU; 64-wide ones run two, waste
+// less at the array's edge and fill the CUs on small launches.  Measured per
+// round of workgroups (1000 spectra): 119 us for 128-wide tiles, 90 us for
+// 64-wide ones (their rounds blur once there are two), 79 us for one 64-wide
+// tile per CU or fewer.  E.g. 75 antennas x 3 subbands 262 us (128) and 206
+// us (64); 96 receivers x 4 subbands 95 and 144 us; 1152 receivers x 1
+// subband 1689 and 2021 us.
+int xengine_f32_tile(int N, int n_subbands) {
+    int dev = 0, n_cu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu <= 0)
+        n_cu = 256;
+    auto tiles = [&](int tile) {
+        const int64_t side = ceil_div(N, tile);
+        return side * (side + 1) / 2 * kP * n_subbands;
+    };
+    const double t128 = 119.0 * (double)ceil_div(tiles(128), n_cu);
+    const int64_t n64 = tiles(64);
+    const double r64 = (double)n64 / (2.0 * n_cu);
+    const double t64 = n64 <= n_cu ? 79.0 : 90.0 * (r64 < 2.0 ? std::ceil(r64) : r64);
+    return t64 < t128 ? 64 : 128;
+}
 
 hipError_t launch_xengine(const XLaunch& l, hipStream_t stream) {
     XArgs a{};
@@ -1154,7 +1497,7 @@ hipError_t launch_xengine(const XLaunch& l, hipStream_t stream) {
     a.Sb = l.Sb;
     a.B = l.B;
     a.P = kP;
-    const int tile = xengine_tile(l.dt);
+    const int tile = l.dt == AFC_F32 ? xengine_f32_tile(l.N, l.B) : 128;
     a.n_tiles_side = (int)ceil_div(l.N, tile);
     a.n_tiles = a.n_tiles_side * (a.n_tiles_side + 1) / 2;
     const int64_t total = (int64_t)a.n_tiles * kP * l.B;
@@ -1166,7 +1509,12 @@ hipError_t launch_xengine(const XLaunch& l, hipStream_t stream) {
     switch (l.dt) {
         case AFC_I8: hipLaunchKernelGGL((xengine_kernel<AFC_I8, 128>), grid, dim3(kThreads), 0, stream, a); break;
         case AFC_F16: hipLaunchKernelGGL((xengine_kernel<AFC_F16, 128>), grid, dim3(kThreads), 0, stream, a); break;
-        default: hipLaunchKernelGGL((xengine_kernel<AFC_F32, 64>), grid, dim3(kThreads), 0, stream, a); break;
+        default:
+            if (tile == 128)
+                hipLaunchKernelGGL((xengine_kernel<AFC_F32, 128>), grid, dim3(tile_threads<AFC_F32, 128>()), 0, stream, a);
+            else
+                hipLaunchKernelGGL((xengine_kernel<AFC_F32, 64>), grid, dim3(tile_threads<AFC_F32, 64>()), 0, stream, a);
+            break;
     }
     return hipGetLastError();
 }
@@ -1185,9 +1533,12 @@ hipError_t launch_xengine_list(const void* z_ws, void* vis, int32_t* weights, co
     const int g = xengine_list_grid(ranges);
     if (g == 0) return hipSuccess;
     const dim3 grid((unsigned)g), block(kThreads);
-    if (mode == 1)  // fp32 subbands
-        hipLaunchKernelGGL((xengine_list_kernel<1, 64, 2>), grid, block, 0, stream, z, v, weights, flags, sbs_dev,
-                           work_dev, ranges, N, Na);
+    if (mode == 1 && tile == 128)  // fp32 subbands
+        hipLaunchKernelGGL((xengine_list_kernel<1, 128, 2>), grid, dim3(tile_threads<AFC_F32, 128>()), 0, stream, z, v,
+                           weights, flags, sbs_dev, work_dev, ranges, N, Na);
+    else if (mode == 1)
+        hipLaunchKernelGGL((xengine_list_kernel<1, 64, 2>), grid, dim3(tile_threads<AFC_F32, 64>()), 0, stream, z, v,
+                           weights, flags, sbs_dev, work_dev, ranges, N, Na);
     else if (tile == 128)
         hipLaunchKernelGGL((xengine_list_kernel<0, 128, 2>), grid, block, 0, stream, z, v, weights, flags, sbs_dev,
                            work_dev, ranges, N, Na);

@@ -205,3 +205,81 @@ def test_full_size_sampled(afc, dev, dtype):
     assert int(w.min()) == S and int(w.max()) == S
     del z, vis
     torch.cuda.empty_cache()
+
+
+def _natural_f32(z, S):
+    zn = W.blocked_to_natural(z.cpu(), S).numpy().astype(np.float64)
+    return zn[..., 0] + 1j * zn[..., 1]                     # [B][64][S][N]
+
+
+# tile widths of fp32 launches: 75 antennas x 1 subband 64, x 8 128 (from the
+# launch size); 100 x 1 128 with an interior off-diagonal tile
+@pytest.mark.parametrize("B,Na,S", [(1, 75, 97), (4, 48, 40), (1, 100, 200), (1, 150, 65), (2, 32, 17)])
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** -56, 2.0 ** 50])
+def test_f32_split_and_its_range(afc, dev, B, Na, S, scale):
+    """fp32 samples are split into bf16 parts where every nonzero one lies in
+    [2^-50, 2^50), and multiplied on the fp32 matrix cores otherwise (scaled
+    cases): both within the fp32 bound, normalised by sqrt(V_ii V_jj)."""
+    log(f"xengine f32 split B={B} Na={Na} S={S} scale={scale}")
+    z = W.make_channelised(B, 64, S, 2 * Na, "f32", seed=Na + S, device=dev) * scale
+    z[:, :, :, 3] = 0.0                                     # a dead receiver is in range
+    v, _ = afc.correlate(z, n_spectra=S)
+    a, c = np.tril_indices(Na)
+    got = v.cpu().numpy().astype(np.float64)
+    zn = _natural_f32(z, S)
+    for b in range(B):
+        for ch in (0, 41):
+            x = zn[b, ch].T
+            V = x @ x.conj().T
+            d = np.sqrt(np.maximum(V.diagonal().real, 1e-300))
+            for p in range(2):
+                for q in range(2):
+                    g = got[b, ch, :, p, q, 0] + 1j * got[b, ch, :, p, q, 1]
+                    err = np.abs(g - V[2 * a + p, 2 * c + q]) / (d[2 * a + p] * d[2 * c + q])
+                    err[(2 * a + p == 3) | (2 * c + q == 3)] = 0.0
+                    assert err.max() <= 1e-5, (b, ch, p, q, err.max())
+            dead = got[b, ch][(a == 1)][:, 1]
+            assert np.all(dead == 0)
+
+
+@pytest.mark.parametrize("B,Na", [(1, 75), (1, 100), (1, 150)])
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan, 3.4e38, 2.0 ** -140])
+def test_f32_values_out_of_the_split_range(afc, dev, B, Na, bad):
+    """One sample that the split cannot hold leaves the visibilities of the
+    other receivers as they were (to the fp32 bound) and gives its own the
+    value of the fp32 products: with a real part of +-Inf against finite
+    samples of nonzero parts, infinities and no NaN."""
+    log(f"xengine f32 out of range Na={Na} value={bad}")
+    S, rcv = 70, 2 * Na - 3
+    z = W.make_channelised(B, 64, S, 2 * Na, "f32", seed=5, device=dev)
+    ref, _ = afc.correlate(z, n_spectra=S)
+    y = z.clone()
+    y[0, 7, 5, rcv, 2, 0] = float(bad)
+    got, _ = afc.correlate(y, n_spectra=S)
+    a, c = np.tril_indices(Na)
+    r, g = ref.cpu().numpy(), got.cpu().numpy()
+    same = np.ones(64, bool)
+    same[7] = False
+    np.testing.assert_array_equal(r[0, same], g[0, same])
+    auto = np.sqrt(np.abs(r[0, 7][a == c][:, [0, 1], [0, 1], 0]).astype(np.float64)).reshape(-1)    # [N]
+    for p in range(2):
+        for q in range(2):
+            hit = (2 * a + p == rcv) | (2 * c + q == rcv)
+            d = np.abs(g[0, 7, ~hit, p, q].astype(np.float64) - r[0, 7, ~hit, p, q]).max(-1)
+            assert (d / (auto[2 * a + p] * auto[2 * c + q])[~hit]).max() <= 2e-5
+            v = g[0, 7, hit & (a != c), p, q]
+            if v.size == 0:
+                continue
+            if np.isnan(bad):
+                assert np.isnan(v).all()
+            elif np.isinf(bad):
+                assert np.isinf(v).all()
+            else:
+                x = W.blocked_to_natural(y.cpu(), S).numpy().astype(np.float64)[0, 7]
+                x = x[..., 0] + 1j * x[..., 1]
+                k = np.flatnonzero(hit & (a != c))
+                e = (x[:, 2 * a[k] + p] * x[:, 2 * c[k] + q].conj()).sum(0)
+                fin = np.abs(e) < 1e38                      # (above: float32 overflows in either form)
+                m = np.abs(x).max(0)
+                err = np.abs((v[fin, 0] + 1j * v[fin, 1]) - e[fin])
+                assert np.all(err <= 1e-5 * S * (m[2 * a[k] + p] * m[2 * c[k] + q])[fin])
