@@ -562,6 +562,11 @@ struct afc_plan {
     } mode[3];    // 0: int8 and fp16 subbands (int8 only when split), 1: fp32, 2: fp16 when split
     bool split = false;     // int8 and fp16 subbands in launches of their own
     std::vector<PpfItem> items;
+    // channeliser runs by sample type (afc_dtype)
+    struct Runs {
+        PpfRun* d_runs = nullptr;
+        int n_runs = 0, max_S = 0;
+    } runs[3];
     // A captured graph with the channeliser's item table it reads (the table
     // holds the int8 gains, so each capture has its own).  `done` is recorded
     // on the caller's stream after every launch of the graph: a retired
@@ -836,7 +841,13 @@ int capture_plan(afc_plan* p, const int16_t* x, const float* taps, const std::ve
         free_capture(c);
         return hip_fail(e, "graph capture begin");
     }
-    hipError_t le = launch_ppf_batched(x, taps, z_workspace, c->d_items, B, p->N, p->d.n_spectra, p->cap_stream);
+    hipError_t le = hipSuccess;
+    for (int t = 0; t < 3 && le == hipSuccess; ++t) {
+        const afc_plan::Runs& r = p->runs[t];
+        if (r.n_runs)
+            le = launch_ppf_list({x, taps, z_workspace, c->d_items, r.d_runs, r.n_runs, p->N, r.max_S, (afc_dtype)t},
+                                 p->cap_stream);
+    }
     for (int m = 0; m < 3 && le == hipSuccess; ++m) {
         const afc_plan::Mode& md = p->mode[m];
         if (!md.used) continue;
@@ -917,6 +928,24 @@ AFC_API int afc_plan_create(const afc_dims* d, const afc_dtype* dtype_per_sb, co
     if (e != hipSuccess) {
         afc_plan_destroy(p);
         return hip_fail(e, "plan allocation");
+    }
+    for (int t = 0; t < 3; ++t) {
+        std::vector<int32_t> of_type;
+        for (int b = 0; b < B; ++b)
+            if (p->dt[b] == t) {
+                of_type.push_back(b);
+                p->runs[t].max_S = std::max(p->runs[t].max_S, p->S[b]);
+            }
+        const std::vector<PpfRun> runs = ppf_runs(of_type, p->S, p->N);
+        p->runs[t].n_runs = (int)runs.size();
+        if (runs.empty()) continue;
+        e = hipMalloc(&p->runs[t].d_runs, runs.size() * sizeof(PpfRun));
+        if (e == hipSuccess)
+            e = hipMemcpy(p->runs[t].d_runs, runs.data(), runs.size() * sizeof(PpfRun), hipMemcpyHostToDevice);
+        if (e != hipSuccess) {
+            afc_plan_destroy(p);
+            return hip_fail(e, "plan run table");
+        }
     }
     // int8 / fp16 subbands: tile choice from the tune cache or the tuner
     bool any0 = false, any1 = false;
@@ -1015,6 +1044,8 @@ AFC_API void afc_plan_destroy(afc_plan* p) {
     reap_captures(p, true);
     for (auto& md : p->mode)
         if (md.d_work) hipFree(md.d_work);
+    for (auto& r : p->runs)
+        if (r.d_runs) hipFree(r.d_runs);
     if (p->d_sbs) hipFree(p->d_sbs);
     if (p->cap_stream) hipStreamDestroy(p->cap_stream);
     delete p;

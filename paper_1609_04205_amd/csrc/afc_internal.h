@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 #include "afc.h"
 
 namespace afc {
@@ -41,8 +43,27 @@ struct PpfItem {
     int32_t dt;             // afc_dtype
     float gain;
 };
-hipError_t launch_ppf_batched(const int16_t* x, const float* taps, void* z_ws, const PpfItem* items_dev,
-                              int n_items, int N, int max_S, hipStream_t stream);
+// A workgroup's run of spectra [s_begin, s_end) of one item, s_begin a
+// multiple of 32.
+struct PpfRun {
+    int32_t item;
+    int32_t s_begin, s_end;
+};
+// Runs of the subbands `items` (indices into the item table and into S, all
+// of one sample type) of N receivers.
+std::vector<PpfRun> ppf_runs(const std::vector<int32_t>& items, const std::vector<int32_t>& S, int N);
+// One launch over the runs of one sample type (tables on the device).
+struct PpfListLaunch {
+    const int16_t* x;
+    const float* taps;
+    void* z;                // workspace base
+    const PpfItem* items;
+    const PpfRun* runs;
+    int n_runs, N;
+    int max_S;              // longest of the runs' subbands
+    afc_dtype dt;
+};
+hipError_t launch_ppf_list(const PpfListLaunch& a, hipStream_t stream);
 
 // Fine channeliser: 256-channel bank, delay and bandpass compensation,
 // coherent 4:1 integration to 64 channels, stored in the layout of the
