@@ -219,3 +219,26 @@ def test_sigma_clip_flags_feed_weighted_solver(afc, dev):
         Mz[:, :, pol, pol][sel] = 0
     gz, _ = _solve_gpu_w(afc, dev, Vz, Mz, g0, 40, None, None)
     assert np.abs(gw - gz).max() <= 1e-6 * np.abs(gz).max()
+
+
+# one workgroup per (channel, polarisation) up to 128 antennas (one tile of 64,
+# then three), tile and step kernels above; interior, diagonal and edge tiles
+@pytest.mark.parametrize("Na", [1, 63, 64, 65, 127, 128, 129, 192, 200])
+@pytest.mark.parametrize("form", ["plain", "flags", "weights", "both"])
+def test_solver_tile_edges_match_oracle(afc, dev, Na, form):
+    P, n_iter = 2, 9
+    V, M, g = W.make_calibration(Na=Na, P=P, n_src=4, snr=20.0, seed=Na)
+    nbl = Na * (Na + 1) // 2
+    rng = np.random.default_rng(Na)
+    fl = (rng.random((P, nbl, 2)) < 0.1).astype(np.uint8) if form in ("flags", "both") else None
+    wt = rng.uniform(0.5, 1.5, (P, nbl, 2)).astype(np.float32) if form in ("weights", "both") else None
+    g0 = (rng.uniform(0.8, 1.2, (P, Na, 2)) + 0j).astype(np.complex128)
+    log(f"solve tile edges Na={Na} {form}")
+    got, loss = _solve_gpu_w(afc, dev, V, M, g0, n_iter, fl, wt)
+    w = None if form == "plain" else oracle.cal_weights(P, nbl, flags=fl, weights=wt)
+    ref = oracle.cal_solve(V, M, g0.astype(np.complex64).astype(np.complex128), n_iter, weights=w)
+    assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max()
+    again, _ = _solve_gpu_w(afc, dev, V, M, g0, n_iter, fl, wt)
+    np.testing.assert_array_equal(got, again)
+    gz, _ = _solve_gpu_w(afc, dev, V, M, g0, 0, fl, wt)
+    np.testing.assert_allclose(gz, _ref(g0.astype(np.complex64).astype(np.complex128)), rtol=0, atol=1e-6)
