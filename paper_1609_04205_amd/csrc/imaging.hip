@@ -10,22 +10,29 @@
 // w conj(I) to the mirrored cells (N - j, N - i) (the point -u, -v).  A
 // visibility is gridded only if all eight cells are inside the grid.
 //
-//  * grid_bound_kernel: per (subband, baseline) the sum of 2 w (|Re I| +
-//    |Im I|) over its gridded channels (a bound on any cell) and of 2 w (the
-//    normalisation), reduced in a fixed order.
-//  * grid_kernel: one workgroup per (subband, pair of 48-antenna blocks),
-//    one thread per baseline at a time.  Across the 64 channels of a
-//    subband a baseline's uv point moves by a small fraction of its length,
-//    so the thread accumulates its contributions in a 3 x 3 window of cells
-//    in registers (float64) and only adds the window when the point leaves
-//    it and at the end: to a 64 x 64-cell window in LDS around the blocks'
-//    mean separation (added to the grid once per workgroup), or to the grid.  The grid accumulates in
-//    64-bit fixed point (2^e scaled, e from the bound so that nothing can
-//    overflow): integer atomics make the result independent of the order of
-//    the additions, so the grid is bitwise reproducible.
+//  * grid_estimate_kernel: the sum of 2 w (|Re I| + |Im I|) over a sample of
+//    the gridded visibilities (every 32nd group of 4 baselines on large arrays,
+//    all of them on small ones), reduced in a fixed order: an estimate of a
+//    bound on any cell, from which the fixed-point scale is taken.
+//  * grid_kernel: one workgroup per (subband, part of its channels, pair of
+//    48-antenna blocks), one thread per baseline at a time.  Across a subband
+//    a baseline's uv point moves by a small fraction of its length, so the
+//    thread accumulates the four cells around it in registers (float64) and
+//    only adds them when the point enters another cell and at the end: to a 64
+//    x 64-cell window in LDS around the blocks' mean separation (added to the
+//    grid once per workgroup), or to the grid.  The grid accumulates in 64-bit
+//    fixed point: integer atomics make the result independent of the order of
+//    the additions, so the grid is bitwise reproducible.  The same pass sums
+//    the bound itself and the normalisation.
+//  * grid_verify_kernel: the totals; should the bound exceed what the scale
+//    allows (a sample that missed most of the power), it sets the exact scale
+//    and a flag, and a second clearing and gridding, which otherwise end at
+//    once, replace the grid.
 //  * imaging: (-1)^(p+q) modulation, radix-2 Stockham FFT of each row in LDS,
 //    transpose, row FFT again, and (-1)^(i+j) Re(.) / norm with the
 //    transpose back.
+#include <algorithm>
+
 #include "afc_internal.h"
 
 namespace afc {
@@ -39,7 +46,13 @@ struct GridArgs {
     const double* pos;            // [Na][2]
     const double* freq;           // [B][64]
     int Na, B, N;
-    double inv_du;
+    double per_hz;                // cells per metre and Hz: 1 / (c du)
+};
+
+// scale of the fixed-point grid, and whether the estimated one was too large
+struct Scale {
+    double scale;
+    int redo, pad;
 };
 
 __device__ __forceinline__ void pair_of(int64_t t, int& a, int& c) {
@@ -51,97 +64,140 @@ __device__ __forceinline__ void pair_of(int64_t t, int& a, int& c) {
     c = (int)(t - (int64_t)x * (x - 1) / 2);
 }
 
-struct Vis1 {
-    double re, im, w;
-    double pu, pv;
+// Grid position of a baseline (dx, dy) at frequency nu: the cell below it, the
+// fractions, and whether all eight cells it touches lie inside the grid.
+struct Cell {
+    int i, j;
+    double fu, fv;
     bool ok;
 };
-
-__device__ __forceinline__ Vis1 load_vis(const GridArgs& g, int b, int k, int a, int c, double dx, double dy,
-                                         double w) {
-    Vis1 r;
-    const int64_t nbl = (int64_t)g.Na * (g.Na + 1) / 2;
-    const int64_t bl = (int64_t)a * (a + 1) / 2 + c;
-    const float2* v = g.vis + (((int64_t)b * kP + k) * nbl + bl) * 4;
-    const float2 xx = v[0], yy = v[3];
-    r.re = 0.5 * ((double)xx.x + (double)yy.x);
-    r.im = 0.5 * ((double)xx.y + (double)yy.y);
-    r.w = w;
-    const double nu = g.freq[b * kP + k];
-    r.pu = dx * nu / kC * g.inv_du + 0.5 * g.N;
-    r.pv = dy * nu / kC * g.inv_du + 0.5 * g.N;
-    const double i0 = floor(r.pu), j0 = floor(r.pv);
-    r.ok = w > 0.0 && i0 >= 1.0 && j0 >= 1.0 && i0 <= g.N - 2.0 && j0 <= g.N - 2.0;
-    return r;
+__device__ __forceinline__ Cell cell_of(const GridArgs& g, double dx, double dy, double nu) {
+    const double s = nu * g.per_hz;
+    const double pu = dx * s + 0.5 * g.N, pv = dy * s + 0.5 * g.N;
+    const double i0 = floor(pu), j0 = floor(pv);
+    Cell c;
+    c.ok = i0 >= 1.0 && j0 >= 1.0 && i0 <= g.N - 2.0 && j0 <= g.N - 2.0;
+    c.i = c.ok ? (int)i0 : 0;
+    c.j = c.ok ? (int)j0 : 0;
+    c.fu = pu - i0;
+    c.fv = pv - j0;
+    return c;
 }
 
-// bound and normalisation: partial sums per block of 256 (subband, baseline)
-// threads, tree-reduced in LDS
-__global__ __launch_bounds__(256) void grid_bound_kernel(GridArgs g, double* __restrict__ part_abs,
-                                                         double* __restrict__ part_w, int64_t n_cross) {
-    __shared__ double ra[256], rw[256];
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    double sa = 0.0, sw = 0.0;
-    if (t < n_cross * g.B) {
-        const int b = (int)(t / n_cross);
+// XX and YY of channels k0 .. k0 + kBatch - 1 of one baseline, all loaded
+// before the first is used
+constexpr int kBatch = 8;
+struct Batch {
+    float2 xx[kBatch], yy[kBatch];
+};
+__device__ __forceinline__ Batch load_batch(const float2* __restrict__ v, int64_t ch_stride, int k0) {
+    Batch t;
+#pragma unroll
+    for (int e = 0; e < kBatch; ++e) {
+        t.xx[e] = v[(k0 + e) * ch_stride];
+        t.yy[e] = v[(k0 + e) * ch_stride + 3];
+    }
+    return t;
+}
+
+// sums of 2 w (|Re I| + |Im I|) and 2 w
+struct Sums {
+    double a, w;
+};
+// sums over the workgroup (NT threads), tree-reduced in a fixed order; the
+// result in thread 0
+template <int NT>
+__device__ __forceinline__ Sums block_sums(Sums s, Sums* lds) {
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        s.a += __shfl_xor(s.a, off, 64);
+        s.w += __shfl_xor(s.w, off, 64);
+    }
+    if ((tid & 63) == 0) lds[tid >> 6] = s;
+    __syncthreads();
+    if (tid == 0)
+        for (int v = 1; v < NT / 64; ++v) {
+            s.a += lds[v].a;
+            s.w += lds[v].w;
+        }
+    return s;
+}
+
+// Sample of the bound and clearing of the grid.  The sample: of every `stride`
+// groups of 4 consecutive baselines (4 records share a 128-byte line), all
+// subbands in line, one group; a thread takes 8 channels of a baseline.
+__global__ __launch_bounds__(256) void grid_estimate_kernel(GridArgs g, int64_t n_cross, int64_t n_sample, int stride,
+                                                            Sums* __restrict__ part,
+                                                            unsigned long long* __restrict__ grid, int64_t n_words) {
+    __shared__ Sums red[4];
+    Sums sum{0.0, 0.0};
+    const int64_t t0 = (int64_t)blockIdx.x * 256 + threadIdx.x, n_thr = (int64_t)gridDim.x * 256;
+    for (int64_t t = t0; t < n_sample * (kP / kBatch); t += n_thr) {
+        const int k0 = (int)(t / n_sample) * kBatch;
+        const int64_t q = t % n_sample, e = q / 4 * 4 * stride + q % 4;
+        if (e >= n_cross * g.B) continue;
+        const int b = (int)(e / n_cross);
         int a, c;
-        pair_of(t % n_cross, a, c);
+        pair_of(e % n_cross, a, c);
         const double dx = g.pos[a * 2] - g.pos[c * 2], dy = g.pos[a * 2 + 1] - g.pos[c * 2 + 1];
-        const double w = g.weights ? (double)g.weights[(int64_t)b * ((int64_t)g.Na * (g.Na + 1) / 2) +
-                                                       (int64_t)a * (a + 1) / 2 + c]
-                                   : 1.0;
-        for (int k = 0; k < kP; ++k) {
-            const Vis1 v = load_vis(g, b, k, a, c, dx, dy, w);
-            if (!v.ok) continue;
-            sa += 2.0 * w * (fabs(v.re) + fabs(v.im));
-            sw += 2.0 * w;
+        const int64_t nbl = (int64_t)g.Na * (g.Na + 1) / 2, bl = (int64_t)a * (a + 1) / 2 + c;
+        const double w = g.weights ? (double)g.weights[(int64_t)b * nbl + bl] : 1.0;
+        if (w <= 0.0) continue;
+        const Batch t8 = load_batch(g.vis + ((int64_t)b * kP * nbl + bl) * 4, nbl * 4, k0);
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k) {
+            if (!cell_of(g, dx, dy, g.freq[b * kP + k0 + k]).ok) continue;
+            sum.a += 2.0 * w * (fabs(0.5 * ((double)t8.xx[k].x + (double)t8.yy[k].x)) +
+                                fabs(0.5 * ((double)t8.xx[k].y + (double)t8.yy[k].y)));
         }
     }
-    ra[threadIdx.x] = sa;
-    rw[threadIdx.x] = sw;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) {
-            ra[threadIdx.x] += ra[threadIdx.x + s];
-            rw[threadIdx.x] += rw[threadIdx.x + s];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        part_abs[blockIdx.x] = ra[0];
-        part_w[blockIdx.x] = rw[0];
-    }
+    sum = block_sums<256>(sum, red);
+    if (threadIdx.x == 0) part[blockIdx.x] = sum;
+    for (int64_t i = t0; i < n_words; i += n_thr) grid[i] = 0ull;
 }
 
-// one block: totals in a fixed order; scale = 2^e with bound * scale < 2^61
-__global__ __launch_bounds__(256) void grid_total_kernel(const double* __restrict__ part_abs,
-                                                         const double* __restrict__ part_w, int n_part,
-                                                         double* __restrict__ scale, double* __restrict__ norm) {
-    __shared__ double ra[256], rw[256];
-    double sa = 0.0, sw = 0.0;
+// totals of n_part partial sums in a fixed order (one workgroup)
+__device__ __forceinline__ Sums total_sums(const Sums* __restrict__ part, int n_part, Sums* lds) {
+    Sums s{0.0, 0.0};
     for (int i = threadIdx.x; i < n_part; i += 256) {
-        sa += part_abs[i];
-        sw += part_w[i];
+        s.a += part[i].a;
+        s.w += part[i].w;
     }
-    ra[threadIdx.x] = sa;
-    rw[threadIdx.x] = sw;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) {
-            ra[threadIdx.x] += ra[threadIdx.x + s];
-            rw[threadIdx.x] += rw[threadIdx.x + s];
-        }
-        __syncthreads();
-    }
+    return block_sums<256>(s, lds);
+}
+
+// scale = 2^(bits - e) with bound < 2^e
+__device__ __forceinline__ double scale_for(double bound, int bits) {
+    int e = 0;
+    frexp(bound > 0.0 ? bound : 1.0, &e);
+    return ldexp(1.0, bits - e);
+}
+
+// Scale from the estimate: with a sample, 2^60 for the estimated bound, so that
+// the bound may be seven times the estimate; without (stride 1), 2^61.
+__global__ __launch_bounds__(256) void grid_scale_kernel(const Sums* __restrict__ part, int n_part, int stride,
+                                                         Scale* __restrict__ scale) {
+    __shared__ Sums red[4];
+    const Sums s = total_sums(part, n_part, red);
+    if (threadIdx.x == 0) *scale = Scale{scale_for(s.a * stride, stride > 1 ? 60 : 61), 0, 0};
+}
+
+// Totals of the gridding pass: the normalisation, and whether every cell must
+// fit 63 bits at the scale used.
+__global__ __launch_bounds__(256) void grid_verify_kernel(const Sums* __restrict__ part, int n_part,
+                                                          Scale* __restrict__ scale, double* __restrict__ norm) {
+    __shared__ Sums red[4];
+    const Sums s = total_sums(part, n_part, red);
     if (threadIdx.x == 0) {
-        int e = 0;
-        frexp(ra[0] > 0.0 ? ra[0] : 1.0, &e);              // bound < 2^e
-        scale[0] = ldexp(1.0, 61 - e);
-        norm[0] = rw[0];
+        norm[0] = s.w;
+        if (s.a * scale->scale >= 0x1.f8p62) *scale = Scale{scale_for(s.a, 61), 1, 0};
     }
 }
 
-__global__ void zero_words_kernel(unsigned long long* __restrict__ p, int64_t n) {
+// clears the grid if the pass has to be repeated
+__global__ void grid_clear_kernel(unsigned long long* __restrict__ p, int64_t n, const Scale* __restrict__ scale) {
+    if (!scale->redo) return;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         p[i] = 0ull;
 }
@@ -158,37 +214,40 @@ constexpr int kGB = 48;                      // antennas per block
 constexpr int kGW = 64;                      // LDS window side, cells
 constexpr int kGThreads = 1024;
 
+// (a sum that is zero, of flagged data say, adds nothing)
 __device__ __forceinline__ void add_fixed(unsigned long long* cell, double v, double scale) {
     if (v != 0.0) atomicAdd(cell, (unsigned long long)llrint(v * scale));
 }
 
-// one baseline a > c of subband b: its 64 channels through a 3 x 3 window of
-// cells in registers (float64), flushed to the LDS window or the grid when
-// the point leaves it and at the end
-__device__ __forceinline__ void grid_baseline(const GridArgs& g, int b, int a, int c, double scale,
+// One baseline a > c of subband b, channels k_begin .. k_end - 1: its
+// contributions are summed in registers (float64) while its point stays in one
+// cell, and the four corners flushed to the LDS window or the grid when it
+// leaves the cell and at the end; `sum` takes the bound and the weights.
+// (Across a subband a point moves by 0.3% of
+// its baseline's length, a cell or two at most; a 3 x 3 window of corners,
+// flushed less often, cost three times the vector instructions per visibility.)
+__device__ __forceinline__ void grid_baseline(const GridArgs& g, int b, int a, int c, int k_begin, int k_end, double scale,
                                               unsigned long long* __restrict__ grid, unsigned long long* win,
-                                              int i0w, int j0w) {
+                                              int i0w, int j0w, Sums& sum) {
     const double dx = g.pos[a * 2] - g.pos[c * 2], dy = g.pos[a * 2 + 1] - g.pos[c * 2 + 1];
-    const double w = g.weights ? (double)g.weights[(int64_t)b * ((int64_t)g.Na * (g.Na + 1) / 2) +
-                                                   (int64_t)a * (a + 1) / 2 + c]
-                               : 1.0;
+    const int64_t nbl = (int64_t)g.Na * (g.Na + 1) / 2, bl = (int64_t)a * (a + 1) / 2 + c;
+    const double w = g.weights ? (double)g.weights[(int64_t)b * nbl + bl] : 1.0;
     if (w <= 0.0) return;
     const int N = g.N;
-    double wr[3][3], wi[3][3];
-    int ai = 0, aj = 0;
-    bool open = false;
+    const float2* v = g.vis + ((int64_t)b * kP * nbl + bl) * 4;
+    double wr[2][2], wi[2][2];
+    int ai = 0, aj = 0;                                       // (0 is no cell of a gridded visibility)
     auto flush = [&]() {
 #pragma unroll
-        for (int y = 0; y < 3; ++y)
+        for (int y = 0; y < 2; ++y)
 #pragma unroll
-            for (int x = 0; x < 3; ++x) {
+            for (int x = 0; x < 2; ++x) {
                 const int i = ai + x, j = aj + y;
-                if (wr[y][x] == 0.0 && wi[y][x] == 0.0) continue;
                 const unsigned li = (unsigned)(i - i0w), lj = (unsigned)(j - j0w);
                 if (li < (unsigned)kGW && lj < (unsigned)kGW) {
                     unsigned long long* l = win + (lj * kGW + li) * 2;
-                    if (wr[y][x] != 0.0) atomicAdd(l, (unsigned long long)llrint(wr[y][x] * scale));
-                    if (wi[y][x] != 0.0) atomicAdd(l + 1, (unsigned long long)llrint(wi[y][x] * scale));
+                    add_fixed(l, wr[y][x], scale);
+                    add_fixed(l + 1, wi[y][x], scale);
                 } else {
                     // cells of gridded visibilities: 1 <= i, j <= N-1, mirrors likewise
                     unsigned long long* d = grid + ((int64_t)j * N + i) * 2;
@@ -200,42 +259,49 @@ __device__ __forceinline__ void grid_baseline(const GridArgs& g, int b, int a, i
                 }
             }
     };
-    for (int k = 0; k < kP; ++k) {
-        const Vis1 v = load_vis(g, b, k, a, c, dx, dy, w);
-        if (!v.ok) continue;
-        const int i0 = (int)floor(v.pu), j0 = (int)floor(v.pv);
-        const double fu = v.pu - i0, fv = v.pv - j0;
-        if (!open || i0 < ai || j0 < aj || i0 + 1 > ai + 2 || j0 + 1 > aj + 2) {
-            if (open) flush();
-            ai = i0;
-            aj = j0;
-            open = true;
+    for (int k0 = k_begin; k0 < k_end; k0 += kBatch) {
+        const Batch t = load_batch(v, nbl * 4, k0);
 #pragma unroll
-            for (int y = 0; y < 3; ++y)
+        for (int e = 0; e < kBatch; ++e) {
+            const Cell p = cell_of(g, dx, dy, g.freq[b * kP + k0 + e]);
+            if (!p.ok) continue;
+            if (p.i != ai || p.j != aj) {
+                if (ai) flush();
+                ai = p.i;
+                aj = p.j;
 #pragma unroll
-                for (int x = 0; x < 3; ++x) wr[y][x] = wi[y][x] = 0.0;
-        }
-        const int ox = i0 - ai, oy = j0 - aj;                 // 0 or 1
+                for (int y = 0; y < 2; ++y)
 #pragma unroll
-        for (int y = 0; y < 3; ++y) {
-            const double wy = y == oy ? 1.0 - fv : y == oy + 1 ? fv : 0.0;
+                    for (int x = 0; x < 2; ++x) wr[y][x] = wi[y][x] = 0.0;
+            }
+            const double re = 0.5 * w * ((double)t.xx[e].x + (double)t.yy[e].x);
+            const double im = 0.5 * w * ((double)t.xx[e].y + (double)t.yy[e].y);
+            sum.a += 2.0 * (fabs(re) + fabs(im));
+            sum.w += 2.0 * w;
 #pragma unroll
-            for (int x = 0; x < 3; ++x) {
-                const double wx = x == ox ? 1.0 - fu : x == ox + 1 ? fu : 0.0;
-                const double f = wx * wy * w;
-                wr[y][x] += f * v.re;
-                wi[y][x] += f * v.im;
+            for (int y = 0; y < 2; ++y) {
+                const double wy = y ? p.fv : 1.0 - p.fv;
+#pragma unroll
+                for (int x = 0; x < 2; ++x) {
+                    const double f = (x ? p.fu : 1.0 - p.fu) * wy;
+                    wr[y][x] += f * re;
+                    wi[y][x] += f * im;
+                }
             }
         }
     }
-    if (open) flush();
+    if (ai) flush();
 }
 
-__global__ __launch_bounds__(kGThreads) void grid_kernel(GridArgs g, const double* __restrict__ scale_p,
-                                                         unsigned long long* __restrict__ grid) {
+__global__ __launch_bounds__(kGThreads) void grid_kernel(GridArgs g, const Scale* __restrict__ scale_p,
+                                                         unsigned long long* __restrict__ grid, int n_split,
+                                                         Sums* __restrict__ part, int repeat) {
     __shared__ unsigned long long win[kGW * kGW * 2];
     __shared__ double msum[2];
-    const int b = blockIdx.y;
+    __shared__ Sums red[kGThreads / 64];
+    if (repeat && !scale_p->redo) return;
+    const int b = blockIdx.y / n_split;
+    const int k_begin = blockIdx.y % n_split * (kP / n_split), k_end = k_begin + kP / n_split;
     int ba, bc;                                               // block pair ba >= bc
     {
         const int t = blockIdx.x;
@@ -275,10 +341,11 @@ __global__ __launch_bounds__(kGThreads) void grid_kernel(GridArgs g, const doubl
     }
     __syncthreads();
     const double nu = g.freq[b * kP + kP / 2];
-    const double ur = msum[0] * nu / kC * g.inv_du + 0.5 * g.N;
-    const double vr = msum[1] * nu / kC * g.inv_du + 0.5 * g.N;
+    const double ur = msum[0] * nu * g.per_hz + 0.5 * g.N;
+    const double vr = msum[1] * nu * g.per_hz + 0.5 * g.N;
     const int i0w = (int)floor(ur) - kGW / 2, j0w = (int)floor(vr) - kGW / 2;
-    const double scale = scale_p[0];
+    const double scale = scale_p->scale;
+    Sums sum{0.0, 0.0};
 
     const int n_bl = ba == bc ? nA * (nA - 1) / 2 : nA * nC;
     for (int q = tid; q < n_bl; q += kGThreads) {
@@ -291,9 +358,10 @@ __global__ __launch_bounds__(kGThreads) void grid_kernel(GridArgs g, const doubl
             a = a0 + q / nC;
             c = c0 + q % nC;
         }
-        grid_baseline(g, b, a, c, scale, grid, win, i0w, j0w);
+        grid_baseline(g, b, a, c, k_begin, k_end, scale, grid, win, i0w, j0w, sum);
     }
-    __syncthreads();
+    sum = block_sums<kGThreads>(sum, red);                    // (its barrier also completes the window)
+    if (tid == 0 && !repeat) part[blockIdx.y * gridDim.x + blockIdx.x] = sum;
     const int N = g.N;
     for (int e = tid; e < kGW * kGW; e += kGThreads) {
         const long long re = (long long)win[e * 2], im = (long long)win[e * 2 + 1];
@@ -314,9 +382,9 @@ __global__ __launch_bounds__(kGThreads) void grid_kernel(GridArgs g, const doubl
 }
 
 // fixed point -> float2 grid (un-normalised), as the gridding's output
-__global__ void grid_to_float_kernel(const unsigned long long* __restrict__ grid, const double* __restrict__ scale_p,
+__global__ void grid_to_float_kernel(const unsigned long long* __restrict__ grid, const Scale* __restrict__ scale_p,
                                      float2* __restrict__ out, int64_t n) {
-    const double inv = 1.0 / scale_p[0];
+    const double inv = 1.0 / scale_p->scale;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const long long re = (long long)grid[i * 2], im = (long long)grid[i * 2 + 1];
         out[i] = make_float2((float)((double)re * inv), (float)((double)im * inv));
@@ -413,22 +481,46 @@ hipError_t launch_grid(const float2* vis, const int32_t* weights, const double* 
                        int N, double du, float2* grid_out, double* norm, void* ws, hipStream_t stream) {
     const int64_t n_cross = (int64_t)Na * (Na - 1) / 2;
     const int64_t n_thr = std::max<int64_t>(1, n_cross * B);
-    const int n_part = (int)ceil_div(n_thr, 256);
+    const int64_t n_part = ceil_div(n_thr, 256);              // pairs of doubles the workspace holds
     char* w = reinterpret_cast<char*>(ws);
     unsigned long long* fixed = reinterpret_cast<unsigned long long*>(w);
-    double* part_abs = reinterpret_cast<double*>(w + (size_t)N * N * 16 + (size_t)N * N * 16 + (size_t)N / 2 * 8);
-    double* part_w = part_abs + n_part;
-    double* scale = part_w + n_part;
-    GridArgs g{vis, weights, pos, freq, Na, B, N, 1.0 / du};
+    char* planes = w + (size_t)N * N * 16;                    // the imager's, free here
+    Sums* tail = reinterpret_cast<Sums*>(planes + (size_t)N * N * 16 + (size_t)N / 2 * 8);
+    Scale* scale = reinterpret_cast<Scale*>(tail + n_part);
+    GridArgs g{vis, weights, pos, freq, Na, B, N, 1.0 / (kC * du)};
     const int64_t n_words = (int64_t)N * N * 2;
-    hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(n_words, 256), 4096)), dim3(256),
-                       0, stream, fixed, n_words);
-    hipLaunchKernelGGL(grid_bound_kernel, dim3(n_part), dim3(256), 0, stream, g, part_abs, part_w, n_cross);
-    hipLaunchKernelGGL(grid_total_kernel, dim3(1), dim3(256), 0, stream, part_abs, part_w, n_part, scale, norm);
+    // A sample of 1 in 32 costs 3% of a pass over the visibilities; below 2^19
+    // baselines (times subbands) it thins out, below 2^15 all are taken.
+    const int stride = (int)std::min<int64_t>(32, std::max<int64_t>(1, n_thr >> 14));
+    const int64_t n_sample = ceil_div(n_thr, 4 * stride) * 4;
+    // workgroups: enough to clear the grid as well; their partial sums lie in
+    // the planes (read before the gridding pass writes its own there)
+    const int n_est = (int)std::min<int64_t>(std::max<int64_t>(ceil_div(n_sample * (kP / kBatch), 256), n_words / 1024),
+                                             std::min<int64_t>((int64_t)N * N, 4096));
+    Sums* est = reinterpret_cast<Sums*>(planes);
+    hipLaunchKernelGGL(grid_estimate_kernel, dim3(n_est), dim3(256), 0, stream, g, n_cross, n_sample, stride, est, fixed,
+                       n_words);
+    hipLaunchKernelGGL(grid_scale_kernel, dim3(1), dim3(256), 0, stream, est, n_est, stride, scale);
     const int n_blk = (int)ceil_div(Na, kGB);
-    if (n_cross > 0 && B > 0)
-        hipLaunchKernelGGL(grid_kernel, dim3((unsigned)(n_blk * (n_blk + 1) / 2), (unsigned)B), dim3(kGThreads), 0,
-                           stream, g, scale, fixed);
+    // Channels of a subband in 1, 2 or 4 workgroups: two workgroups run on a
+    // CU at a time, and 1.5 rounds of them or more even out (576 antennas x 8
+    // subbands 624 workgroups 709 us, 1248 630 us; 96 x 8 24 and 96 workgroups
+    // 146 and 81 us for the whole gridding); every part adds its window to the
+    // grid, so no more parts than that.
+    const int64_t n_pair = (int64_t)n_blk * (n_blk + 1) / 2;
+    const int64_t cap = std::max<int64_t>(n_part, (int64_t)N * N);
+    int n_split = 1;
+    while (n_split < 4 && n_pair * B * n_split < 768 && n_pair * B * n_split * 2 <= cap) n_split *= 2;
+    const int64_t n_wg = n_pair * B * n_split;
+    Sums* part = n_wg <= n_part ? tail : reinterpret_cast<Sums*>(planes);
+    const dim3 grid((unsigned)n_pair, (unsigned)(B * n_split));
+    const dim3 cgrid((unsigned)std::min<int64_t>(ceil_div(n_words, 256), 4096));
+    hipLaunchKernelGGL(grid_kernel, grid, dim3(kGThreads), 0, stream, g, scale, fixed, n_split, part, 0);
+    hipLaunchKernelGGL(grid_verify_kernel, dim3(1), dim3(256), 0, stream, part, (int)n_wg, scale, norm);
+    if (stride > 1) {
+        hipLaunchKernelGGL(grid_clear_kernel, cgrid, dim3(256), 0, stream, fixed, n_words, scale);
+        hipLaunchKernelGGL(grid_kernel, grid, dim3(kGThreads), 0, stream, g, scale, fixed, n_split, part, 1);
+    }
     hipLaunchKernelGGL(grid_to_float_kernel, dim3((unsigned)std::min<int64_t>(ceil_div((int64_t)N * N, 256), 4096)),
                        dim3(256), 0, stream, fixed, scale, grid_out, (int64_t)N * N);
     return hipGetLastError();

@@ -174,3 +174,37 @@ def test_full_size_aartfaac12(afc, dev):
         assert (ii, jj) == (2, 2)
     del V, grid
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("case", ["uniform", "sample misses the power", "zeros"])
+@pytest.mark.parametrize("Na,B,N", [(300, 1, 64), (97, 8, 128), (49, 3, 64)])
+def test_grid_scale_from_a_sample(afc, dev, Na, B, N, case):
+    """Above 2^15 baselines the fixed-point scale comes from a sample of the
+    visibilities (groups of 4 baselines at a stride): the grid equals the
+    oracle's where the sample is fair, where every sampled baseline is 1e-7 of
+    the others (the pass is then repeated with the exact scale), and where all
+    are zero."""
+    rng = np.random.default_rng(Na + B)
+    nbl, n_cross = Na * (Na + 1) // 2, Na * (Na - 1) // 2
+    V = np.zeros((B, 64, nbl, 2, 2, 2), np.float32)
+    if case != "zeros":
+        V[:] = rng.standard_normal(V.shape).astype(np.float32)
+    if case == "sample misses the power":
+        stride = min(32, max(1, (n_cross * B) >> 14))
+        a, c = np.tril_indices(Na)
+        cross = np.flatnonzero(a != c)
+        e = np.arange(n_cross * B)
+        hit = (e // 4) % stride == 0
+        for b in range(B):
+            V[b][:, cross[hit[b * n_cross:(b + 1) * n_cross]]] *= 1e-7
+    pos = rng.uniform(-40, 40, size=(Na, 2))
+    freq = _freqs(B)
+    wt = rng.integers(1, 5, size=(B, nbl)).astype(np.int32)
+    log(f"grid scale Na={Na} B={B} N={N} {case}")
+    im = afc.Imager(torch.from_numpy(pos).to(dev), B, N, 1.0)
+    args = (torch.from_numpy(V).to(dev), torch.from_numpy(freq).to(dev), torch.from_numpy(wt).to(dev))
+    grid = im.grid(*args)
+    G, norm = oracle.grid_visibilities(V, wt, pos, freq, N, 1.0)
+    assert im.norm.item() == norm
+    assert np.abs(_cg(grid) - G).max() <= 1e-6 * np.abs(G).max()
+    assert torch.equal(im.grid(*args), grid)
