@@ -162,3 +162,47 @@ def test_validity_full_size_sampled(afc, dev):
                 hi, lo = max(a, c), min(a, c)
                 assert Wt[b, hi * (hi + 1) // 2 + lo] == int(np.sum(v[i] & v[j]))
         log(f"  sb={b} antennas={ants} valid fraction {v.mean():.4f}")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "i8"])
+@pytest.mark.parametrize("S", [1, 8, 31, 66])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_zero_invalid_runs(afc, dev, dtype, S, offset):
+    """Every run of invalid spectra (random masks, all of a word, none) is
+    zeroed and nothing else, in a buffer at a 16-byte boundary and in one a
+    sample past it (single-sample stores)."""
+    B, Na = 2, 37
+    N, Sb, Wd = 2 * Na, (S + 7) // 8, (S + 31) // 32
+    rng = np.random.default_rng(S + offset)
+    v = rng.random((B, S, Na)) < rng.choice([0.0, 0.3, 0.5, 0.9, 1.0], size=(B, 1, Na))
+    bits = np.zeros((B, Wd, Na), np.uint32)
+    for s in range(S):
+        bits[:, s // 32] |= v[:, s].astype(np.uint32) << np.uint32(s % 32)
+    z0 = W.make_channelised(B, 64, S, N, dtype, seed=5, device=dev)
+    z0[z0 == 0] = 3
+    flat = torch.zeros(z0.numel() + 2, dtype=z0.dtype, device=dev)
+    z = flat[2 * offset:2 * offset + z0.numel()].view(z0.shape)
+    z.copy_(z0)
+    afc.zero_invalid(z, torch.from_numpy(bits.view(np.int32)).to(dev), S)
+    keep = np.ones((B, Sb * 8, N), bool)
+    keep[:, :S] = np.repeat(v, 2, axis=2)
+    keep = keep.reshape(B, Sb, 8, N).transpose(0, 1, 3, 2)[:, None, :, :, :, None]
+    before = z0.cpu().numpy()
+    np.testing.assert_array_equal(z.cpu().numpy(), np.where(keep, before, np.zeros_like(before)))
+    assert flat[:2 * offset].eq(0).all() and flat[2 * offset + z0.numel():].eq(0).all()
+
+
+@pytest.mark.parametrize("Na,S,Q,Ps,n_extra", [(3, 1, 1, 64, 0), (70, 45, 5000, 64, 0), (5, 33, 3, 256, -4),
+                                               (64, 64, 16, 64, -1), (2, 40, 1 << 20, 256, 3)])
+def test_validity_packet_sizes(afc, dev, Na, S, Q, Ps, n_extra):
+    """Packets of one sample to more than the whole subband, fewer or more of
+    them than the input holds, everything lost of one antenna."""
+    n_pk = max(1, -(-(S + 15) * Ps // Q) + n_extra)
+    rng = np.random.default_rng(Na)
+    pkt = (rng.random((2, n_pk, Na)) > min(0.2, 2.0 / n_pk)).astype(np.uint8) * 7
+    pkt[1, :, 0] = 0
+    got = _unpack(afc.validity(torch.from_numpy(pkt).to(dev), S, Q, Ps), S)
+    for b in range(2):
+        full = np.zeros((max(n_pk, -(-(S + 15) * Ps // Q)), Na), np.uint8)
+        full[:n_pk] = pkt[b]
+        np.testing.assert_array_equal(got[b], oracle.spectrum_validity(full, Q, Ps, 16, S))
