@@ -11,7 +11,7 @@
 // visibility is gridded only if all eight cells are inside the grid.
 //
 //  * grid_estimate_kernel: the sum of 2 w (|Re I| + |Im I|) over a sample of
-//    the gridded visibilities (every 32nd group of 4 baselines on large arrays,
+//    the gridded visibilities (every 64th group of 4 baselines on large arrays,
 //    all of them on small ones), reduced in a fixed order: an estimate of a
 //    bound on any cell, from which the fixed-point scale is taken.
 //  * grid_kernel: one workgroup per (subband, part of its channels, pair of
@@ -28,10 +28,10 @@
 //    allows (a sample that missed most of the power), it sets the exact scale
 //    and a flag, and a second clearing and gridding, which otherwise end at
 //    once, replace the grid.
-//  * imaging: (-1)^(p+q) modulation, radix-2 Stockham FFT of each row in LDS,
-//    transpose, row FFT again, and (-1)^(i+j) Re(.) / norm with the
-//    transpose back.
+//  * imaging: (-1)^(p+q) modulation, FFT of the rows with the transpose in its
+//    store, row FFT again, and (-1)^(i+j) Re(.) / norm with the transpose back.
 #include <algorithm>
+#include <type_traits>
 
 #include "afc_internal.h"
 
@@ -395,75 +395,149 @@ __global__ void grid_to_float_kernel(const unsigned long long* __restrict__ grid
 __device__ __forceinline__ float2 cmulf(float2 a, float2 b) {
     return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
+__device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
+__device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
+__device__ __forceinline__ float2 mul_mi(float2 a) { return make_float2(a.y, -a.x); }         // -i a
 
-__global__ void twiddle_kernel(float2* __restrict__ tw, int N) {
-    const int m = blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= N / 2) return;
-    const double ang = -2.0 * 3.14159265358979323846 * (double)m / (double)N;
-    tw[m] = make_float2((float)cos(ang), (float)sin(ang));
+// R-point DFT in place, natural order, R = 2, 4 or 8
+template <int R>
+__device__ __forceinline__ void dft(float2 (&x)[R]) {
+    if constexpr (R == 2) {
+        const float2 t = x[0];
+        x[0] = cadd(t, x[1]);
+        x[1] = csub(t, x[1]);
+    } else if constexpr (R == 4) {
+        const float2 a = cadd(x[0], x[2]), b = csub(x[0], x[2]), c = cadd(x[1], x[3]), d = mul_mi(csub(x[1], x[3]));
+        x[0] = cadd(a, c);
+        x[1] = cadd(b, d);
+        x[2] = csub(a, c);
+        x[3] = csub(b, d);
+    } else {
+        constexpr float r2 = 0.70710678118654752440f;   // sqrt(1/2)
+        float2 e[4] = {x[0], x[2], x[4], x[6]}, o[4] = {x[1], x[3], x[5], x[7]};
+        dft<4>(e);
+        dft<4>(o);
+        o[1] = make_float2(r2 * (o[1].x + o[1].y), r2 * (o[1].y - o[1].x));
+        o[2] = mul_mi(o[2]);
+        o[3] = make_float2(r2 * (o[3].y - o[3].x), -r2 * (o[3].x + o[3].y));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            x[k] = cadd(e[k], o[k]);
+            x[k + 4] = csub(e[k], o[k]);
+        }
+    }
 }
 
-// Forward DFT of each row of `data` (N points, N a power of two) in place:
-// X[k] = sum_n x[n] exp(-2 pi i k n / N).  Radix-2 Stockham: with sub-DFTs
-// of size ns done, butterfly j (< N/2) takes x[j] and x[j + N/2], rotates
-// the second by exp(-2 pi i (j mod ns) / (2 ns)) and writes the sum and the
-// difference to positions (j / ns) 2 ns + j mod ns and that + ns.
-// Optional (-1)^(row + column) modulation on load.
-__global__ __launch_bounds__(256) void fft_rows_kernel(float2* __restrict__ data, const float2* __restrict__ tw,
-                                                       int N, int log2N, int modulate) {
-    extern __shared__ float2 buf[];
-    float2* x = buf;
-    float2* y = buf + N;
-    const int row = blockIdx.x;
-    float2* r = data + (int64_t)row * N;
-    for (int i = threadIdx.x; i < N; i += blockDim.x) {
-        float2 v = r[i];
-        if (modulate && ((row + i) & 1)) v = make_float2(-v.x, -v.y);
-        x[i] = v;
+// Rows per workgroup of the N-point transform: enough that the transposed
+// store writes 64 bytes (2048 points; 128 KB of LDS) and a workgroup has at
+// least one wave, few enough that 256 workgroups result where N allows.
+template <int N>
+constexpr int fft_rows() { return N >= 4096 ? 2 : N >= 2048 ? 8 : N >= 512 ? 4 : N >= 128 ? 1024 / N : 32; }
+constexpr int kFftPer = 16;                      // points per thread
+
+// Forward DFT of rows, X[k] = sum_n x[n] exp(-2 pi i n k / N), with the
+// transpose fused into the store: out[k][row].  Stockham passes of radix 8
+// (the last 4 or 2) over registers and one LDS buffer: with sub-DFTs of size
+// ns done, butterfly j takes x[j + r N / R], rotates it by exp(-2 pi i r (j mod
+// ns) / (R ns)) and writes its outputs to (j / ns) R ns + j mod ns + r ns.
+// kFirst: input the gridding's grid, modulated by (-1)^(row + column), output
+// float2; otherwise output float, (-1)^(row + k) Re(.) / norm.  Bound by the
+// memory traffic and by latency: 2048^2 takes 40 us for both transforms (five
+// passes over 32 MB); radix-2 passes, twiddles, transposes and a copy in
+// launches of their own took 111 us.
+template <int N, bool kFirst>
+__global__ __launch_bounds__(fft_rows<N>() * N / kFftPer) void fft_kernel(const float2* __restrict__ in,
+                                                                          void* __restrict__ out,
+                                                                          const double* __restrict__ norm_p) {
+    constexpr int kRows = fft_rows<N>(), kThr = kRows * N / kFftPer;
+    // one element of padding per 8, so that butterflies' stores (8 elements
+    // apart) meet all banks; rows 8 elements apart, for the transposed reads
+    constexpr int kRS = N + N / 8 + 8;
+    __shared__ float2 buf[kRows * kRS];
+    __shared__ float2 tw[N / 2];
+    const int tid = threadIdx.x;
+    // rows of one XCD are neighbours, whose stores share lines
+    const int per = gridDim.x / 8;
+    const int w = per ? (int)((blockIdx.x & 7) * per + (blockIdx.x >> 3)) : (int)blockIdx.x;
+    const int row0 = w * kRows;
+    auto at = [](int row, int i) { return row * kRS + i + (i >> 3); };
+    for (int m = tid; m < N / 2; m += kThr) {
+        double sn, cs;
+        sincospi(-2.0 * (double)m / (double)N, &sn, &cs);
+        tw[m] = make_float2((float)cs, (float)sn);
     }
-    __syncthreads();
-    const int half = N / 2;
-    for (int l = 0; l < log2N; ++l) {
-        const int ns = 1 << l;
-        for (int j = threadIdx.x; j < half; j += blockDim.x) {
-            const int k = j & (ns - 1);
-            const float2 a = x[j];
-            const float2 b = cmulf(x[j + half], tw[k << (log2N - 1 - l)]);
-            const int o = ((j >> l) << (l + 1)) + k;
-            y[o] = make_float2(a.x + b.x, a.y + b.y);
-            y[o + ns] = make_float2(a.x - b.x, a.y - b.y);
+    auto pass = [&](auto r_tag, int ns, bool first) {
+        constexpr int R = decltype(r_tag)::value, kB = kFftPer / R;
+        float2 v[kB][R];
+#pragma unroll
+        for (int b = 0; b < kB; ++b) {
+            const int id = tid + b * kThr, row = id / (N / R), j = id % (N / R);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int i = j + r * (N / R);
+                if (first) {
+                    float2 x = in[(int64_t)(row0 + row) * N + i];
+                    if (kFirst && ((row0 + row + i) & 1)) x = make_float2(-x.x, -x.y);
+                    v[b][r] = x;
+                } else {
+                    v[b][r] = buf[at(row, i)];
+                }
+            }
+        }
+        __syncthreads();                                      // all reads done (and, first, the twiddles written)
+#pragma unroll
+        for (int b = 0; b < kB; ++b) {
+            const int id = tid + b * kThr, row = id / (N / R), j = id % (N / R), k = j & (ns - 1);
+            if (!first) {
+                const int step = k * (N / R / ns);
+#pragma unroll
+                for (int r = 1; r < R; ++r) {
+                    const int m = r * step;                   // below N
+                    const float2 t = tw[m & (N / 2 - 1)];
+                    v[b][r] = cmulf(v[b][r], m & (N / 2) ? make_float2(-t.x, -t.y) : t);
+                }
+            }
+            dft<R>(v[b]);
+            const int o = (j - k) * R + k;
+#pragma unroll
+            for (int r = 0; r < R; ++r) buf[at(row, o + r * ns)] = v[b][r];
         }
         __syncthreads();
-        float2* t = x;
-        x = y;
-        y = t;
+    };
+    constexpr int kLog = __builtin_ctz(N);
+    using R8 = std::integral_constant<int, 8>;
+    pass(R8{}, 1, true);
+    int ns = 8;
+#pragma unroll
+    for (int p = 1; p < kLog / 3; ++p, ns *= 8) pass(R8{}, ns, false);
+    if constexpr (kLog % 3 == 1) pass(std::integral_constant<int, 2>{}, ns, false);
+    if constexpr (kLog % 3 == 2) pass(std::integral_constant<int, 4>{}, ns, false);
+    float inv = 1.0f;
+    if constexpr (!kFirst) {
+        const double nv = norm_p[0];
+        inv = (float)(1.0 / (nv > 0.0 ? nv : 1.0));
     }
-    for (int i = threadIdx.x; i < N; i += blockDim.x) r[i] = x[i];
+#pragma unroll
+    for (int e = 0; e < kFftPer; ++e) {
+        const int id = tid + e * kThr, row = id % kRows, k = id / kRows;
+        const float2 v = buf[at(row, k)];
+        const int64_t o = (int64_t)k * N + row0 + row;
+        if constexpr (kFirst) {
+            reinterpret_cast<float2*>(out)[o] = v;
+        } else {
+            const float f = v.x * inv;
+            reinterpret_cast<float*>(out)[o] = ((k + row0 + row) & 1) ? -f : f;
+        }
+    }
 }
 
-// out[c][r] = in[r][c] for an N x N float2 matrix; 32 x 32 tiles via LDS.
-// finalize: out is float, (-1)^(r+c) Re(in[r][c]) / norm.
-template <bool kFinal>
-__global__ __launch_bounds__(256) void transpose_kernel(const float2* __restrict__ in, void* __restrict__ out, int N,
-                                                        const double* __restrict__ norm_p) {
-    __shared__ float2 tile[32][33];
-    const int bx = blockIdx.x * 32, by = blockIdx.y * 32;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;       // 32 x 8
-    for (int y = ty; y < 32; y += 8) tile[y][tx] = in[(int64_t)(by + y) * N + bx + tx];
-    __syncthreads();
-    if constexpr (kFinal) {
-        const double nv = norm_p[0];
-        const float inv = (float)(1.0 / (nv > 0.0 ? nv : 1.0));
-        float* o = reinterpret_cast<float*>(out);
-        for (int y = ty; y < 32; y += 8) {
-            const int orow = bx + y, ocol = by + tx;                   // element in[ocol][orow]
-            const float v = tile[tx][y].x * inv;
-            o[(int64_t)orow * N + ocol] = ((orow + ocol) & 1) ? -v : v;
-        }
-    } else {
-        float2* o = reinterpret_cast<float2*>(out);
-        for (int y = ty; y < 32; y += 8) o[(int64_t)(bx + y) * N + by + tx] = tile[tx][y];
-    }
+template <int N>
+hipError_t launch_fft2(const float2* grid, const double* norm, float* image, float2* plane, hipStream_t stream) {
+    constexpr int kRows = fft_rows<N>(), kThr = kRows * N / kFftPer;
+    static_assert(N % kRows == 0 && kThr >= 64 && kThr <= 1024, "rows per workgroup");
+    hipLaunchKernelGGL((fft_kernel<N, true>), dim3(N / kRows), dim3(kThr), 0, stream, grid, (void*)plane, nullptr);
+    hipLaunchKernelGGL((fft_kernel<N, false>), dim3(N / kRows), dim3(kThr), 0, stream, plane, (void*)image, norm);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -472,8 +546,8 @@ size_t imaging_workspace_bytes(int Na, int B, int N) {
     const int64_t n_cross = (int64_t)Na * (Na - 1) / 2;
     const int64_t n_part = ceil_div(std::max<int64_t>(1, n_cross * B), 256);
     return (size_t)N * N * 16                      // fixed-point grid
-           + (size_t)N * N * 8 * 2                 // two float2 planes
-           + (size_t)N / 2 * 8                     // twiddles
+           + (size_t)N * N * 8 * 2                 // the imager's plane, partial sums of the gridding
+           + (size_t)N / 2 * 8
            + (size_t)n_part * 16 + 64;             // partial sums, scale
 }
 
@@ -489,9 +563,11 @@ hipError_t launch_grid(const float2* vis, const int32_t* weights, const double* 
     Scale* scale = reinterpret_cast<Scale*>(tail + n_part);
     GridArgs g{vis, weights, pos, freq, Na, B, N, 1.0 / (kC * du)};
     const int64_t n_words = (int64_t)N * N * 2;
-    // A sample of 1 in 32 costs 3% of a pass over the visibilities; below 2^19
-    // baselines (times subbands) it thins out, below 2^15 all are taken.
-    const int stride = (int)std::min<int64_t>(32, std::max<int64_t>(1, n_thr >> 14));
+    // 1 in 64 of the baselines (times subbands), from 2^19 of them on, of the
+    // fewer at least 2^13, below 2^14 all.  At 576 antennas x 8 subbands the
+    // sample's scattered lines and the clearing take 30 us; 1 in 32 48 us, 1 in
+    // 128 23 us.
+    const int stride = (int)std::min<int64_t>(64, std::max<int64_t>(1, n_thr >> 13));
     const int64_t n_sample = ceil_div(n_thr, 4 * stride) * 4;
     // workgroups: enough to clear the grid as well; their partial sums lie in
     // the planes (read before the gridding pass writes its own there)
@@ -527,22 +603,18 @@ hipError_t launch_grid(const float2* vis, const int32_t* weights, const double* 
 }
 
 hipError_t launch_image(const float2* grid, const double* norm, float* image, int N, void* ws, hipStream_t stream) {
-    int log2N = 0;
-    while ((1 << log2N) < N) ++log2N;
-    char* w = reinterpret_cast<char*>(ws);
-    float2* a = reinterpret_cast<float2*>(w + (size_t)N * N * 16);
-    float2* b = a + (size_t)N * N;
-    float2* tw = b + (size_t)N * N;
-    hipLaunchKernelGGL(twiddle_kernel, dim3((unsigned)ceil_div(N / 2, 256)), dim3(256), 0, stream, tw, N);
-    hipError_t e = hipMemcpyAsync(a, grid, (size_t)N * N * sizeof(float2), hipMemcpyDeviceToDevice, stream);
-    if (e != hipSuccess) return e;
-    const size_t lds = (size_t)2 * N * sizeof(float2);
-    const dim3 tgrid((unsigned)(N / 32), (unsigned)(N / 32));
-    hipLaunchKernelGGL(fft_rows_kernel, dim3(N), dim3(256), lds, stream, a, tw, N, log2N, 1);
-    hipLaunchKernelGGL(transpose_kernel<false>, tgrid, dim3(256), 0, stream, a, b, N, norm);
-    hipLaunchKernelGGL(fft_rows_kernel, dim3(N), dim3(256), lds, stream, b, tw, N, log2N, 0);
-    hipLaunchKernelGGL(transpose_kernel<true>, tgrid, dim3(256), 0, stream, b, image, N, norm);
-    return hipGetLastError();
+    float2* plane = reinterpret_cast<float2*>(reinterpret_cast<char*>(ws) + (size_t)N * N * 16);
+    switch (N) {
+        case 32: return launch_fft2<32>(grid, norm, image, plane, stream);
+        case 64: return launch_fft2<64>(grid, norm, image, plane, stream);
+        case 128: return launch_fft2<128>(grid, norm, image, plane, stream);
+        case 256: return launch_fft2<256>(grid, norm, image, plane, stream);
+        case 512: return launch_fft2<512>(grid, norm, image, plane, stream);
+        case 1024: return launch_fft2<1024>(grid, norm, image, plane, stream);
+        case 2048: return launch_fft2<2048>(grid, norm, image, plane, stream);
+        case 4096: return launch_fft2<4096>(grid, norm, image, plane, stream);
+        default: return hipErrorInvalidValue;                 // refused by the entry point
+    }
 }
 
 }  // namespace afc
