@@ -242,3 +242,13 @@ def test_solver_tile_edges_match_oracle(afc, dev, Na, form):
     np.testing.assert_array_equal(got, again)
     gz, _ = _solve_gpu_w(afc, dev, V, M, g0, 0, fl, wt)
     np.testing.assert_allclose(gz, _ref(g0.astype(np.complex64).astype(np.complex128)), rtol=0, atol=1e-6)
+
+
+# channels held in registers up to 64, read again above; one workgroup takes 64
+# baselines, a partial sum of stage 1 4096
+@pytest.mark.parametrize("Na,P", [(1, 3), (2, 1), (10, 7), (11, 64), (12, 65), (30, 130), (90, 8), (91, 9)])
+def test_sigma_clip_channel_and_baseline_edges(afc, dev, Na, P):
+    V = _rfi_vis(P, Na, seed=Na * 100 + P) if Na > 1 else np.ones((P, 1, 2, 2, 2), np.float32)
+    log(f"sigma clip edges Na={Na} P={P}")
+    f = afc.sigma_clip(torch.from_numpy(V).to(dev), 3.0).cpu().numpy()
+    _compare_flags(f, oracle.sigma_clip(V, 3.0), V, 3.0)
