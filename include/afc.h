@@ -434,7 +434,8 @@ AFC_API int afc_image_from_grid(int32_t grid_size, const void* grid, const doubl
  *                    choices {"key": [tile, workgroups per CU, split]} (read,
  *                    and written after tuning; split = 1 puts int8 and fp16
  *                    subbands in correlator launches of their own), or NULL
- *                    for the built-in default (128, 2, 0).  Tuning runs kernels on the current
+ *                    for a tile width by the plan's sizes (the rule of
+ *                    afc_correlate) and split = 0.  Tuning runs kernels on the current
  *                    device at creation time on scratch memory it allocates
  *                    and frees there.
  * afc_plan_workspace_bytes  bytes of the caller-owned workspace that holds

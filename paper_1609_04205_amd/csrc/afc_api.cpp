@@ -955,6 +955,13 @@ AFC_API int afc_plan_create(const afc_dims* d, const afc_dtype* dtype_per_sb, co
     }
     if (any0) {
         TuneChoice ch;
+        std::vector<int32_t> dt0, S0;
+        for (int b = 0; b < B; ++b)
+            if (p->dt[b] != AFC_F32) {
+                dt0.push_back(p->dt[b]);
+                S0.push_back(p->S[b]);
+            }
+        ch.tile = xengine_tile(p->N, dt0.data(), S0.data(), (int)dt0.size());
         if (tune_cache_path && *tune_cache_path) {
             auto cache = read_cache(tune_cache_path);
             const std::string key = tune_key(*p);

@@ -128,6 +128,9 @@ hipError_t launch_xengine_list(const void* z_ws, void* vis, int32_t* weights, co
                                const XSubband* sbs_dev, const XWork* work_dev, const XcdRanges& ranges,
                                int N, int Na, int mode, int tile, hipStream_t stream);
 int xengine_list_grid(const XcdRanges& ranges);
+// tile width of the int8 / fp16 correlator for N receivers and subbands of
+// types dt and lengths S
+int xengine_tile(int N, const int32_t* dt, const int32_t* S, int n_subbands);
 // tile width of the fp32 correlator for N receivers and its subband count
 int xengine_f32_tile(int N, int n_subbands);
 // Fill `bytes` (a multiple of 4) of device memory with hashed bytes that are

@@ -1372,7 +1372,10 @@ __device__ __forceinline__ void xtile(const char* __restrict__ z, char* __restri
 }
 
 template <int DT, int TILE>
-__global__ __launch_bounds__((tile_threads<DT, TILE>()), 2) void xengine_kernel(XArgs a) {
+// (64-wide int8 / fp16 tiles hold 32 accumulator registers: four workgroups per
+// CU, the others two, or one of 8 waves)
+__global__ __launch_bounds__((tile_threads<DT, TILE>()), (DT != AFC_F32 && TILE == 64 ? 4 : 2)) void xengine_kernel(
+    XArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[lds_bytes<DT, TILE>()];
     // XCD-aware order: consecutive workgroup ids go round-robin over the 8
     // XCDs; give each XCD a contiguous range of work so that the tiles of one
@@ -1483,6 +1486,36 @@ int xengine_f32_tile(int N, int n_subbands) {
     return t64 < t128 ? 64 : 128;
 }
 
+// int8 / fp16 tile width.  A round (two 128-wide or four 64-wide off-diagonal
+// tiles on every CU) takes a fixed part, the tiles' first loads and stores, and
+// one per spectrum; a diagonal tile 0.6 (128) or 0.75 (64) of an off-diagonal
+// one.  64-wide tiles move twice the operand bytes per product, but start and
+// store sooner, fill the CUs on small launches and waste less at the array's
+// edge.  Fitted in us over 16 to 1152 receivers, 1 to 16 subbands, 200 and 1000
+// spectra; e.g. int8 150 receivers x 4 subbands x 1000 spectra 48 us (128) and
+// 29 us (64), 600 x 1 x 1000 38 and 25 us, 200 x 16 x 1000 163 and 191 us, 1152
+// x 2 x 1000 375 and 462 us.
+int xengine_tile(int N, const int32_t* dt, const int32_t* S, int n_subbands) {
+    int dev = 0, n_cu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu <= 0)
+        n_cu = 256;
+    auto time = [&](int tile) {
+        const double side = (double)ceil_div(N, tile);
+        const double area = side * (side - 1.0) / 2.0 + (tile == 128 ? 0.6 : 0.75) * side;
+        const double rounds = area * kP / ((tile == 128 ? 2.0 : 4.0) * n_cu);           // of one subband
+        double sum = 0.0, longest = 0.0;
+        for (int b = 0; b < n_subbands; ++b) {
+            const double t = dt[b] == AFC_I8 ? (tile == 128 ? 9.9 + 0.0266 * S[b] : 3.6 + 0.0195 * S[b])
+                                             : (tile == 128 ? 15.5 + 0.0465 * S[b] : 6.3 + 0.0347 * S[b]);
+            sum += t * rounds;
+            longest = std::max(longest, t);
+        }
+        return sum + 0.3 * longest;
+    };
+    return time(64) < time(128) ? 64 : 128;
+}
+
 hipError_t launch_xengine(const XLaunch& l, hipStream_t stream) {
     XArgs a{};
     a.z = reinterpret_cast<const char*>(l.z);
@@ -1497,7 +1530,9 @@ hipError_t launch_xengine(const XLaunch& l, hipStream_t stream) {
     a.Sb = l.Sb;
     a.B = l.B;
     a.P = kP;
-    const int tile = l.dt == AFC_F32 ? xengine_f32_tile(l.N, l.B) : 128;
+    int32_t dts[AFC_MAX_SUBBANDS];
+    std::fill_n(dts, l.B, (int32_t)l.dt);
+    const int tile = l.dt == AFC_F32 ? xengine_f32_tile(l.N, l.B) : xengine_tile(l.N, dts, l.S_host, l.B);
     a.n_tiles_side = (int)ceil_div(l.N, tile);
     a.n_tiles = a.n_tiles_side * (a.n_tiles_side + 1) / 2;
     const int64_t total = (int64_t)a.n_tiles * kP * l.B;
@@ -1506,16 +1541,17 @@ hipError_t launch_xengine(const XLaunch& l, hipStream_t stream) {
     a.per_xcd = (int)ceil_div(total, 8);
     for (int b = 0; b < l.B; ++b) a.S[b] = l.S_host[b];
     const dim3 grid((unsigned)(a.per_xcd * 8));
+#define AFC_X_LAUNCH(DT)                                                                                          \
+    if (tile == 128)                                                                                              \
+        hipLaunchKernelGGL((xengine_kernel<DT, 128>), grid, dim3(tile_threads<DT, 128>()), 0, stream, a);           \
+    else                                                                                                          \
+        hipLaunchKernelGGL((xengine_kernel<DT, 64>), grid, dim3(tile_threads<DT, 64>()), 0, stream, a);
     switch (l.dt) {
-        case AFC_I8: hipLaunchKernelGGL((xengine_kernel<AFC_I8, 128>), grid, dim3(kThreads), 0, stream, a); break;
-        case AFC_F16: hipLaunchKernelGGL((xengine_kernel<AFC_F16, 128>), grid, dim3(kThreads), 0, stream, a); break;
-        default:
-            if (tile == 128)
-                hipLaunchKernelGGL((xengine_kernel<AFC_F32, 128>), grid, dim3(tile_threads<AFC_F32, 128>()), 0, stream, a);
-            else
-                hipLaunchKernelGGL((xengine_kernel<AFC_F32, 64>), grid, dim3(tile_threads<AFC_F32, 64>()), 0, stream, a);
-            break;
+        case AFC_I8: AFC_X_LAUNCH(AFC_I8) break;
+        case AFC_F16: AFC_X_LAUNCH(AFC_F16) break;
+        default: AFC_X_LAUNCH(AFC_F32) break;
     }
+#undef AFC_X_LAUNCH
     return hipGetLastError();
 }
 

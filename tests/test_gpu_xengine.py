@@ -283,3 +283,25 @@ def test_f32_values_out_of_the_split_range(afc, dev, B, Na, bad):
                 m = np.abs(x).max(0)
                 err = np.abs((v[fin, 0] + 1j * v[fin, 1]) - e[fin])
                 assert np.all(err <= 1e-5 * S * (m[2 * a[k] + p] * m[2 * c[k] + q])[fin])
+
+
+@pytest.mark.parametrize("dtype", ["i8", "f16", "f32"])
+@pytest.mark.parametrize("Na,S,B", [(100, 1000, 12), (128, 700, 10), (48, 1500, 8), (33, 1200, 24)])
+def test_tile_width_does_not_change_results(afc, dev, dtype, Na, S, B):
+    """The tile width follows the launch's size: one of these subbands alone
+    takes 64-wide tiles (fp32 at 100 and 128 antennas 128-wide), all of them
+    together 128-wide ones (at 66 receivers 64-wide).  The sums run over the
+    spectra in the same order either way: identical bit for bit, flags,
+    weights and ragged lengths among them."""
+    log(f"xengine tile widths {dtype} Na={Na} S={S} B={B}")
+    z = W.make_channelised(B, 64, S, 2 * Na, dtype, seed=Na, device=dev)
+    fl = torch.zeros((B, Na), dtype=torch.uint8, device=dev)
+    fl[:, 5] = 1
+    S_sb = [S - 13 * b for b in range(B)]
+    v, w = afc.correlate(z, n_spectra=S, n_spectra_per_sb=S_sb, flags=fl)
+    for b in (0, B - 1):
+        v1, w1 = afc.correlate(z[b:b + 1].contiguous(), n_spectra=S, n_spectra_per_sb=S_sb[b:b + 1], flags=fl[b:b + 1])
+        assert torch.equal(v1[0].view(torch.int32), v[b].view(torch.int32)), b
+        assert torch.equal(w1[0], w[b])
+    del z, v
+    torch.cuda.empty_cache()
