@@ -346,17 +346,36 @@ __device__ __forceinline__ float2 unflagged_model(float2 m, bool flagged) {
 // them; one polarisation at a time, because the sums of two take the
 // registers of a wave per SIMD.
 template <bool kW>
-__global__ __launch_bounds__(kThreads) void cal_solve_tiles_kernel(int Na, int n_tiles, const float2* __restrict__ V,
+__global__ __launch_bounds__(kThreads) void cal_solve_tiles_kernel(int Na, int P, int nT, const float2* __restrict__ V,
                                                                    const float2* __restrict__ M,
                                                                    const float2* __restrict__ g,
                                                                    double2* __restrict__ rowpart,
                                                                    double2* __restrict__ colpart,
                                                                    double* __restrict__ rowd, double* __restrict__ cold,
-                                                                   const float* __restrict__ wt) {
+                                                                   const float* __restrict__ wt, int reverse) {
     __shared__ double col_lds[4][kTileA][3];
-    const int t = blockIdx.x, ch = blockIdx.y, pol = blockIdx.z;
+    // Whole tiles first, then the array's last rows, then the diagonal (5/8 of
+    // the elements): the launch is one to two rounds of workgroups, and the
+    // short ones even out its end.  Every second step takes them in the opposite
+    // order, on the same XCD (workgroup id modulo 8): what the caches still hold
+    // from the end of a step is then the first to be read of the next instead
+    // of being pushed out first.  (Together 1043 -> 1009 us for the solve of 288
+    // antennas x 64 channels with flagging, 3.15 -> 2.99 ms at 576.)
+    const int n8 = (int)gridDim.x >> 3, id8 = (int)blockIdx.x >> 3;
+    const int id = reverse && id8 < n8 ? ((n8 - 1 - id8) << 3) | (int)(blockIdx.x & 7) : (int)blockIdx.x;
+    const int P2 = 2 * P, k = id / P2, ch = id % P2 >> 1, pol = id & 1;
+    const int n_whole = (nT - 1) * (nT - 2) / 2;
     int ti, tj;
-    tile_rc(t, ti, tj);
+    if (k < n_whole) {
+        tile_rc(k, ti, tj);
+        ++ti;
+    } else if (k < n_whole + nT - 1) {
+        ti = nT - 1;
+        tj = k - n_whole;
+    } else {
+        ti = tj = k - n_whole - (nT - 1);
+    }
+    const int t = ti * (ti + 1) / 2 + tj, n_tiles = nT * (nT + 1) / 2;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int c4 = tid & 15, r4 = tid >> 4;
     const int64_t nbl = (int64_t)Na * (Na + 1) / 2;
@@ -707,12 +726,13 @@ hipError_t launch_calibrate_solve(int Na, int P, const float2* V, const float2* 
         gc = ga;
     }
     for (int it = 1; it <= n_iter; ++it) {
+        const dim3 grid((unsigned)(n_tiles * P * 2));
         if (wt)
-            hipLaunchKernelGGL(cal_solve_tiles_kernel<true>, dim3(n_tiles, P, 2), dim3(kThreads), 0, stream, Na, n_tiles,
-                               Vc, Mc, gc, rowpart, colpart, rowd, cold, wt);
+            hipLaunchKernelGGL(cal_solve_tiles_kernel<true>, grid, dim3(kThreads), 0, stream, Na, P, nT, Vc, Mc, gc,
+                               rowpart, colpart, rowd, cold, wt, it % 2 == 0);
         else
-            hipLaunchKernelGGL(cal_solve_tiles_kernel<false>, dim3(n_tiles, P, 2), dim3(kThreads), 0, stream, Na, n_tiles,
-                               Vc, Mc, gc, rowpart, colpart, rowd, cold, nullptr);
+            hipLaunchKernelGGL(cal_solve_tiles_kernel<false>, grid, dim3(kThreads), 0, stream, Na, P, nT, Vc, Mc, gc,
+                               rowpart, colpart, rowd, cold, nullptr, it % 2 == 0);
         hipLaunchKernelGGL(cal_step_kernel, dim3((unsigned)nT, P, 2), dim3(kTileA), 0, stream, Na, nT, n_tiles, rowpart,
                            colpart, rowd, cold, gc, ga, (int)(it % 2 == 0));
         gc = ga;
