@@ -1,6 +1,6 @@
 // Device helpers shared by the channelisers: complex float2 arithmetic,
-// 4- and 16-point DFTs, quad broadcasts, the int8 requantiser and the
-// sample store into the channelised layout.
+// 4- and 16-point DFTs, the int8 requantiser and the sample store into the
+// channelised layout.
 #pragma once
 
 #include <hip/hip_fp16.h>
@@ -50,14 +50,6 @@ __device__ __forceinline__ void dft16(float2 (&a)[16]) {
     a[3 + 12] = cmul(a[3 + 12], make_float2(-c8, s8));  // 9
 #pragma unroll
     for (int ga = 0; ga < 4; ++ga) dft4(a[4 * ga], a[4 * ga + 1], a[4 * ga + 2], a[4 * ga + 3]);
-}
-
-// value of the lane at (this lane xor M) inside the quad, M = 1 or 2
-// (DPP quad_perm [1,0,3,2] or [2,3,0,1])
-template <int M>
-__device__ __forceinline__ float quad_xor(float v) {
-    constexpr int ctrl = M == 1 ? (1 | (0 << 2) | (3 << 4) | (2 << 6)) : (2 | (3 << 2) | (0 << 4) | (1 << 6));
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), ctrl, 0xF, 0xF, false));
 }
 
 // clamp(rint(y * gain), -127, 127) of the exact product (one rounding, ties

@@ -69,6 +69,63 @@ struct FineArgs {
     float gain;
 };
 
+// The radix-4 over the lane quad with the lane exchange as the first operand
+// of the multiply-adds.  The compiler folds such an operand into an addition
+// but not into a multiply-add, and issued 16 moves per spectrum and lane beside
+// them: 5% of the kernel's vector instructions, which bound it (2160 -> 2095 us
+// for 4 subbands x 1152 receivers x 762 spectra, int8; the operations and their
+// order are the same, so are the bits).  The s_nop is the wait that a lane
+// exchange needs after the instruction that wrote its operand.
+
+// u += s * (u of the lane at j ^ 2), eight values
+__device__ __forceinline__ void quad_fma8(float (&u)[4][2], float s) {
+#if defined(__HIP_DEVICE_COMPILE__)
+#define AFC_DPP " quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+    asm("s_nop 1\n\t"
+        "v_fmac_f32_dpp %0, %0, %8" AFC_DPP
+        "v_fmac_f32_dpp %1, %1, %8" AFC_DPP
+        "v_fmac_f32_dpp %2, %2, %8" AFC_DPP
+        "v_fmac_f32_dpp %3, %3, %8" AFC_DPP
+        "v_fmac_f32_dpp %4, %4, %8" AFC_DPP
+        "v_fmac_f32_dpp %5, %5, %8" AFC_DPP
+        "v_fmac_f32_dpp %6, %6, %8" AFC_DPP
+        "v_fmac_f32_dpp %7, %7, %8" AFC_DPP
+        : "+&v"(u[0][0]), "+&v"(u[0][1]), "+&v"(u[1][0]), "+&v"(u[1][1]), "+&v"(u[2][0]), "+&v"(u[2][1]),
+          "+&v"(u[3][0]), "+&v"(u[3][1])
+        : "v"(s));
+#undef AFC_DPP
+#endif
+}
+
+// o += b * (e of the lane at j ^ 1), complex, four values
+__device__ __forceinline__ void quad_cfma4(float2 (&o)[4], const float (&e)[4][2], float2 b, float nby) {
+#if defined(__HIP_DEVICE_COMPILE__)
+#define AFC_DPP " quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+    asm("s_nop 1\n\t"
+        "v_fmac_f32_dpp %0, %8, %16" AFC_DPP
+        "v_fmac_f32_dpp %1, %9, %16" AFC_DPP
+        "v_fmac_f32_dpp %2, %10, %16" AFC_DPP
+        "v_fmac_f32_dpp %3, %11, %16" AFC_DPP
+        "v_fmac_f32_dpp %4, %12, %16" AFC_DPP
+        "v_fmac_f32_dpp %5, %13, %16" AFC_DPP
+        "v_fmac_f32_dpp %6, %14, %16" AFC_DPP
+        "v_fmac_f32_dpp %7, %15, %16" AFC_DPP
+        "v_fmac_f32_dpp %0, %9, %18" AFC_DPP
+        "v_fmac_f32_dpp %1, %8, %17" AFC_DPP
+        "v_fmac_f32_dpp %2, %11, %18" AFC_DPP
+        "v_fmac_f32_dpp %3, %10, %17" AFC_DPP
+        "v_fmac_f32_dpp %4, %13, %18" AFC_DPP
+        "v_fmac_f32_dpp %5, %12, %17" AFC_DPP
+        "v_fmac_f32_dpp %6, %15, %18" AFC_DPP
+        "v_fmac_f32_dpp %7, %14, %17" AFC_DPP
+        : "+&v"(o[0].x), "+&v"(o[0].y), "+&v"(o[1].x), "+&v"(o[1].y), "+&v"(o[2].x), "+&v"(o[2].y), "+&v"(o[3].x),
+          "+&v"(o[3].y)
+        : "v"(e[0][0]), "v"(e[0][1]), "v"(e[1][0]), "v"(e[1][1]), "v"(e[2][0]), "v"(e[2][1]), "v"(e[3][0]),
+          "v"(e[3][1]), "v"(b.x), "v"(b.y), "v"(nby));
+#undef AFC_DPP
+#endif
+}
+
 template <int DT, bool kVec4, bool kOne>
 __global__ __launch_bounds__(kThreadsF) void ppf_fine_kernel(FineArgs a, Tw64 tw64) {
     __shared__ __attribute__((aligned(16))) float2 lds[kQF * kQS];
@@ -117,9 +174,10 @@ __global__ __launch_bounds__(kThreadsF) void ppf_fine_kernel(FineArgs a, Tw64 tw
     const float2 be = j == 2 ? make_float2(0.0f, -1.0f) : make_float2(1.0f, 0.0f);
     // with the twiddle folded in (al and be are 1, -1, i or -i: exact)
     const float2 alw = cmul(al, tw_o), bew = cmul(be, tw_o);
+    // the taps carry s1, so that step 1 adds -s1 times the partner's value
     float h[16];
 #pragma unroll
-    for (int t = 0; t < 16; ++t) h[t] = a.taps[t * kPF + p];
+    for (int t = 0; t < 16; ++t) h[t] = s1 * a.taps[t * kPF + p];
     // first receiver of this lane's four; loads clamped into the row (the
     // clamped receivers are never stored)
     const int rb = i0 + 4 * rh;
@@ -184,18 +242,15 @@ __global__ __launch_bounds__(kThreadsF) void ppf_fine_kernel(FineArgs a, Tw64 tw
                         for (int t = 0; t < 16; ++t) acc = fmaf(h[t], win[r][c][(q + t) & 15], acc);
                         u[r][c] = acc;
                     }
+                // step 1: with the lane at j ^ 2
+                quad_fma8(u, -s1);
+                // step 2: with the lane at j ^ 1,
+                // (al e + be f) exp(-2 pi i p1 k1o / 256)
                 float2 o[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    // step 1: with the lane at j ^ 2
-                    const float e0 = fmaf(s1, u[r][0], quad_xor<2>(u[r][0]));
-                    const float e1 = fmaf(s1, u[r][1], quad_xor<2>(u[r][1]));
-                    // step 2: with the lane at j ^ 1
-                    const float f0 = quad_xor<1>(e0), f1 = quad_xor<1>(e1);
-                    // (al e + be f) exp(-2 pi i p1 k1o / 256)
-                    o[r].x = alw.x * e0 - alw.y * e1 + bew.x * f0 - bew.y * f1;
-                    o[r].y = alw.x * e1 + alw.y * e0 + bew.x * f1 + bew.y * f0;
-                }
+                for (int r = 0; r < 4; ++r)
+                    o[r] = make_float2(fmaf(alw.x, u[r][0], -(alw.y * u[r][1])), fmaf(alw.y, u[r][0], alw.x * u[r][1]));
+                quad_cfma4(o, u, bew, -bew.y);
                 float4* dst = reinterpret_cast<float4*>(lds + ql * kQS + k1o * kK1S + p1 * kNiF + 4 * rh);
                 dst[0] = make_float4(o[0].x, o[0].y, o[1].x, o[1].y);
                 dst[1] = make_float4(o[2].x, o[2].y, o[3].x, o[3].y);
