@@ -123,14 +123,17 @@ struct XcdRanges {
 };
 // One workgroup per work item (workgroup ids go round-robin over the 8
 // XCDs); mode 0: int8 / fp16 subbands with tile-wide tiles (128 or 64),
-// mode 1: fp32 subbands (128 or 64).
+// mode 1: fp32 subbands (128 or 64).  groups > 1 (xengine_i8_groups) only for
+// 64-wide tiles of int8 subbands.
 hipError_t launch_xengine_list(const void* z_ws, void* vis, int32_t* weights, const uint8_t* flags,
                                const XSubband* sbs_dev, const XWork* work_dev, const XcdRanges& ranges,
-                               int N, int Na, int mode, int tile, hipStream_t stream);
+                               int N, int Na, int mode, int tile, int groups, hipStream_t stream);
 int xengine_list_grid(const XcdRanges& ranges);
 // tile width of the int8 / fp16 correlator for N receivers and subbands of
 // types dt and lengths S
 int xengine_tile(int N, const int32_t* dt, const int32_t* S, int n_subbands);
+// groups of waves per 64-wide int8 tile of a launch of this many workgroups
+int xengine_i8_groups(int64_t n_workgroups);
 // tile width of the fp32 correlator for N receivers and its subband count
 int xengine_f32_tile(int N, int n_subbands);
 // Fill `bytes` (a multiple of 4) of device memory with hashed bytes that are

@@ -21,7 +21,8 @@
 // gives wave w the column blocks w and 7-w, nine blocks on or below the
 // diagonal each.  64-wide tiles: four row blocks x column block w off the
 // diagonal, ten blocks split 3/3/2/2 on it.  Tiles wholly above the diagonal
-// are never launched.
+// are never launched.  Where a launch leaves the CUs mostly empty, two or four
+// such sets of waves share a 64-wide tile's spectra (kGroups).
 // int8 / fp16: the row panel of a tile streams through LDS in stages of one
 // MFMA k-step (direct global-to-LDS loads of the block layout
 // [block][receiver][8 spectra], XOR-swizzled 16-byte chunks so that the MFMA
@@ -382,7 +383,7 @@ constexpr int last_use_b(int j) {
     return last;
 }
 
-template <int DT, int TILE, class J>
+template <int DT, int TILE, int kGroups, class J>
 __device__ __forceinline__ void xtile_mm16(const char* __restrict__ z, char* __restrict__ vis_ch,
                                            int32_t* __restrict__ w_sb, const uint8_t* __restrict__ fl_sb,
                                            int N, int Na, int S, int ti, int tj, bool write_weights,
@@ -409,13 +410,20 @@ __device__ __forceinline__ void xtile_mm16(const char* __restrict__ z, char* __r
     static_assert(RS <= 4, "register ring of at most four stages");
     constexpr int BUF = PANEL + (BD || kDiagJob ? 0 : PANEL_B);
 
-    const int tid = threadIdx.x, lane = tid & 63, lc = lane & 15, lg = lane >> 4;
+    // stage st of group kg is stage st * kGroups + kg of the integration
+    const int kg = kGroups > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads) : 0;
+    const int tid = threadIdx.x - kg * kThreads, lane = tid & 63, lc = lane & 15, lg = lane >> 4;
     const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i0 = ti * TILE, j0 = tj * TILE;
     const bool diag = ti == tj;
     const int nb = (S + kSBlk - 1) / kSBlk;
     const int tail_valid = S - (nb - 1) * kSBlk;
-    const int n_st = (nb + kStg * RS - 1) / (kStg * RS) * RS;
+    const int n_st = (nb + kStg * kGroups * RS - 1) / (kStg * kGroups * RS) * RS;
+    static_assert(kGroups == 1 || (DT == AFC_I8 && !BD), "exact sums, added in the epilogue of the LDS-staged form");
+    static_assert(kGroups == 1 || kGroups * NP * 8 * kThreads * 4 <= kGroups * lds_bytes<DT, TILE>(),
+                  "the groups' sums fit their rings");
+    char* const ring = lds_raw + kg * lds_bytes<DT, TILE>();
+    auto whole_st = [&](int st) { return kGroups == 1 ? st : st * kGroups + kg; };
     const int n_final = n_st - RS;
     // this lane's K chunk: spectrum block lbl of the stage, plane q of it
     const int lbl = DT == AFC_I8 ? lg : lg >> 1;
@@ -447,7 +455,7 @@ __device__ __forceinline__ void xtile_mm16(const char* __restrict__ z, char* __r
     };
     // zero the spectra >= S of an operand chunk of stage st
     auto mask_op = [&](int st, uint4& v) {
-        const int blk = st * kStg + lbl;
+        const int blk = whole_st(st) * kStg + lbl;
         if (blk < nb - 1 || (blk == nb - 1 && tail_valid == kSBlk)) return;
         v = mask_tail<DT>(v, q, blk == nb - 1 ? tail_valid : 0);
     };
@@ -489,10 +497,11 @@ __device__ __forceinline__ void xtile_mm16(const char* __restrict__ z, char* __r
     // main loop of the register-ring form issues.
     auto issue_panel = [&](auto clamp_tag, int st, char* panel, int c, int src) {
         char* dst = panel + (c * kThreads + wid * 64) * 16;
-        int voff = src, soff = st * stage_bytes;
-        if (decltype(clamp_tag)::value && (st + 1) * kStg > nb) {
+        const int ws = whole_st(st);
+        int voff = src, soff = ws * stage_bytes;
+        if (decltype(clamp_tag)::value && (ws + 1) * kStg > nb) {
             const int bl = (tid + c * kThreads) / (TILE * PLANES);
-            voff += (min(st * kStg + bl, nb - 1) - bl) * N * RB;
+            voff += (min(ws * kStg + bl, nb - 1) - bl) * N * RB;
             soff = 0;
         }
         buffer_load_lds16(z, z_bytes, dst, voff, soff);
@@ -513,7 +522,7 @@ __device__ __forceinline__ void xtile_mm16(const char* __restrict__ z, char* __r
         for (int x = 0; x < NBO; ++x) bdir[slot][x] = buffer_load16(z, z_bytes, b_off[x] + dv, soff);
     };
     auto issue_a = [&](auto clamp_tag, int st) {
-        char* buf = lds_raw + (st % NB) * BUF;
+        char* buf = ring + (st % NB) * BUF;
 #pragma unroll
         for (int c = 0; c < CPT; ++c) issue_panel(clamp_tag, st, buf, c, src_a[c]);
         if constexpr (!BD) {
@@ -533,8 +542,8 @@ __device__ __forceinline__ void xtile_mm16(const char* __restrict__ z, char* __r
         else wait_vmcnt_runtime<CPT + CPT_B, kDmaDepth>(later);
     };
     auto wait_landed_bd = [&](auto later_tag) { wait_vmcnt<(CPT + NBO) * decltype(later_tag)::value>(); };
-    auto buf_a = [&](int st) -> const char* { return lds_raw + (st % NB) * BUF; };
-    auto buf_b = [&](int st) -> const char* { return lds_raw + (st % NB) * BUF + (diag ? 0 : PANEL); };
+    auto buf_a = [&](int st) -> const char* { return ring + (st % NB) * BUF; };
+    auto buf_b = [&](int st) -> const char* { return ring + (st % NB) * BUF + (diag ? 0 : PANEL); };
 
     // this stage's operands: rows as read, columns as read and J-swapped;
     // each is replaced by the next stage's right after its last MFMA
@@ -645,6 +654,31 @@ __device__ __forceinline__ void xtile_mm16(const char* __restrict__ z, char* __r
                   std::true_type{}, std::true_type{});
     });
     lds_barrier();
+    if constexpr (kGroups > 1) {
+        // group g finishes the blocks p with p % kGroups == g: the other
+        // groups' sums come through LDS, added in the order of the groups
+        acc_t* const part = reinterpret_cast<acc_t*>(lds_raw);
+        auto slot = [&](int g, int p, int c) -> acc_t& { return part[((g * NP + p) * 2 + c) * kThreads + tid]; };
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+            if (p % kGroups != kg) {
+                slot(kg, p, 0) = accR[p];
+                slot(kg, p, 1) = accI[p];
+            }
+        lds_barrier();
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+            if (p % kGroups == kg) {
+                acc_t r{}, i{};
+#pragma unroll
+                for (int g = 0; g < kGroups; ++g) {
+                    r += g == kg ? accR[p] : slot(g, p, 0);
+                    i += g == kg ? accI[p] : slot(g, p, 1);
+                }
+                accR[p] = r;
+                accI[p] = i;
+            }
+    }
 
     // ---- epilogue: 2 x 2 polarisation blocks of antennas a >= b.  Rows
     // 4 (lane / 16) + {0, 1} and {2, 3} of a lane are the two polarisations
@@ -774,6 +808,7 @@ __device__ __forceinline__ void xtile_mm16(const char* __restrict__ z, char* __r
             for (int k = 0; k < 2; ++k) frow[i][k] = fl_sb ? flag_of(i0 + am[i] * 16 + 4 * lg + 2 * k) : false;
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
+            if (p % kGroups != kg) continue;
             const int ia = J::T.IA[p], ib = J::T.IB[p];
 #pragma unroll
             for (int r = 0; r < 4; r += 2)
@@ -1306,7 +1341,7 @@ __device__ __forceinline__ void xtile_f32(const char* __restrict__ z, char* __re
 // One tile of one (subband, channel).  int8 / fp16: each wave computes its
 // job of 16 x 16 blocks (diagonal tiles spread their lower-triangle blocks
 // over the waves); fp32: 2 x 2 waves of one 32 x 32 block each.
-template <int DT, int TILE>
+template <int DT, int TILE, int kGroups = 1>
 __device__ __forceinline__ void xtile(const char* __restrict__ z, char* __restrict__ vis_ch,
                                       int32_t* __restrict__ w_sb, const uint8_t* __restrict__ fl_sb,
                                       int N, int Na, int S, int ti, int tj, bool write_weights, char* lds_raw) {
@@ -1335,9 +1370,9 @@ __device__ __forceinline__ void xtile(const char* __restrict__ z, char* __restri
             }
         }
     } else {
-        const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % (kGroups > 1 ? 4 : 64);
         auto run = [&](auto job, const int (&am)[8], const int (&bn)[2]) {
-            xtile_mm16<DT, TILE, decltype(job)>(z, vis_ch, w_sb, fl_sb, N, Na, S, ti, tj, write_weights, lds_raw,
+            xtile_mm16<DT, TILE, kGroups, decltype(job)>(z, vis_ch, w_sb, fl_sb, N, Na, S, ti, tj, write_weights, lds_raw,
                                                 am, bn);
         };
         if constexpr (TILE == 128) {
@@ -1371,12 +1406,12 @@ __device__ __forceinline__ void xtile(const char* __restrict__ z, char* __restri
     }
 }
 
-template <int DT, int TILE>
+template <int DT, int TILE, int kGroups>
 // (64-wide int8 / fp16 tiles hold 32 accumulator registers: four workgroups per
 // CU, the others two, or one of 8 waves)
-__global__ __launch_bounds__((tile_threads<DT, TILE>()), (DT != AFC_F32 && TILE == 64 ? 4 : 2)) void xengine_kernel(
+__global__ __launch_bounds__((tile_threads<DT, TILE>() * kGroups), (DT != AFC_F32 && TILE == 64 ? 4 : 2)) void xengine_kernel(
     XArgs a) {
-    __shared__ __attribute__((aligned(16))) char lds[lds_bytes<DT, TILE>()];
+    __shared__ __attribute__((aligned(16))) char lds[kGroups * lds_bytes<DT, TILE>()];
     // XCD-aware order: consecutive workgroup ids go round-robin over the 8
     // XCDs; give each XCD a contiguous range of work so that the tiles of one
     // channel share that XCD's L2.  (One tile per workgroup: the hardware
@@ -1396,7 +1431,7 @@ __global__ __launch_bounds__((tile_threads<DT, TILE>()), (DT != AFC_F32 && TILE 
     char* vis = a.vis + ((int64_t)sb * a.P + ch) * nbl * 4 * 8;
     int32_t* wsb = a.weights ? a.weights + (int64_t)sb * nbl : nullptr;
     const uint8_t* fl = a.flags ? a.flags + (int64_t)sb * a.Na : nullptr;
-    xtile<DT, TILE>(z, vis, wsb, fl, a.N, a.Na, a.S[sb], ti, tj, wsb != nullptr && ch == 0, lds);
+    xtile<DT, TILE, kGroups>(z, vis, wsb, fl, a.N, a.Na, a.S[sb], ti, tj, wsb != nullptr && ch == 0, lds);
 }
 
 // Batched form: one workgroup per work item of a host-built list; each item
@@ -1406,15 +1441,16 @@ __global__ __launch_bounds__((tile_threads<DT, TILE>()), (DT != AFC_F32 && TILE 
 // round-robin over the 8 XCDs and the list holds each XCD's items (whole
 // channels, cost-balanced across XCDs) contiguously, so that the hardware
 // dispatcher keeps the tiles in flight on an XCD a window of few channels.
-template <int MODE, int TILE, int WPC>
-__global__ __launch_bounds__((MODE == 1 ? tile_threads<AFC_F32, TILE>() : kThreads), WPC) void xengine_list_kernel(
+// kGroups > 1: a list of int8 subbands only.
+template <int MODE, int TILE, int WPC, int kGroups = 1>
+__global__ __launch_bounds__((MODE == 1 ? tile_threads<AFC_F32, TILE>() : kGroups * kThreads), WPC) void xengine_list_kernel(
     const char* __restrict__ z_ws, char* __restrict__ vis, int32_t* __restrict__ weights,
     const uint8_t* __restrict__ flags, const XSubband* __restrict__ sbs, const XWork* __restrict__ work,
     XcdRanges r, int N, int Na) {
     constexpr int kLds = MODE == 0 ? (lds_bytes<AFC_I8, TILE>() > lds_bytes<AFC_F16, TILE>() ? lds_bytes<AFC_I8, TILE>()
                                                                                             : lds_bytes<AFC_F16, TILE>())
                                    : lds_bytes<AFC_F32, TILE>();
-    __shared__ __attribute__((aligned(16))) char lds[kLds];
+    __shared__ __attribute__((aligned(16))) char lds[kGroups * kLds];
     const int x = blockIdx.x & 7, k = blockIdx.x >> 3;
     if (k >= r.count[x]) return;
     const int64_t nbl = (int64_t)Na * (Na + 1) / 2;
@@ -1427,10 +1463,10 @@ __global__ __launch_bounds__((MODE == 1 ? tile_threads<AFC_F32, TILE>() : kThrea
     if constexpr (MODE == 0) {
         if (sd.dt == AFC_I8) {
             const char* z = z_ws + sd.z_off + (int64_t)wk.ch * sd.Sb * N * kSBlk * 2;
-            xtile<AFC_I8, TILE>(z, vis_ch, wsb, fl, N, Na, sd.S, wk.ti, wk.tj, ww, lds);
+            xtile<AFC_I8, TILE, kGroups>(z, vis_ch, wsb, fl, N, Na, sd.S, wk.ti, wk.tj, ww, lds);
         } else {
             const char* z = z_ws + sd.z_off + (int64_t)wk.ch * sd.Sb * N * kSBlk * 4;
-            xtile<AFC_F16, TILE>(z, vis_ch, wsb, fl, N, Na, sd.S, wk.ti, wk.tj, ww, lds);
+            if constexpr (kGroups == 1) xtile<AFC_F16, TILE>(z, vis_ch, wsb, fl, N, Na, sd.S, wk.ti, wk.tj, ww, lds);
         }
     } else {
         const char* z = z_ws + sd.z_off + (int64_t)wk.ch * sd.Sb * N * kSBlk * 8;
@@ -1516,6 +1552,24 @@ int xengine_tile(int N, const int32_t* dt, const int32_t* S, int n_subbands) {
     return time(64) < time(128) ? 64 : 128;
 }
 
+// Groups of four waves per 64-wide int8 tile, which share its stages (int8
+// only: its sums are exact in any order; a float sum would depend on the
+// launch's size).  A workgroup alone on its CU takes about 0.24 us per stage
+// whatever the depth of its ring: one wave per SIMD, and a stage is a chain of
+// barrier, LDS reads and MFMAs.  With four groups four chains run on the CU.
+// Four while the launch has no more workgroups than the card CUs, two while it
+// has fewer than two per CU; from there on the CUs hold several workgroups
+// anyway.  In us for one, two and four groups at 3051 spectra: 16 receivers x
+// 1 subband (64 workgroups) 25.8, 18.0, 15.1; 96 x 1 (192) 28.2, 19.2, 16.6;
+// 150 x 1 (384) 35.1, 27.8, 32.5; 150 x 2 (768) 40.8, 43.4, 48.8.
+int xengine_i8_groups(int64_t n_workgroups) {
+    int dev = 0, n_cu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu <= 0)
+        n_cu = 256;
+    return n_workgroups <= n_cu ? 4 : n_workgroups < 2 * n_cu ? 2 : 1;
+}
+
 hipError_t launch_xengine(const XLaunch& l, hipStream_t stream) {
     XArgs a{};
     a.z = reinterpret_cast<const char*>(l.z);
@@ -1541,16 +1595,25 @@ hipError_t launch_xengine(const XLaunch& l, hipStream_t stream) {
     a.per_xcd = (int)ceil_div(total, 8);
     for (int b = 0; b < l.B; ++b) a.S[b] = l.S_host[b];
     const dim3 grid((unsigned)(a.per_xcd * 8));
-#define AFC_X_LAUNCH(DT)                                                                                          \
-    if (tile == 128)                                                                                              \
-        hipLaunchKernelGGL((xengine_kernel<DT, 128>), grid, dim3(tile_threads<DT, 128>()), 0, stream, a);           \
-    else                                                                                                          \
-        hipLaunchKernelGGL((xengine_kernel<DT, 64>), grid, dim3(tile_threads<DT, 64>()), 0, stream, a);
-    switch (l.dt) {
-        case AFC_I8: AFC_X_LAUNCH(AFC_I8) break;
-        case AFC_F16: AFC_X_LAUNCH(AFC_F16) break;
-        default: AFC_X_LAUNCH(AFC_F32) break;
+    const int groups = tile == 64 && l.dt == AFC_I8 ? xengine_i8_groups(total) : 1;
+#define AFC_X_LAUNCH(DT, TILE, GROUPS)                                                                            \
+    hipLaunchKernelGGL((xengine_kernel<DT, TILE, GROUPS>), grid, dim3(tile_threads<DT, TILE>() * GROUPS), 0,      \
+                       stream, a)
+#define AFC_X_WIDTHS(DT)                                                                                          \
+    if (tile == 128) AFC_X_LAUNCH(DT, 128, 1);                                                                    \
+    else AFC_X_LAUNCH(DT, 64, 1);
+    if (groups == 4) {
+        AFC_X_LAUNCH(AFC_I8, 64, 4);
+    } else if (groups == 2) {
+        AFC_X_LAUNCH(AFC_I8, 64, 2);
+    } else {
+        switch (l.dt) {
+            case AFC_I8: AFC_X_WIDTHS(AFC_I8) break;
+            case AFC_F16: AFC_X_WIDTHS(AFC_F16) break;
+            default: AFC_X_WIDTHS(AFC_F32) break;
+        }
     }
+#undef AFC_X_WIDTHS
 #undef AFC_X_LAUNCH
     return hipGetLastError();
 }
@@ -1563,7 +1626,7 @@ int xengine_list_grid(const XcdRanges& r) {
 
 hipError_t launch_xengine_list(const void* z_ws, void* vis, int32_t* weights, const uint8_t* flags,
                                const XSubband* sbs_dev, const XWork* work_dev, const XcdRanges& ranges, int N,
-                               int Na, int mode, int tile, hipStream_t stream) {
+                               int Na, int mode, int tile, int groups, hipStream_t stream) {
     const char* z = reinterpret_cast<const char*>(z_ws);
     char* v = reinterpret_cast<char*>(vis);
     const int g = xengine_list_grid(ranges);
@@ -1578,9 +1641,15 @@ hipError_t launch_xengine_list(const void* z_ws, void* vis, int32_t* weights, co
     else if (tile == 128)
         hipLaunchKernelGGL((xengine_list_kernel<0, 128, 2>), grid, block, 0, stream, z, v, weights, flags, sbs_dev,
                            work_dev, ranges, N, Na);
-    else
+    else if (groups == 1)
         hipLaunchKernelGGL((xengine_list_kernel<0, 64, 4>), grid, block, 0, stream, z, v, weights, flags, sbs_dev,
                            work_dev, ranges, N, Na);
+    else if (groups == 2)
+        hipLaunchKernelGGL((xengine_list_kernel<0, 64, 4, 2>), grid, dim3(2 * kThreads), 0, stream, z, v, weights,
+                           flags, sbs_dev, work_dev, ranges, N, Na);
+    else
+        hipLaunchKernelGGL((xengine_list_kernel<0, 64, 4, 4>), grid, dim3(4 * kThreads), 0, stream, z, v, weights,
+                           flags, sbs_dev, work_dev, ranges, N, Na);
     return hipGetLastError();
 }
 

@@ -107,6 +107,17 @@ def test_plan_small_mixed(afc, dev, tmp_path):
     assert (tmp_path / "tune.json").exists()
 
 
+@pytest.mark.parametrize("S_list", [[300], [300, 47]])
+def test_plan_small_int8(afc, dev, S_list):
+    """int8 subbands alone in a small plan: four (192 work items) or two (384)
+    groups of waves per tile."""
+    log(f"plan small int8 {S_list}")
+    flags = np.zeros((len(S_list), 40), np.uint8)
+    flags[0, [2, 39]] = 1
+    info = _run_plan(afc, dev, 40, S_list, ["i8"] * len(S_list), flags)
+    assert info.tile == 64 and info.n_work_items == 192 * len(S_list)
+
+
 def test_plan_f32_subbands(afc, dev):
     log("plan fp32 + int8")
     Na = 24

@@ -305,3 +305,25 @@ def test_tile_width_does_not_change_results(afc, dev, dtype, Na, S, B):
         assert torch.equal(w1[0], w[b])
     del z, v
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("Na,B", [(33, 1), (8, 4), (48, 1), (48, 2), (75, 1), (8, 8)])
+@pytest.mark.parametrize("S", [1, 31, 32, 33, 128, 129, 401])
+def test_int8_groups_of_a_small_launch(afc, dev, Na, B, S):
+    """A launch that leaves the CUs mostly empty gives each int8 tile four or
+    two groups of waves, which share its stages of 32 spectra: fewer stages
+    than groups, one each, remainders, ragged lengths, flags and weights, up to
+    the workgroup counts where the groups change (256 and 512)."""
+    log(f"xengine int8 groups Na={Na} B={B} S={S}")
+    z = W.make_channelised(B, 64, S, 2 * Na, "i8", seed=Na + S, device=dev)
+    S_sb = [max(1, S - 5 * b) for b in range(B)]
+    fl_np = np.zeros((B, Na), np.uint8)
+    fl_np[:, 3] = 1
+    vis, w = afc.correlate(z, n_spectra=S, n_spectra_per_sb=S_sb, flags=torch.from_numpy(fl_np).to(dev))
+    vis_np, w_np = vis.cpu().numpy(), w.cpu().numpy()
+    zn = W.blocked_to_natural(z.cpu(), z.shape[2] * 8).numpy()
+    for b in {0, B - 1}:
+        for ch in (0, 41, 63):
+            V, W_ = oracle.xcorr_int(zn[b, ch, :S_sb[b]], fl_np[b])
+            np.testing.assert_array_equal(vis_np[b, ch].astype(np.int64), V)
+            np.testing.assert_array_equal(w_np[b], W_)
