@@ -521,8 +521,18 @@ __device__ __forceinline__ void xtile_mm16(const char* __restrict__ z, char* __r
 #pragma unroll
         for (int x = 0; x < NBO; ++x) bdir[slot][x] = buffer_load16(z, z_bytes, b_off[x] + dv, soff);
     };
-    auto issue_a = [&](auto clamp_tag, int st) {
-        char* buf = ring + (st % NB) * BUF;
+    // ring slot of stage st + ahead, where st is the stage being multiplied and
+    // cur its slot (a remainder by the fp16 ring's 5 is a chain of scalar
+    // multiplications in every stage; counting on: 96 receivers x 1 subband x
+    // 3051 spectra 60.1 -> 54.9 us, 150 x 2 82.3 -> 78.4 us, large ones the same)
+    int cur = 0;
+    auto slot_at = [&](int st, auto ahead_tag) -> int {
+        constexpr int ahead = decltype(ahead_tag)::value;
+        if constexpr (BD || (NB & (NB - 1)) == 0) return (st + ahead) % NB;
+        else return cur + ahead >= NB ? cur + ahead - NB : cur + ahead;
+    };
+    auto issue_a = [&](auto clamp_tag, int st, int at) {
+        char* buf = ring + at * BUF;
 #pragma unroll
         for (int c = 0; c < CPT; ++c) issue_panel(clamp_tag, st, buf, c, src_a[c]);
         if constexpr (!BD) {
@@ -533,7 +543,7 @@ __device__ __forceinline__ void xtile_mm16(const char* __restrict__ z, char* __r
         }
     };
     auto issue = [&](auto slot_tag, int st) {
-        issue_a(std::true_type{}, st);
+        issue_a(std::true_type{}, st, st % NB);
         if constexpr (BD) issue_b(std::true_type{}, slot_tag, st);
     };
     auto wait_landed = [&](int s) {
@@ -542,17 +552,17 @@ __device__ __forceinline__ void xtile_mm16(const char* __restrict__ z, char* __r
         else wait_vmcnt_runtime<CPT + CPT_B, kDmaDepth>(later);
     };
     auto wait_landed_bd = [&](auto later_tag) { wait_vmcnt<(CPT + NBO) * decltype(later_tag)::value>(); };
-    auto buf_a = [&](int st) -> const char* { return ring + (st % NB) * BUF; };
-    auto buf_b = [&](int st) -> const char* { return ring + (st % NB) * BUF + (diag ? 0 : PANEL); };
+    auto buf_a = [&](int at) -> const char* { return ring + at * BUF; };
+    auto buf_b = [&](int at) -> const char* { return ring + at * BUF + (diag ? 0 : PANEL); };
 
     // this stage's operands: rows as read, columns as read and J-swapped;
     // each is replaced by the next stage's right after its last MFMA
     uint4 a_op[NA];
     V bv[NBO], bj[NBO];
     uint4 b_raw[NBO];                  // the next stage's columns as read (LDS-staged forms)
-    auto read_b = [&](int st) {
+    auto read_b = [&](int at) {
 #pragma unroll
-        for (int x = 0; x < NBO; ++x) b_raw[x] = rd(buf_b(st), bn[x] * 16 + lc);
+        for (int x = 0; x < NBO; ++x) b_raw[x] = rd(buf_b(at), bn[x] * 16 + lc);
     };
 
     // stage st in ring slot R; kMask: the stage is in the final group (its
@@ -564,6 +574,8 @@ __device__ __forceinline__ void xtile_mm16(const char* __restrict__ z, char* __r
         constexpr bool kNext = decltype(has_next_tag)::value;
         constexpr bool kMask = decltype(mask_tag)::value;
         constexpr bool kMaskNext = decltype(mask_next_tag)::value;
+        const std::integral_constant<int, 1> next{};
+        const std::integral_constant<int, 1 + kDmaDepth> refill{};
         static_for<NP>([&](auto p_tag) {
             constexpr int p = decltype(p_tag)::value;
             constexpr int ia = J::T.IA[p], ib = J::T.IB[p];
@@ -580,19 +592,20 @@ __device__ __forceinline__ void xtile_mm16(const char* __restrict__ z, char* __r
                     constexpr int later = kMask ? (RS - 2 - R > 0 ? RS - 2 - R : 0) : kDmaDepth - 1;
                     wait_landed_bd(std::integral_constant<int, later>{});
                     dma_barrier();
-                    if constexpr (!kMask) issue_a(clamp_tag, st + 1 + kDmaDepth);
+                    if constexpr (!kMask) issue_a(clamp_tag, st + 1 + kDmaDepth, slot_at(st, refill));
                 } else {
                     wait_landed(st + 1);
                     dma_barrier();
                     // (with a ring of one stage the main loop also issues the
                     // last stages, so the offsets are always checked)
-                    if (st + 1 + kDmaDepth < n_st) issue_a(std::true_type{}, st + 1 + kDmaDepth);
-                    read_b(st + 1);
+                    if (st + 1 + kDmaDepth < n_st)
+                        issue_a(std::true_type{}, st + 1 + kDmaDepth, slot_at(st, refill));
+                    read_b(slot_at(st, next));
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
             if constexpr (kNext && last_use<J>(ia) == p) {
-                a_op[ia] = rd(buf_a(st + 1), am[ia] * 16 + lc);
+                a_op[ia] = rd(buf_a(slot_at(st, next)), am[ia] * 16 + lc);
                 if constexpr (kMaskNext) mask_op(st + 1, a_op[ia]);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -613,6 +626,7 @@ __device__ __forceinline__ void xtile_mm16(const char* __restrict__ z, char* __r
                 __builtin_amdgcn_sched_barrier(0);
             }
         });
+        cur = slot_at(st, next);
     };
     __builtin_amdgcn_s_waitcnt(0xC07F);
     static_for<kDmaDepth>([&](auto d) {
