@@ -111,9 +111,9 @@ constexpr int lds_bytes() {
     constexpr int panels = TILE == 128 ? 1 : 2;
     return dma_buffers<DT>() * panels * stage_blocks<DT, TILE>() * TILE * XT<DT>::RB;
 }
-// threads of a tile's workgroup
+// threads of a tile's workgroup (one group's, int8 / fp16)
 template <int DT, int TILE>
-constexpr int tile_threads() { return DT == AFC_F32 ? 4 * TILE : kThreads; }
+constexpr int tile_threads() { return DT == AFC_F32 ? 512 : kThreads; }
 
 // Workgroup barrier for the DMA pipeline: no memory fence (which would wait
 // for every outstanding global-to-LDS load) and no wait for the wave's LDS
@@ -850,11 +850,14 @@ __device__ __forceinline__ void xtile_mm16(const char* __restrict__ z, char* __r
 // 128-wide tiles: 8 waves, wave (rh, cg) takes the row blocks 4 rh .. 4 rh + 3
 // of two column blocks, 2 cg and 2 cg + 1, or on a diagonal tile cg and 7 - cg,
 // so that the waves of one SIMD (cg, both rh) share 9 blocks of the lower
-// triangle.  64-wide tiles: 4 waves, wave cg the four row blocks of column
-// block cg.  A step is 16 spectra: each thread loads 32 bytes (4 spectra of a
-// receiver) of the row panel and of the column panel, splits them and writes
-// the parts to LDS (plane, receiver, four 16-byte K chunks, swizzled as in
-// swz()) while the previous step is multiplied from the other buffer.  Sums
+// triangle.  64-wide tiles: 8 waves too, wave (rh, cg) the row blocks 2 rh and
+// 2 rh + 1 of column block cg; with 128 registers four waves per SIMD (75
+// antennas x 3 subbands x 1000 spectra 226 -> 205 us, 64 receivers x 1 subband
+// 66 -> 49 us against 4 waves of four blocks, two per SIMD; the same sums in the
+// same order).  A step is 16 spectra: each thread loads 32 bytes (4 spectra of a
+// receiver) of the row panel and of the column panel (64-wide: waves 0-3 of the
+// row panel, waves 4-7 of the column panel), splits them and writes the parts
+// to LDS (plane, receiver, four 16-byte K chunks, swizzled as in swz()) while the previous step is multiplied from the other buffer.  Sums
 // are kept in two levels: the MFMA accumulators take kSplitInner steps and are
 // then added to an outer sum.
 template <int TILE>
@@ -894,11 +897,12 @@ template <int TILE, bool kFull>
 __device__ __forceinline__ bool xtile_split(const char* __restrict__ z, char* __restrict__ vis_ch,
                                             int32_t* __restrict__ w_sb, const uint8_t* __restrict__ fl_sb,
                                             int N, int S, int ti, int tj, bool write_weights, char* lds) {
-    constexpr int RB = 64, NC = TILE == 128 ? 2 : 1;
+    constexpr int RB = 64, NC = TILE == 128 ? 2 : 1, NR = TILE == 128 ? 4 : 2;
+    constexpr int kPan = TILE == 128 ? 2 : 1;            // panels a thread stages; one: its half of the workgroup's
     constexpr int kSplitPlane = split_plane<TILE>(), kSplitPanel = split_panel<TILE>();
     const int tid = threadIdx.x, lane = tid & 63, lc = lane & 15, lg = lane >> 4;
     const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int cg = wid & 3, rh = wid >> 2;               // rh = 0 in 64-wide tiles
+    const int cg = wid & 3, rh = wid >> 2;
     const int i0 = ti * TILE, j0 = tj * TILE;
     const bool diag = !kFull && ti == tj;
     const int nb = (S + kSBlk - 1) / kSBlk;
@@ -908,39 +912,42 @@ __device__ __forceinline__ bool xtile_split(const char* __restrict__ z, char* __
     const int bn[2] = {diag || NC == 1 ? cg : 2 * cg, diag ? 7 - cg : 2 * cg + 1};
     // blocks this wave computes: those with a row and a column below N, on or
     // below the diagonal
-    bool on[4][NC];
+    bool on[NR][NC];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < NR; ++i)
 #pragma unroll
         for (int x = 0; x < NC; ++x)
-            on[i][x] = kFull || (i0 + (4 * rh + i) * 16 < N && j0 + bn[x] * 16 < N && (!diag || 4 * rh + i >= bn[x]));
+            on[i][x] = kFull ||
+                       (i0 + (NR * rh + i) * 16 < N && j0 + bn[x] * 16 < N && (!diag || NR * rh + i >= bn[x]));
 
     // staging: 4 spectra (sh) of one receiver of block sb of the step, in
     // either panel; rows beyond N repeat row N - 1 (they only feed outputs
     // that are never stored), blocks beyond the data the last block
-    const int sh = tid & 1, srow = (tid >> 1) & (TILE - 1), sb = tid / (2 * TILE);
-    const unsigned src_a = (unsigned)min(i0 + srow, N - 1) * RB + sh * 32;
-    const unsigned src_b = (unsigned)min(j0 + srow, N - 1) * RB + sh * 32;
+    const int sh = tid & 1, srow = (tid >> 1) & (TILE - 1), sb = (tid / (2 * TILE)) & 1;
+    const unsigned src[2] = {(unsigned)min((kPan == 1 && rh ? j0 : i0) + srow, N - 1) * RB + sh * 32,
+                             (unsigned)min(j0 + srow, N - 1) * RB + sh * 32};
+    const bool stages = kPan == 2 || !diag || rh == 0;
     const unsigned dst = (unsigned)srow * 64 + (unsigned)((((sb * 2 + sh) ^ (srow >> 2)) & 3) * 16);
     constexpr int kDepth = 2;                            // steps of loads in flight beyond the one being staged
-    float4 raws[kDepth][2][2];
+    float4 raws[kDepth][kPan][2];
     auto load = [&](int k, auto slot_tag) {
-        float4 (&raw)[2][2] = raws[decltype(slot_tag)::value];
+        float4 (&raw)[kPan][2] = raws[decltype(slot_tag)::value];
         const unsigned off = (unsigned)min(2 * k + sb, nb - 1) * (unsigned)(N * RB);
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
-            raw[0][e] = *reinterpret_cast<const float4*>(z + (src_a + off + 16 * e));
-            if (!diag) raw[1][e] = *reinterpret_cast<const float4*>(z + (src_b + off + 16 * e));
+            if (stages) raw[0][e] = *reinterpret_cast<const float4*>(z + (src[0] + off + 16 * e));
+            if (kPan == 2 && !diag) raw[kPan - 1][e] = *reinterpret_cast<const float4*>(z + (src[1] + off + 16 * e));
         }
     };
     float mx = 0.0f;
     unsigned mn = 0xFFFFFFFFu;
     auto stage = [&](int k, auto slot_tag) {
-        float4 (&raw)[2][2] = raws[decltype(slot_tag)::value];
+        if (!stages) return;
+        float4 (&raw)[kPan][2] = raws[decltype(slot_tag)::value];
         if (2 * k + 2 > full_blocks) {                   // uniform: zero the spectra >= S
             const int first = (2 * k + sb) * kSBlk + sh * 4;
 #pragma unroll
-            for (int pn = 0; pn < 2; ++pn)
+            for (int pn = 0; pn < kPan; ++pn)
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
                     float4& v = raw[pn][e];
@@ -948,9 +955,9 @@ __device__ __forceinline__ bool xtile_split(const char* __restrict__ z, char* __
                     if (first + 2 * e + 1 >= S) v.z = v.w = 0.0f;
                 }
         }
-        char* base = lds + (k & 1) * 2 * kSplitPanel + dst;
+        char* base = lds + ((k & 1) * 2 + (kPan == 1 ? rh : 0)) * kSplitPanel + dst;
 #pragma unroll
-        for (int pn = 0; pn < 2; ++pn) {
+        for (int pn = 0; pn < kPan; ++pn) {
             if (pn == 1 && diag) break;
             uint4 h, m, l;
             const float4 u = raw[pn][0], v = raw[pn][1];
@@ -968,9 +975,9 @@ __device__ __forceinline__ bool xtile_split(const char* __restrict__ z, char* __
             *reinterpret_cast<uint4*>(p + 2 * kSplitPlane) = l;
         }
     };
-    v4f accR[4][NC], accI[4][NC], outR[4][NC], outI[4][NC];
+    v4f accR[NR][NC], accI[NR][NC], outR[NR][NC], outI[NR][NC];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < NR; ++i)
 #pragma unroll
         for (int x = 0; x < NC; ++x) accR[i][x] = accI[i][x] = outR[i][x] = outI[i][x] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
     auto rd = [&](const char* panel, int part, int row) -> uint4 {
@@ -1003,7 +1010,7 @@ __device__ __forceinline__ bool xtile_split(const char* __restrict__ z, char* __
         for (int i = decltype(first_tag)::value; i < decltype(last_tag)::value; ++i) {
             uint4 a[3];
 #pragma unroll
-            for (int p = 0; p < 3; ++p) a[p] = rd(pa, p, (4 * rh + i) * 16 + lc);
+            for (int p = 0; p < 3; ++p) a[p] = rd(pa, p, (NR * rh + i) * 16 + lc);
             if constexpr (kFull) {
 #pragma unroll
                 for (int q = 0; q < 6; ++q)
@@ -1027,7 +1034,7 @@ __device__ __forceinline__ bool xtile_split(const char* __restrict__ z, char* __
     };
     auto fold = [&]() {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < NR; ++i)
 #pragma unroll
             for (int x = 0; x < NC; ++x) {
                 outR[i][x] += accR[i][x];
@@ -1061,12 +1068,12 @@ __device__ __forceinline__ bool xtile_split(const char* __restrict__ z, char* __
             load(k + 1 + kDepth, slot_tag);
         }
         columns(k);
-        rows(k, std::integral_constant<int, 0>{}, std::integral_constant<int, 2>{});
+        rows(k, std::integral_constant<int, 0>{}, std::integral_constant<int, NR / 2>{});
         if (kFull && rh == 1 && more) {
             stage(k + 1, slot_tag);
             load(k + 1 + kDepth, slot_tag);
         }
-        rows(k, std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
+        rows(k, std::integral_constant<int, NR / 2>{}, std::integral_constant<int, NR>{});
         if (++inner == kSplitInner) {
             inner = 0;
             fold();
@@ -1086,34 +1093,36 @@ __device__ __forceinline__ bool xtile_split(const char* __restrict__ z, char* __
 
     const StorePair<float> st{vis_ch, w_sb, N, S, write_weights, (lc & 1) != 0};
     auto flag_of = [&](int rcv) { return fl_sb && fl_sb[min(rcv, N - 1) >> 1] != 0; };
-    bool fr[4][2];
+    bool fr[NR][2];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < NR; ++i)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) fr[i][h] = flag_of(i0 + (4 * rh + i) * 16 + 4 * lg + 2 * h);
+        for (int h = 0; h < 2; ++h) fr[i][h] = flag_of(i0 + (NR * rh + i) * 16 + 4 * lg + 2 * h);
 #pragma unroll
     for (int x = 0; x < NC; ++x) {
         const int Jc = j0 + bn[x] * 16 + lc;
         const bool fc = flag_of(Jc);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < NR; ++i) {
             if (!on[i][x]) continue;
 #pragma unroll
             for (int r = 0; r < 4; r += 2)
                 st(outR[i][x][r], outI[i][x][r], outR[i][x][r + 1], outI[i][x][r + 1],
-                   i0 + (4 * rh + i) * 16 + 4 * lg + r, Jc, fc || fr[i][r >> 1]);
+                   i0 + (NR * rh + i) * 16 + 4 * lg + r, Jc, fc || fr[i][r >> 1]);
         }
     }
     return true;
 }
 
 // One fp32 tile on the fp32 matrix cores: 2 x 2 waves of one 32 x 32 block
-// each (threads tid 0..255), samples staged through registers.  The tiles
+// each (threads tid 0..255), samples staged through the registers of kStagers
+// threads (512: four more waves that only stage; all loads in flight then fit
+// in 128 registers).  The tiles
 // whose samples the bf16 split cannot hold take it (infinities, magnitudes
 // outside 2^-50 .. 2^50); sums in two levels of 64 spectra.  `z` points at
 // channel ch of subband sb; off: the tile is only stepped through (its
 // barriers), neither multiplied nor stored.
-template <int DT, int TILE>
+template <int DT, int TILE, int kStagers>
 __device__ __forceinline__ void xtile_f32(const char* __restrict__ z, char* __restrict__ vis_ch,
                                       int32_t* __restrict__ w_sb, const uint8_t* __restrict__ fl_sb,
                                       int N, int Na, int S, int ti, int tj, bool write_weights,
@@ -1123,8 +1132,8 @@ __device__ __forceinline__ void xtile_f32(const char* __restrict__ z, char* __re
     constexpr int WT = TILE / 2, MB = WT / 32;
     constexpr int PANEL = kStg * TILE * RB;                  // bytes of one panel in one stage
     constexpr int CHUNKS = kStg * TILE * PLANES;             // 16-byte chunks per panel per stage
-    constexpr int CPT = CHUNKS / kThreads;
-    static_assert(CHUNKS % kThreads == 0, "a stage must split evenly over the threads");
+    constexpr int CPT = CHUNKS / kStagers;
+    static_assert(CHUNKS % kStagers == 0, "a stage must split evenly over the threads");
     static_assert(DT == AFC_F32, "fp32 only");
     using acc_t = typename Tr::acc_t;
 
@@ -1133,7 +1142,7 @@ __device__ __forceinline__ void xtile_f32(const char* __restrict__ z, char* __re
     const int wr = wid >> 1, wc = wid & 1;
     const int i0 = ti * TILE, j0 = tj * TILE;
     const bool diag = ti == tj;
-    const bool wave_on = !off && !(diag && wr < wc);
+    const bool wave_on = !off && wid < 4 && !(diag && wr < wc);
     const int nb = (S + kSBlk - 1) / kSBlk;
     const int tail_valid = S - (nb - 1) * kSBlk;             // spectra in the last block
     const int n_stages = (nb + kStg - 1) / kStg;
@@ -1165,13 +1174,15 @@ __device__ __forceinline__ void xtile_f32(const char* __restrict__ z, char* __re
             const int r0 = pn == 0 ? i0 : j0;
 #pragma unroll
             for (int c = 0; c < CPT; ++c) {
-                const int chunk = tid + c * kThreads;
+                const int chunk = tid + c * kStagers;
                 const int bl = chunk / (TILE * PLANES);
                 const int rem = chunk % (TILE * PLANES);
                 const int row = rem / PLANES, q = rem % PLANES;
                 const int blk = min(st * kStg + bl, nb - 1);
                 const int rg = min(r0 + row, N - 1);
-                pre[slot][pn][c] = *reinterpret_cast<const uint4*>(z + ((int64_t)blk * N + rg) * RB + q * 16);
+                // (a channel of samples is below 2^27 bytes)
+                const unsigned off = ((unsigned)blk * (unsigned)N + (unsigned)rg) * RB + q * 16;
+                pre[slot][pn][c] = *reinterpret_cast<const uint4*>(z + off);
             }
         }
     };
@@ -1189,7 +1200,7 @@ __device__ __forceinline__ void xtile_f32(const char* __restrict__ z, char* __re
             char* base = lds_raw + (buf * 2 + pn) * PANEL;
 #pragma unroll
             for (int c = 0; c < CPT; ++c) {
-                const int chunk = tid + c * kThreads;
+                const int chunk = tid + c * kStagers;
                 const int bl = chunk / (TILE * PLANES);
                 const int rem = chunk % (TILE * PLANES);
                 const int row = rem / PLANES, q = rem % PLANES;
@@ -1354,7 +1365,8 @@ __device__ __forceinline__ void xtile_f32(const char* __restrict__ z, char* __re
 
 // One tile of one (subband, channel).  int8 / fp16: each wave computes its
 // job of 16 x 16 blocks (diagonal tiles spread their lower-triangle blocks
-// over the waves); fp32: 2 x 2 waves of one 32 x 32 block each.
+// over the waves); fp32: the bf16 split, or the fp32 matrix cores where a
+// sample is out of its range.
 template <int DT, int TILE, int kGroups = 1>
 __device__ __forceinline__ void xtile(const char* __restrict__ z, char* __restrict__ vis_ch,
                                       int32_t* __restrict__ w_sb, const uint8_t* __restrict__ fl_sb,
@@ -1369,7 +1381,7 @@ __device__ __forceinline__ void xtile(const char* __restrict__ z, char* __restri
             return;
         __syncthreads();
         if constexpr (TILE == 64) {
-            xtile_f32<DT, 64>(z, vis_ch, w_sb, fl_sb, N, Na, S, ti, tj, write_weights, lds_raw, threadIdx.x, false);
+            xtile_f32<DT, 64, 512>(z, vis_ch, w_sb, fl_sb, N, Na, S, ti, tj, write_weights, lds_raw, threadIdx.x, false);
         } else {
             // the 64-wide quarters, two at a time: waves 0-3 the left ones,
             // waves 4-7 the right ones (above the diagonal on a diagonal
@@ -1379,7 +1391,7 @@ __device__ __forceinline__ void xtile(const char* __restrict__ z, char* __restri
             for (int r = 0; r < 2; ++r) {
                 const int qi = 2 * ti + r, qj = 2 * tj + half;
                 const bool off = qi < qj || qi * 64 >= N || qj * 64 >= N;
-                xtile_f32<DT, 64>(z, vis_ch, w_sb, fl_sb, N, Na, S, qi, qj, write_weights,
+                xtile_f32<DT, 64, 256>(z, vis_ch, w_sb, fl_sb, N, Na, S, qi, qj, write_weights,
                                   lds_raw + half * lds_f32_bytes<64>(), threadIdx.x & 255, off);
             }
         }
@@ -1421,9 +1433,9 @@ __device__ __forceinline__ void xtile(const char* __restrict__ z, char* __restri
 }
 
 template <int DT, int TILE, int kGroups>
-// (64-wide int8 / fp16 tiles hold 32 accumulator registers: four workgroups per
-// CU, the others two, or one of 8 waves)
-__global__ __launch_bounds__((tile_threads<DT, TILE>() * kGroups), (DT != AFC_F32 && TILE == 64 ? 4 : 2)) void xengine_kernel(
+// (64-wide tiles hold 32 accumulator registers: 16 waves per CU; 128-wide ones
+// 8)
+__global__ __launch_bounds__((tile_threads<DT, TILE>() * kGroups), (TILE == 64 ? 4 : 2)) void xengine_kernel(
     XArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[kGroups * lds_bytes<DT, TILE>()];
     // XCD-aware order: consecutive workgroup ids go round-robin over the 8
@@ -1514,12 +1526,12 @@ hipError_t launch_fill_scratch(void* p, size_t bytes, hipStream_t stream) {
 
 // fp32 tile width.  128-wide tiles convert and read each sample for twice as
 // many products, but run one workgroup per CU; 64-wide ones run two, waste
-// less at the array's edge and fill the CUs on small launches.  Measured per
-// round of workgroups (1000 spectra): 119 us for 128-wide tiles, 90 us for
-// 64-wide ones (their rounds blur once there are two), 79 us for one 64-wide
-// tile per CU or fewer.  E.g. 75 antennas x 3 subbands 262 us (128) and 206
-// us (64); 96 receivers x 4 subbands 95 and 144 us; 1152 receivers x 1
-// subband 1689 and 2021 us.
+// less at the array's edge and fill the CUs on small launches.  Measured (1000
+// spectra): 119 us per round of 128-wide tiles; 64-wide ones 53 us for at most
+// one per CU, 85 us for at most two, then 20 us + 80 us per round of two (a
+// round just begun costs it whole).  E.g. (64, 128) 75 antennas x 3 subbands 185
+// and 260 us, 150 x 2 340 and 381, 96 receivers x 4 subbands 116 and 93, 200
+// antennas x 1 287 and 349, 300 x 1 570 and 523, 576 x 1 1962 and 1665.
 int xengine_f32_tile(int N, int n_subbands) {
     int dev = 0, n_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
@@ -1532,7 +1544,7 @@ int xengine_f32_tile(int N, int n_subbands) {
     const double t128 = 119.0 * (double)ceil_div(tiles(128), n_cu);
     const int64_t n64 = tiles(64);
     const double r64 = (double)n64 / (2.0 * n_cu);
-    const double t64 = n64 <= n_cu ? 79.0 : 90.0 * (r64 < 2.0 ? std::ceil(r64) : r64);
+    const double t64 = r64 <= 0.5 ? 53.0 : r64 <= 1.0 ? 85.0 : std::max(130.0, 20.0 + 80.0 * r64);
     return t64 < t128 ? 64 : 128;
 }
 
@@ -1650,7 +1662,7 @@ hipError_t launch_xengine_list(const void* z_ws, void* vis, int32_t* weights, co
         hipLaunchKernelGGL((xengine_list_kernel<1, 128, 2>), grid, dim3(tile_threads<AFC_F32, 128>()), 0, stream, z, v,
                            weights, flags, sbs_dev, work_dev, ranges, N, Na);
     else if (mode == 1)
-        hipLaunchKernelGGL((xengine_list_kernel<1, 64, 2>), grid, dim3(tile_threads<AFC_F32, 64>()), 0, stream, z, v,
+        hipLaunchKernelGGL((xengine_list_kernel<1, 64, 4>), grid, dim3(tile_threads<AFC_F32, 64>()), 0, stream, z, v,
                            weights, flags, sbs_dev, work_dev, ranges, N, Na);
     else if (tile == 128)
         hipLaunchKernelGGL((xengine_list_kernel<0, 128, 2>), grid, block, 0, stream, z, v, weights, flags, sbs_dev,

@@ -212,7 +212,7 @@ def _natural_f32(z, S):
     return zn[..., 0] + 1j * zn[..., 1]                     # [B][64][S][N]
 
 
-# tile widths of fp32 launches: 75 antennas x 1 subband 64, x 8 128 (from the
+# tile widths of fp32 launches: 75 antennas x 1 subband 64, 48 x 4 128 (from the
 # launch size); 100 x 1 128 with an interior off-diagonal tile
 @pytest.mark.parametrize("B,Na,S", [(1, 75, 97), (4, 48, 40), (1, 100, 200), (1, 150, 65), (2, 32, 17)])
 @pytest.mark.parametrize("scale", [1.0, 2.0 ** -56, 2.0 ** 50])
