@@ -1396,7 +1396,7 @@ __device__ __forceinline__ void xtile(const char* __restrict__ z, char* __restri
             }
         }
     } else {
-        const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % (kGroups > 1 ? 4 : 64);
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wid = kGroups > 1 ? wave % 4 : wave;
         auto run = [&](auto job, const int (&am)[8], const int (&bn)[2]) {
             xtile_mm16<DT, TILE, kGroups, decltype(job)>(z, vis_ch, w_sb, fl_sb, N, Na, S, ti, tj, write_weights, lds_raw,
                                                 am, bn);
