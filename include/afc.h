@@ -12,9 +12,9 @@
  *                       gradient with respect to the complex gains
  *   afc_plan_*          batching form: many subbands with their own
  *                       integration length, sample type and antenna flags in
- *                       one graph of one channeliser launch and one
- *                       correlator launch per sample-type family, tile shape
- *                       from a measured tuner
+ *                       one graph of one channeliser launch per sample type
+ *                       and one correlator launch per sample-type family, tile
+ *                       shape by rule or from a measured tuner
  *
  * Conventions (all entry points):
  *   - Pointers are DEVICE pointers unless the comment says "host".  The caller
@@ -424,9 +424,10 @@ AFC_API int afc_image_from_grid(int32_t grid_size, const void* grid, const doubl
 /* ---------------------------------------------------------------------------
  * Batching form (Sec. "GPU Processing": each subband is an independent unit
  * of work; the paper hands subbands to free GPUs one by one, here all of them
- * go into one channeliser launch and one correlator launch per family of
- * sample types (int8 + fp16 together, fp32 apart) whose workgroups each take
- * one tile of a host-built, XCD-balanced work list, replayed as a HIP graph).
+ * go into one channeliser launch per sample type and one correlator launch
+ * per family of sample types (int8 + fp16 together, fp32 apart) whose
+ * workgroups each take one tile of a host-built, XCD-balanced work list,
+ * replayed as a HIP graph).
  *
  * afc_plan_create    d: shape with n_spectra = max S_b; dtype_per_sb host
  *                    [B] (AFC_F16 or AFC_I8 each, or AFC_F32); n_spectra_per_sb

@@ -605,7 +605,8 @@ class PlanInfo:
 
 
 class Plan:
-    """Batching form: one graph of one channeliser launch and one correlator launch per sample-type family."""
+    """Batching form: one graph of one channeliser launch per sample type and one correlator launch
+    per sample-type family."""
 
     def __init__(self, n_antennas: int, n_spectra_per_sb: Sequence[int], dtypes: Sequence[str],
                  tune_cache: Optional[str] = None, n_spectra: Optional[int] = None):
