@@ -157,14 +157,16 @@ __global__ __launch_bounds__(256) void grid_estimate_kernel(GridArgs g, int64_t 
     for (int64_t i = t0; i < n_words; i += n_thr) grid[i] = 0ull;
 }
 
-// totals of n_part partial sums in a fixed order (one workgroup)
+// totals of n_part partial sums in a fixed order (a workgroup of NT threads;
+// the result in thread 0)
+template <int NT>
 __device__ __forceinline__ Sums total_sums(const Sums* __restrict__ part, int n_part, Sums* lds) {
     Sums s{0.0, 0.0};
-    for (int i = threadIdx.x; i < n_part; i += 256) {
+    for (int i = threadIdx.x; i < n_part; i += NT) {
         s.a += part[i].a;
         s.w += part[i].w;
     }
-    return block_sums<256>(s, lds);
+    return block_sums<NT>(s, lds);
 }
 
 // scale = 2^(bits - e) with bound < 2^e
@@ -174,32 +176,29 @@ __device__ __forceinline__ double scale_for(double bound, int bits) {
     return ldexp(1.0, bits - e);
 }
 
-// Scale from the estimate: with a sample, 2^60 for the estimated bound, so that
-// the bound may be seven times the estimate; without (stride 1), 2^61.
-__global__ __launch_bounds__(256) void grid_scale_kernel(const Sums* __restrict__ part, int n_part, int stride,
-                                                         Scale* __restrict__ scale) {
+// Totals of the gridding pass: the normalisation, whether every cell must fit
+// 63 bits at the scale used, and else the scale for a second pass and the
+// grid cleared for it.  Every workgroup adds up the totals for itself, which
+// saves a launch (this and the scale in the gridding kernel: 150 antennas x 3
+// subbands on 1024^2 75.6 -> 70.6 us, 576 x 8 on 2048^2 702 -> 697).
+__global__ __launch_bounds__(256) void grid_check_kernel(const Sums* __restrict__ part, int n_part,
+                                                         Scale* __restrict__ scale, double* __restrict__ norm,
+                                                         unsigned long long* __restrict__ grid, int64_t n_words) {
     __shared__ Sums red[4];
-    const Sums s = total_sums(part, n_part, red);
-    if (threadIdx.x == 0) *scale = Scale{scale_for(s.a * stride, stride > 1 ? 60 : 61), 0, 0};
-}
-
-// Totals of the gridding pass: the normalisation, and whether every cell must
-// fit 63 bits at the scale used.
-__global__ __launch_bounds__(256) void grid_verify_kernel(const Sums* __restrict__ part, int n_part,
-                                                          Scale* __restrict__ scale, double* __restrict__ norm) {
-    __shared__ Sums red[4];
-    const Sums s = total_sums(part, n_part, red);
+    __shared__ int redo;
+    const Sums s = total_sums<256>(part, n_part, red);
     if (threadIdx.x == 0) {
-        norm[0] = s.w;
-        if (s.a * scale->scale >= 0x1.f8p62) *scale = Scale{scale_for(s.a, 61), 1, 0};
+        Scale next{scale[0].scale, 0, 0};
+        if (s.a * next.scale >= 0x1.f8p62) next = Scale{scale_for(s.a, 61), 1, 0};
+        redo = next.redo;
+        if (blockIdx.x == 0) {
+            norm[0] = s.w;
+            scale[1] = next;
+        }
     }
-}
-
-// clears the grid if the pass has to be repeated
-__global__ void grid_clear_kernel(unsigned long long* __restrict__ p, int64_t n, const Scale* __restrict__ scale) {
-    if (!scale->redo) return;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = 0ull;
+    __syncthreads();
+    if (!redo) return;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n_words; i += (int64_t)gridDim.x * 256) grid[i] = 0ull;
 }
 
 // Gridding work: one workgroup per (subband, pair of 48-antenna blocks; a
@@ -293,13 +292,18 @@ __device__ __forceinline__ void grid_baseline(const GridArgs& g, int b, int a, i
     if (ai) flush();
 }
 
-__global__ __launch_bounds__(kGThreads) void grid_kernel(GridArgs g, const Scale* __restrict__ scale_p,
+// The scale: from the n_est partial sums of the estimate, which every workgroup
+// adds up for itself (2 per thread, no launch of their own), with a sample 2^60
+// for the estimated bound, so that the bound may be seven times the estimate,
+// without (stride 1) 2^61; the second pass (repeat) takes scale_p[1].
+__global__ __launch_bounds__(kGThreads) void grid_kernel(GridArgs g, const Sums* __restrict__ est, int n_est, int stride,
+                                                         Scale* __restrict__ scale_p,
                                                          unsigned long long* __restrict__ grid, int n_split,
                                                          Sums* __restrict__ part, int repeat) {
     __shared__ unsigned long long win[kGW * kGW * 2];
-    __shared__ double msum[2];
+    __shared__ double msum[2], shared_scale;
     __shared__ Sums red[kGThreads / 64];
-    if (repeat && !scale_p->redo) return;
+    if (repeat && !scale_p[1].redo) return;
     const int b = blockIdx.y / n_split;
     const int k_begin = blockIdx.y % n_split * (kP / n_split), k_end = k_begin + kP / n_split;
     int ba, bc;                                               // block pair ba >= bc
@@ -339,12 +343,21 @@ __global__ __launch_bounds__(kGThreads) void grid_kernel(GridArgs g, const Scale
             msum[1] = sy / nA - ty / nC;
         }
     }
+    if (!repeat) {
+        const Sums s = total_sums<kGThreads>(est, n_est, red);
+        if (tid == 0) {
+            shared_scale = scale_for(s.a * stride, stride > 1 ? 60 : 61);
+            if (blockIdx.x == 0 && blockIdx.y == 0) scale_p[0] = Scale{shared_scale, 0, 0};
+        }
+    } else if (tid == 0) {
+        shared_scale = scale_p[1].scale;
+    }
     __syncthreads();
     const double nu = g.freq[b * kP + kP / 2];
     const double ur = msum[0] * nu * g.per_hz + 0.5 * g.N;
     const double vr = msum[1] * nu * g.per_hz + 0.5 * g.N;
     const int i0w = (int)floor(ur) - kGW / 2, j0w = (int)floor(vr) - kGW / 2;
-    const double scale = scale_p->scale;
+    const double scale = shared_scale;
     Sums sum{0.0, 0.0};
 
     const int n_bl = ba == bc ? nA * (nA - 1) / 2 : nA * nC;
@@ -548,7 +561,7 @@ size_t imaging_workspace_bytes(int Na, int B, int N) {
     return (size_t)N * N * 16                      // fixed-point grid
            + (size_t)N * N * 8 * 2                 // the imager's plane, partial sums of the gridding
            + (size_t)N / 2 * 8
-           + (size_t)n_part * 16 + 64;             // partial sums, scale
+           + (size_t)n_part * 16 + 64;             // partial sums, two scales
 }
 
 hipError_t launch_grid(const float2* vis, const int32_t* weights, const double* pos, const double* freq, int Na, int B,
@@ -570,13 +583,13 @@ hipError_t launch_grid(const float2* vis, const int32_t* weights, const double* 
     const int stride = (int)std::min<int64_t>(64, std::max<int64_t>(1, n_thr >> 13));
     const int64_t n_sample = ceil_div(n_thr, 4 * stride) * 4;
     // workgroups: enough to clear the grid as well; their partial sums lie in
-    // the planes (read before the gridding pass writes its own there)
+    // the first half of the planes
+    const int64_t half = (int64_t)N * N / 2;
     const int n_est = (int)std::min<int64_t>(std::max<int64_t>(ceil_div(n_sample * (kP / kBatch), 256), n_words / 1024),
-                                             std::min<int64_t>((int64_t)N * N, 4096));
+                                             std::min<int64_t>(half, 2048));
     Sums* est = reinterpret_cast<Sums*>(planes);
     hipLaunchKernelGGL(grid_estimate_kernel, dim3(n_est), dim3(256), 0, stream, g, n_cross, n_sample, stride, est, fixed,
                        n_words);
-    hipLaunchKernelGGL(grid_scale_kernel, dim3(1), dim3(256), 0, stream, est, n_est, stride, scale);
     const int n_blk = (int)ceil_div(Na, kGB);
     // Channels of a subband in 1, 2 or 4 workgroups: two workgroups run on a
     // CU at a time, and 1.5 rounds of them or more even out (576 antennas x 8
@@ -584,21 +597,25 @@ hipError_t launch_grid(const float2* vis, const int32_t* weights, const double* 
     // 146 and 81 us for the whole gridding); every part adds its window to the
     // grid, so no more parts than that.
     const int64_t n_pair = (int64_t)n_blk * (n_blk + 1) / 2;
-    const int64_t cap = std::max<int64_t>(n_part, (int64_t)N * N);
+    // (the sums of the parts lie in the tail of the workspace, or, more than it
+    // holds, in the second half of the planes: without a split at most one per
+    // subband, that is)
+    const int64_t cap = std::max<int64_t>(n_part, half);
     int n_split = 1;
     while (n_split < 4 && n_pair * B * n_split < 768 && n_pair * B * n_split * 2 <= cap) n_split *= 2;
     const int64_t n_wg = n_pair * B * n_split;
-    Sums* part = n_wg <= n_part ? tail : reinterpret_cast<Sums*>(planes);
+    Sums* part = n_wg <= n_part ? tail : est + half;
     const dim3 grid((unsigned)n_pair, (unsigned)(B * n_split));
-    const dim3 cgrid((unsigned)std::min<int64_t>(ceil_div(n_words, 256), 4096));
-    hipLaunchKernelGGL(grid_kernel, grid, dim3(kGThreads), 0, stream, g, scale, fixed, n_split, part, 0);
-    hipLaunchKernelGGL(grid_verify_kernel, dim3(1), dim3(256), 0, stream, part, (int)n_wg, scale, norm);
-    if (stride > 1) {
-        hipLaunchKernelGGL(grid_clear_kernel, cgrid, dim3(256), 0, stream, fixed, n_words, scale);
-        hipLaunchKernelGGL(grid_kernel, grid, dim3(kGThreads), 0, stream, g, scale, fixed, n_split, part, 1);
-    }
+    hipLaunchKernelGGL(grid_kernel, grid, dim3(kGThreads), 0, stream, g, est, n_est, stride, scale, fixed, n_split,
+                       part, 0);
+    // (without a sample the bound is the estimate: no second pass, nothing to clear)
+    hipLaunchKernelGGL(grid_check_kernel, dim3(stride > 1 ? 512 : 1), dim3(256), 0, stream, part, (int)n_wg, scale, norm,
+                       fixed, stride > 1 ? n_words : 0);
+    if (stride > 1)
+        hipLaunchKernelGGL(grid_kernel, grid, dim3(kGThreads), 0, stream, g, est, n_est, stride, scale, fixed, n_split,
+                           part, 1);
     hipLaunchKernelGGL(grid_to_float_kernel, dim3((unsigned)std::min<int64_t>(ceil_div((int64_t)N * N, 256), 4096)),
-                       dim3(256), 0, stream, fixed, scale, grid_out, (int64_t)N * N);
+                       dim3(256), 0, stream, fixed, scale + 1, grid_out, (int64_t)N * N);
     return hipGetLastError();
 }
 
