@@ -24,10 +24,11 @@
 //    fixed point: integer atomics make the result independent of the order of
 //    the additions, so the grid is bitwise reproducible.  The same pass sums
 //    the bound itself and the normalisation.
-//  * grid_verify_kernel: the totals; should the bound exceed what the scale
-//    allows (a sample that missed most of the power), it sets the exact scale
-//    and a flag, and a second clearing and gridding, which otherwise end at
-//    once, replace the grid.
+//  * grid_check_kernel: the totals; should the bound exceed what the scale
+//    allows (a sample that missed most of the power) or the scale resolve it
+//    to fewer than 60 bits (a sample that met nothing, or an outlier), it sets
+//    the exact scale and a flag, and a second clearing and gridding, which
+//    otherwise end at once, replace the grid.
 //  * imaging: (-1)^(p+q) modulation, FFT of the rows with the transpose in its
 //    store, row FFT again, and (-1)^(i+j) Re(.) / norm with the transpose back.
 #include <algorithm>
@@ -49,7 +50,7 @@ struct GridArgs {
     double per_hz;                // cells per metre and Hz: 1 / (c du)
 };
 
-// scale of the fixed-point grid, and whether the estimated one was too large
+// scale of the fixed-point grid, and whether the estimated one did not do
 struct Scale {
     double scale;
     int redo, pad;
@@ -169,19 +170,23 @@ __device__ __forceinline__ Sums total_sums(const Sums* __restrict__ part, int n_
     return block_sums<NT>(s, lds);
 }
 
-// scale = 2^(bits - e) with bound < 2^e
-__device__ __forceinline__ double scale_for(double bound, int bits) {
+// scale = 2^k that takes the exact bound to 2^60 .. 2^61, the estimated one to
+// 2^60.5 .. 2^61.5
+__device__ __forceinline__ double scale_for(double bound, bool exact) {
     int e = 0;
-    frexp(bound > 0.0 ? bound : 1.0, &e);
-    return ldexp(1.0, bits - e);
+    const double m = frexp(bound > 0.0 ? bound : 1.0, &e);
+    return ldexp(1.0, 61 - e + (!exact && m < 0.70710678118654752440 ? 1 : 0));
 }
 
-// Totals of the gridding pass: the normalisation, whether every cell must fit
-// 63 bits at the scale used, and else the scale for a second pass and the
-// grid cleared for it.  Every workgroup adds up the totals for itself, which
+// Totals of the gridding pass: the normalisation, whether the scale from the
+// sample (sampled) took the bound to 2^60 .. 2^63, so that every cell fits 63
+// bits and none is held in fewer than with the exact bound, and else the scale
+// for a second pass and the grid cleared for it.  The estimate may thus be 0.36
+// to 1.4 of the bound; a sample that meets no visibility says nothing about
+// it.  Every workgroup adds up the totals for itself, which
 // saves a launch (this and the scale in the gridding kernel: 150 antennas x 3
 // subbands on 1024^2 75.6 -> 70.6 us, 576 x 8 on 2048^2 702 -> 697).
-__global__ __launch_bounds__(256) void grid_check_kernel(const Sums* __restrict__ part, int n_part,
+__global__ __launch_bounds__(256) void grid_check_kernel(const Sums* __restrict__ part, int n_part, bool sampled,
                                                          Scale* __restrict__ scale, double* __restrict__ norm,
                                                          unsigned long long* __restrict__ grid, int64_t n_words) {
     __shared__ Sums red[4];
@@ -189,7 +194,8 @@ __global__ __launch_bounds__(256) void grid_check_kernel(const Sums* __restrict_
     const Sums s = total_sums<256>(part, n_part, red);
     if (threadIdx.x == 0) {
         Scale next{scale[0].scale, 0, 0};
-        if (s.a * next.scale >= 0x1.f8p62) next = Scale{scale_for(s.a, 61), 1, 0};
+        const double t = s.a * next.scale;                    // (zero: every cell is; NaN: as with the exact bound)
+        if (sampled && t != 0.0 && !(t >= 0x1p60 && t < 0x1.f8p62)) next = Scale{scale_for(s.a, true), 1, 0};
         redo = next.redo;
         if (blockIdx.x == 0) {
             norm[0] = s.w;
@@ -293,9 +299,8 @@ __device__ __forceinline__ void grid_baseline(const GridArgs& g, int b, int a, i
 }
 
 // The scale: from the n_est partial sums of the estimate, which every workgroup
-// adds up for itself (2 per thread, no launch of their own), with a sample 2^60
-// for the estimated bound, so that the bound may be seven times the estimate,
-// without (stride 1) 2^61; the second pass (repeat) takes scale_p[1].
+// adds up for itself (2 per thread, no launch of their own; without a sample,
+// stride 1, it is the bound); the second pass (repeat) takes scale_p[1].
 __global__ __launch_bounds__(kGThreads) void grid_kernel(GridArgs g, const Sums* __restrict__ est, int n_est, int stride,
                                                          Scale* __restrict__ scale_p,
                                                          unsigned long long* __restrict__ grid, int n_split,
@@ -346,7 +351,7 @@ __global__ __launch_bounds__(kGThreads) void grid_kernel(GridArgs g, const Sums*
     if (!repeat) {
         const Sums s = total_sums<kGThreads>(est, n_est, red);
         if (tid == 0) {
-            shared_scale = scale_for(s.a * stride, stride > 1 ? 60 : 61);
+            shared_scale = scale_for(s.a * stride, stride == 1);
             if (blockIdx.x == 0 && blockIdx.y == 0) scale_p[0] = Scale{shared_scale, 0, 0};
         }
     } else if (tid == 0) {
@@ -609,8 +614,8 @@ hipError_t launch_grid(const float2* vis, const int32_t* weights, const double* 
     hipLaunchKernelGGL(grid_kernel, grid, dim3(kGThreads), 0, stream, g, est, n_est, stride, scale, fixed, n_split,
                        part, 0);
     // (without a sample the bound is the estimate: no second pass, nothing to clear)
-    hipLaunchKernelGGL(grid_check_kernel, dim3(stride > 1 ? 512 : 1), dim3(256), 0, stream, part, (int)n_wg, scale, norm,
-                       fixed, stride > 1 ? n_words : 0);
+    hipLaunchKernelGGL(grid_check_kernel, dim3(stride > 1 ? 512 : 1), dim3(256), 0, stream, part, (int)n_wg, stride > 1,
+                       scale, norm, fixed, n_words);
     if (stride > 1)
         hipLaunchKernelGGL(grid_kernel, grid, dim3(kGThreads), 0, stream, g, est, n_est, stride, scale, fixed, n_split,
                            part, 1);

@@ -210,6 +210,55 @@ def test_grid_scale_from_a_sample(afc, dev, Na, B, N, case):
     assert torch.equal(im.grid(*args), grid)
 
 
+@pytest.mark.parametrize("strong,weak,by_weight", [(0.0, 1.0, True), (0.0, 1e-15, True), (0.0, 1e-20, True),
+                                                   (0.0, 1e-15, False), (1.0, 1e-10, False), (1e-12, 1e-22, False)])
+def test_grid_scale_of_a_sample_that_misleads(afc, dev, strong, weak, by_weight):
+    """A sample that meets no gridded visibility (all but one unsampled baseline
+    have weight 0, or are zero), or that meets an outlier (every 64th group of 4
+    baselines is sampled; baseline (1, 0) is in it, (300, 10) is not): no cell
+    is held in fewer bits than the bound on any cell, the sum of all
+    visibilities' |Re| + |Im| at both points, needs: half a unit of bound *
+    2^-60 per component and addition (16: 4 cells around the moving point times
+    4 parts of the channels; 1 for a single channel), beside the rounding of
+    the output to float32 and 1e-12 of the visibilities for the position."""
+    Na, B, N, ch = 576, 8, 128, 5
+    nbl = Na * (Na + 1) // 2
+    rng = np.random.default_rng(8)
+    pos = rng.uniform(-25, 25, size=(Na, 2))
+    freq = _freqs(B)
+    n_ch = 64 if by_weight else 1
+    V = torch.zeros((B, 64, nbl, 2, 2, 2), dtype=torch.float32, device=dev)
+    wt = torch.zeros((B, nbl), dtype=torch.int32, device=dev) if by_weight else None
+    if by_weight:
+        V += weak
+    G, tol, bound = np.zeros((N, N), np.complex128), np.zeros((N, N)), 0.0
+    for a, c, amp in ((1, 0, strong), (300, 10, weak)):
+        if amp == 0.0:
+            continue
+        bl = a * (a + 1) // 2 + c
+        sub = np.zeros((1, 64, 3, 2, 2, 2), np.float32)
+        sub[0, slice(None) if by_weight else ch, 1, [0, 1], [0, 1]] = np.float32([amp, -0.7 * amp])
+        V[0, :, bl] = torch.from_numpy(sub[0, :, 1]).to(dev)
+        if by_weight:
+            wt[0, bl] = 1
+        g, norm = oracle.grid_visibilities(sub, None, pos[[c, a]], freq[:1], N, 0.5)
+        G += g
+        tol += 2.0 ** -24 * np.abs(g) + 1e-12 * 2 * amp * n_ch * (g != 0)
+        bound += 2.0 * 1.7 * amp * n_ch
+    log(f"grid scale strong={strong} weak={weak} by_weight={by_weight}")
+    im = afc.Imager(torch.from_numpy(pos).to(dev), B, N, 0.5)
+    grid = im.grid(V, torch.from_numpy(freq).to(dev), wt)
+    tol += (16 if by_weight else 2) * 0.5 * np.sqrt(2.0) * bound * 2.0 ** -60
+    if by_weight:
+        assert im.norm.item() == norm
+    assert np.count_nonzero(G) >= 8
+    err = np.abs(_cg(grid) - G)
+    log(f"  worst {np.max(err / tol):.2e} of the tolerance")
+    assert np.all(err <= tol)
+    del V, grid
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("N", [32, 64, 128, 256, 512, 1024, 2048, 4096])
 def test_image_every_size_matches_fft(afc, dev, N):
     """Every transform size against numpy's float64 FFT of the same grid:
