@@ -48,6 +48,7 @@ struct GridArgs {
     const double* freq;           // [B][64]
     int Na, B, N;
     double per_hz;                // cells per metre and Hz: 1 / (c du)
+    double inv_du;
 };
 
 // scale of the fixed-point grid, and whether the estimated one did not do
@@ -66,18 +67,27 @@ __device__ __forceinline__ void pair_of(int64_t t, int& a, int& c) {
 }
 
 // Grid position of a baseline (dx, dy) at frequency nu: the cell below it, the
-// fractions, and whether all eight cells it touches lie inside the grid.
+// fractions, and whether all eight cells it touches lie inside the grid.  The
+// position takes one product with 1 / (c du) instead of a division per
+// coordinate; within 1e-9 cells of the grid's edge, where its last bit decides
+// on a visibility (regular layouts put points exactly there), it is formed as
+// dx nu / c / du.
 struct Cell {
     int i, j;
     double fu, fv;
     bool ok;
 };
 __device__ __forceinline__ Cell cell_of(const GridArgs& g, double dx, double dy, double nu) {
-    const double s = nu * g.per_hz;
-    const double pu = dx * s + 0.5 * g.N, pv = dy * s + 0.5 * g.N;
-    const double i0 = floor(pu), j0 = floor(pv);
+    const double s = nu * g.per_hz, x = dx * s, y = dy * s, edge = 0.5 * g.N - 1.0;
+    double pu = x + 0.5 * g.N, pv = y + 0.5 * g.N;
     Cell c;
-    c.ok = i0 >= 1.0 && j0 >= 1.0 && i0 <= g.N - 2.0 && j0 <= g.N - 2.0;
+    c.ok = fabs(x) < edge - 1e-9 && fabs(y) < edge - 1e-9;
+    if (!c.ok && fabs(x) < edge + 1e-9 && fabs(y) < edge + 1e-9) {
+        pu = dx * nu / kC * g.inv_du + 0.5 * g.N;
+        pv = dy * nu / kC * g.inv_du + 0.5 * g.N;
+        c.ok = floor(pu) >= 1.0 && floor(pv) >= 1.0 && floor(pu) <= g.N - 2.0 && floor(pv) <= g.N - 2.0;
+    }
+    const double i0 = floor(pu), j0 = floor(pv);
     c.i = c.ok ? (int)i0 : 0;
     c.j = c.ok ? (int)j0 : 0;
     c.fu = pu - i0;
@@ -579,7 +589,7 @@ hipError_t launch_grid(const float2* vis, const int32_t* weights, const double* 
     char* planes = w + (size_t)N * N * 16;                    // the imager's, free here
     Sums* tail = reinterpret_cast<Sums*>(planes + (size_t)N * N * 16 + (size_t)N / 2 * 8);
     Scale* scale = reinterpret_cast<Scale*>(tail + n_part);
-    GridArgs g{vis, weights, pos, freq, Na, B, N, 1.0 / (kC * du)};
+    GridArgs g{vis, weights, pos, freq, Na, B, N, 1.0 / (kC * du), 1.0 / du};
     const int64_t n_words = (int64_t)N * N * 2;
     // 1 in 64 of the baselines (times subbands), from 2^19 of them on, of the
     // fewer at least 2^13, below 2^14 all.  At 576 antennas x 8 subbands the

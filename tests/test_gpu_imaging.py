@@ -259,6 +259,25 @@ def test_grid_scale_of_a_sample_that_misleads(afc, dev, strong, weak, by_weight)
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("du", [0.25, 0.5, 2.0])
+@pytest.mark.parametrize("waves", [1.0, 1.5, 3.0, 7.0])
+def test_points_on_the_edge_of_the_grid(afc, dev, du, waves):
+    """Regular layouts put baselines exactly on the last cell of the grid: the
+    same visibilities are gridded as in the oracle (the normalisation is equal),
+    whose position is dx nu / c / du + N / 2."""
+    Na, B, N = 6, 2, 64
+    step = du / waves                                        # one cell, metres
+    pos = np.array([[0, 0], [-31, 3], [31, -2], [4, -31], [-5, 31], [-31, -31]], np.float64) * step
+    freq = np.full((B, 64), waves * C)
+    V = np.random.default_rng(6).standard_normal((B, 64, Na * (Na + 1) // 2, 2, 2, 2)).astype(np.float32)
+    log(f"grid edge du={du} waves={waves}")
+    im = afc.Imager(torch.from_numpy(pos).to(dev), B, N, du)
+    grid = im.grid(torch.from_numpy(V).to(dev), torch.from_numpy(freq).to(dev))
+    G, norm = oracle.grid_visibilities(V, None, pos, freq, N, du)
+    assert im.norm.item() == norm
+    assert np.abs(_cg(grid) - G).max() <= 1e-6 * np.abs(G).max()
+
+
 @pytest.mark.parametrize("N", [32, 64, 128, 256, 512, 1024, 2048, 4096])
 def test_image_every_size_matches_fft(afc, dev, N):
     """Every transform size against numpy's float64 FFT of the same grid:
