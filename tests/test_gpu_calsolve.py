@@ -244,6 +244,35 @@ def test_solver_tile_edges_match_oracle(afc, dev, Na, form):
     np.testing.assert_allclose(gz, _ref(g0.astype(np.complex64).astype(np.complex128)), rtol=0, atol=1e-6)
 
 
+@pytest.mark.parametrize("Na", [40, 100, 150])
+@pytest.mark.parametrize("form", ["weight", "model", "model and weights"])
+def test_flagged_elements_that_are_not_finite(afc, dev, Na, form):
+    """A flagged element's weight is 0 whatever the weight array holds (1 /
+    variance of lost data).  Its terms are its data's times 0: an infinite model
+    makes D of its two antennas NaN, and they keep their gains, as in the
+    oracle.  One workgroup per solve up to 128 antennas, tile kernels above."""
+    P, n_iter = 2, 9
+    V, M, g = W.make_calibration(Na=Na, P=P, n_src=4, snr=20.0, seed=Na)
+    nbl = Na * (Na + 1) // 2
+    rng = np.random.default_rng(Na)
+    fl = (rng.random((P, nbl, 2)) < 0.05).astype(np.uint8)
+    fl[1, :, 0] = 0
+    wt = rng.uniform(0.5, 1.5, (P, nbl, 2)).astype(np.float32) if form != "model" else None
+    if form == "weight":
+        wt[fl != 0] = rng.choice(np.float32([np.inf, -np.inf, np.nan]), int(fl.sum()))
+    else:
+        fl[0, 30 * 31 // 2 + 7] = 1                          # antennas 30 and 7 of channel 0
+        M[0, 30 * 31 // 2 + 7, [0, 1], [0, 1], 0] = np.inf
+    g0 = (rng.uniform(0.8, 1.2, (P, Na, 2)) + 0j).astype(np.complex128)
+    log(f"solve, flagged {form} not finite, Na={Na}")
+    got, _ = _solve_gpu_w(afc, dev, V, M, g0, n_iter, fl, wt)
+    with np.errstate(invalid="ignore"):
+        ref = oracle.cal_solve(V, M, g0.astype(np.complex64).astype(np.complex128), n_iter,
+                               weights=oracle.cal_weights(P, nbl, flags=fl, weights=wt))
+    assert np.all(np.isfinite(ref))
+    assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max()
+
+
 # channels held in registers up to 64, read again above; one workgroup takes 64
 # baselines, a partial sum of stage 1 4096
 @pytest.mark.parametrize("Na,P", [(1, 3), (2, 1), (10, 7), (11, 64), (12, 65), (30, 130), (90, 8), (91, 9)])
