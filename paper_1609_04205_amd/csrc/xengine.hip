@@ -879,19 +879,20 @@ __device__ __forceinline__ void split2(float x, float y, unsigned& h, unsigned& 
     l = __builtin_bit_cast(unsigned, __builtin_convertvector(v2f{x2, y2}, v2b));
 }
 
-// The split holds for samples that are 0 or 2^-50 <= |x| < 2^50: no part is
-// subnormal, no part rounds to infinity and no product of parts leaves the
-// normal range.  mx and mn collect the largest magnitude and the smallest
-// nonzero one (twice the bits, minus one: zero is the largest value).
-constexpr float kSplitMax = 0x1p50f;
-constexpr unsigned kSplitMin = 2u * ((127u - 50u) << 23) - 1u;
-__device__ __forceinline__ void split_range(float x, float y, float& mx, unsigned& mn) {
-    mx = fmaxf(fmaxf(fabsf(x), fabsf(y)), mx);
-    mn = min(min(2u * __float_as_uint(x) - 1u, 2u * __float_as_uint(y) - 1u), mn);
-}
+// The split's range, by the largest magnitude of a receiver's samples (a
+// thread's share of them, a quarter): below 2^50, so that no part rounds to
+// infinity and no sum overflows, and from 2^-44 on or zero, tested every
+// kSplitInner steps (64 spectra).  Parts and products of parts below 2^-126 may
+// then be lost, at most 2^-33 of the product of the two receivers' largest
+// samples from a product.  (A bound on the smallest nonzero sample instead,
+// 2^-50, held no noise: of samples of 1e-9 one in a million is smaller, and
+// most tiles of 3051 spectra started over on the fp32 MFMAs.)
+constexpr float kSplitMax = 0x1p50f, kSplitMin = 0x1p-44f;
+__device__ __forceinline__ float max3_abs(float x, float y, float m) { return fmaxf(fmaxf(fabsf(x), fabsf(y)), m); }
+__device__ __forceinline__ bool out_of_split(float mx) { return !(mx < kSplitMax) || (mx > 0.0f && mx < kSplitMin); }
 
 // kFull: an off-diagonal tile with all rows and columns below N (no block of
-// it is skipped).  False if a sample is out of the split's range; the tile is
+// it is skipped).  False if a receiver is out of the split's range; the tile is
 // then not stored.
 template <int TILE, bool kFull>
 __device__ __forceinline__ bool xtile_split(const char* __restrict__ z, char* __restrict__ vis_ch,
@@ -939,8 +940,7 @@ __device__ __forceinline__ bool xtile_split(const char* __restrict__ z, char* __
             if (kPan == 2 && !diag) raw[kPan - 1][e] = *reinterpret_cast<const float4*>(z + (src[1] + off + 16 * e));
         }
     };
-    float mx = 0.0f;
-    unsigned mn = 0xFFFFFFFFu;
+    float mx[kPan] = {};
     auto stage = [&](int k, auto slot_tag) {
         if (!stages) return;
         float4 (&raw)[kPan][2] = raws[decltype(slot_tag)::value];
@@ -965,10 +965,7 @@ __device__ __forceinline__ bool xtile_split(const char* __restrict__ z, char* __
             split2(u.z, u.w, h.y, m.y, l.y);
             split2(v.x, v.y, h.z, m.z, l.z);
             split2(v.z, v.w, h.w, m.w, l.w);
-            split_range(u.x, u.y, mx, mn);
-            split_range(u.z, u.w, mx, mn);
-            split_range(v.x, v.y, mx, mn);
-            split_range(v.z, v.w, mx, mn);
+            mx[pn] = max3_abs(u.x, u.y, max3_abs(u.z, u.w, max3_abs(v.x, v.y, max3_abs(v.z, v.w, mx[pn]))));
             char* p = base + pn * kSplitPanel;
             *reinterpret_cast<uint4*>(p) = h;
             *reinterpret_cast<uint4*>(p + kSplitPlane) = m;
@@ -1042,12 +1039,12 @@ __device__ __forceinline__ bool xtile_split(const char* __restrict__ z, char* __
                 accR[i][x] = accI[i][x] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
             }
     };
-    // a sample out of range stops the tile: the wave that meets one raises the
+    // a receiver out of range stops the tile: the wave that meets one raises the
     // workgroup's flag before the barrier of the step that folds, and every
     // wave reads it after that barrier (no wave writes it before it is read)
     int* const bad = reinterpret_cast<int*>(lds + 4 * kSplitPanel);
     auto raise = [&]() {
-        if (__any(!(mx < kSplitMax) || mn < kSplitMin) && lane == 0) *bad = 1;
+        if (__any(out_of_split(mx[0]) || out_of_split(mx[kPan - 1])) && lane == 0) *bad = 1;
     };
     if (tid == 0) *bad = 0;
     using S0 = std::integral_constant<int, 0>;
@@ -1118,8 +1115,7 @@ __device__ __forceinline__ bool xtile_split(const char* __restrict__ z, char* __
 // each (threads tid 0..255), samples staged through the registers of kStagers
 // threads (512: four more waves that only stage; all loads in flight then fit
 // in 128 registers).  The tiles
-// whose samples the bf16 split cannot hold take it (infinities, magnitudes
-// outside 2^-50 .. 2^50); sums in two levels of 64 spectra.  `z` points at
+// whose samples the bf16 split cannot hold take it (see out_of_split); sums in two levels of 64 spectra.  `z` points at
 // channel ch of subband sb; off: the tile is only stepped through (its
 // barriers), neither multiplied nor stored.
 template <int DT, int TILE, int kStagers>

@@ -327,3 +327,18 @@ def test_int8_groups_of_a_small_launch(afc, dev, Na, B, S):
             V, W_ = oracle.xcorr_int(zn[b, ch, :S_sb[b]], fl_np[b])
             np.testing.assert_array_equal(vis_np[b, ch].astype(np.int64), V)
             np.testing.assert_array_equal(w_np[b], W_)
+
+
+@pytest.mark.parametrize("B,Na,S", [(1, 75, 97), (4, 48, 40), (1, 100, 200), (1, 150, 65)])
+@pytest.mark.parametrize("power", [-20, -30])
+def test_f32_split_goes_by_the_receivers_scale(afc, dev, B, Na, S, power):
+    """A sample far below its receiver's others does not take a tile off the
+    bf16 split (among samples of 1e-9, some lie below any bound on a single
+    one): the split's products scale exactly, so samples times 2^power give
+    the visibilities times 2^(2 power) bit for bit."""
+    log(f"xengine f32 scale B={B} Na={Na} S={S} power={power}")
+    z = W.make_channelised(B, 64, S, 2 * Na, "f32", seed=Na + S, device=dev)
+    z[:, :, 0, ::2, 1, 0] = 2.0 ** -33                      # scaled: 2^-53, 2^-63
+    ref, _ = afc.correlate(z, n_spectra=S)
+    got, _ = afc.correlate(z * 2.0 ** power, n_spectra=S)
+    assert torch.equal(got, ref * 2.0 ** (2 * power))
