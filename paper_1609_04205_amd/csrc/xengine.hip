@@ -217,12 +217,13 @@ struct StorePair {
     int32_t* w_sb;
     int N, S;
     bool write_weights, odd;
-    __device__ __forceinline__ void operator()(E r0, E i0v, E r1, E i1v, int I, int Jc, bool flagged) const {
+    __device__ __forceinline__ void operator()(E r0, E i0v, E r1, E i1v, int I, int Jc, bool flagged,
+                                               bool skip = false) const {
         // the even lane sends its p = 1 values, the odd lane its p = 0 values
         const E yr = pair_swap(odd ? r0 : r1), yi = pair_swap(odd ? i0v : i1v);
         E o0 = odd ? yr : r0, o1 = odd ? yi : i0v, o2 = odd ? r1 : yr, o3 = odd ? i1v : yi;
         const int a = I >> 1, b = Jc >> 1;
-        if (Jc >= N || I >= N || a < b) return;
+        if (Jc >= N || I >= N || a < b || skip) return;
         if (a == b) {             // inputs equal for (0, 0) and (1, 1)
             if (odd) o3 = E(0);
             else o1 = E(0);
@@ -892,12 +893,17 @@ __device__ __forceinline__ float max3_abs(float x, float y, float m) { return fm
 __device__ __forceinline__ bool out_of_split(float mx) { return !(mx < kSplitMax) || (mx > 0.0f && mx < kSplitMin); }
 
 // kFull: an off-diagonal tile with all rows and columns below N (no block of
-// it is skipped).  False if a receiver is out of the split's range; the tile is
-// then not stored.
+// it is skipped).  False if antennas are out of the split's range: bit a of
+// bad_rows (bad_cols) for antenna a of the row (column) panel.  Their baselines
+// are left to the fp32 MFMAs, the others are stored all the same, so that a
+// baseline's bits depend on its own antennas only, whichever share its tile;
+// if every baseline is left (a panel without an antenna in range) the tile ends
+// there.
 template <int TILE, bool kFull>
 __device__ __forceinline__ bool xtile_split(const char* __restrict__ z, char* __restrict__ vis_ch,
                                             int32_t* __restrict__ w_sb, const uint8_t* __restrict__ fl_sb,
-                                            int N, int S, int ti, int tj, bool write_weights, char* lds) {
+                                            int N, int S, int ti, int tj, bool write_weights, char* lds,
+                                            uint64_t& bad_rows, uint64_t& bad_cols) {
     constexpr int RB = 64, NC = TILE == 128 ? 2 : 1, NR = TILE == 128 ? 4 : 2;
     constexpr int kPan = TILE == 128 ? 2 : 1;            // panels a thread stages; one: its half of the workgroup's
     constexpr int kSplitPlane = split_plane<TILE>(), kSplitPanel = split_panel<TILE>();
@@ -1039,14 +1045,21 @@ __device__ __forceinline__ bool xtile_split(const char* __restrict__ z, char* __
                 accR[i][x] = accI[i][x] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
             }
     };
-    // a receiver out of range stops the tile: the wave that meets one raises the
-    // workgroup's flag before the barrier of the step that folds, and every
-    // wave reads it after that barrier (no wave writes it before it is read)
+    // the antennas out of range, [panel][TILE / 2]: a thread that meets one
+    // raises its flag before the barrier of the step that folds, and every wave
+    // reads them after that barrier (no wave writes them before they are read);
+    // a 64-wide tile's 32 flags twice in the 64 bits
     int* const bad = reinterpret_cast<int*>(lds + 4 * kSplitPanel);
     auto raise = [&]() {
-        if (__any(out_of_split(mx[0]) || out_of_split(mx[kPan - 1])) && lane == 0) *bad = 1;
+#pragma unroll
+        for (int pn = 0; pn < kPan; ++pn)
+            if (out_of_split(mx[pn])) bad[(kPan == 1 ? rh : pn) * (TILE / 2) + (srow >> 1)] = 1;
     };
-    if (tid == 0) *bad = 0;
+    auto read_bad = [&]() {
+        bad_rows = __ballot(bad[lane & (TILE / 2 - 1)] != 0);
+        bad_cols = diag ? bad_rows : __ballot(bad[TILE / 2 + (lane & (TILE / 2 - 1))] != 0);
+    };
+    if (tid < TILE) bad[tid] = 0;
     using S0 = std::integral_constant<int, 0>;
     using S1 = std::integral_constant<int, kDepth - 1>;
     load(0, S0{});
@@ -1079,14 +1092,17 @@ __device__ __forceinline__ bool xtile_split(const char* __restrict__ z, char* __
         lds_barrier();
     };
     for (int k = 0; k < n_k; k += 2) {
-        if (inner == 0 && __builtin_amdgcn_readfirstlane(*bad)) return false;
+        if (inner == 0) {
+            read_bad();
+            if (~bad_rows == 0 || ~bad_cols == 0) return false;
+        }
         step(k, S1{});
         if (k + 1 < n_k) step(k + 1, S0{});
     }
     fold();
     raise();
     lds_barrier();
-    if (__builtin_amdgcn_readfirstlane(*bad)) return false;
+    read_bad();
 
     const StorePair<float> st{vis_ch, w_sb, N, S, write_weights, (lc & 1) != 0};
     auto flag_of = [&](int rcv) { return fl_sb && fl_sb[min(rcv, N - 1) >> 1] != 0; };
@@ -1098,31 +1114,34 @@ __device__ __forceinline__ bool xtile_split(const char* __restrict__ z, char* __
 #pragma unroll
     for (int x = 0; x < NC; ++x) {
         const int Jc = j0 + bn[x] * 16 + lc;
-        const bool fc = flag_of(Jc);
+        const bool fc = flag_of(Jc), skip_c = bad_cols >> ((Jc - j0) >> 1) & 1;
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
             if (!on[i][x]) continue;
 #pragma unroll
-            for (int r = 0; r < 4; r += 2)
-                st(outR[i][x][r], outI[i][x][r], outR[i][x][r + 1], outI[i][x][r + 1],
-                   i0 + (NR * rh + i) * 16 + 4 * lg + r, Jc, fc || fr[i][r >> 1]);
+            for (int r = 0; r < 4; r += 2) {
+                const int row = (NR * rh + i) * 16 + 4 * lg + r;
+                st(outR[i][x][r], outI[i][x][r], outR[i][x][r + 1], outI[i][x][r + 1], i0 + row, Jc,
+                   fc || fr[i][r >> 1], skip_c || (bad_rows >> (row >> 1) & 1));
+            }
         }
     }
-    return true;
+    return (bad_rows | bad_cols) == 0;
 }
 
 // One fp32 tile on the fp32 matrix cores: 2 x 2 waves of one 32 x 32 block
 // each (threads tid 0..255), samples staged through the registers of kStagers
 // threads (512: four more waves that only stage; all loads in flight then fit
-// in 128 registers).  The tiles
-// whose samples the bf16 split cannot hold take it (see out_of_split); sums in two levels of 64 spectra.  `z` points at
-// channel ch of subband sb; off: the tile is only stepped through (its
-// barriers), neither multiplied nor stored.
+// in 128 registers), sums in two levels of 64 spectra.  The baselines of
+// antennas whose samples the bf16 split cannot hold take it (see out_of_split):
+// bits of rows and cols, the 32 antennas of either panel; the others are not
+// stored.  `z` points at channel ch of subband sb; off: the tile is only
+// stepped through (its barriers), neither multiplied nor stored.
 template <int DT, int TILE, int kStagers>
 __device__ __forceinline__ void xtile_f32(const char* __restrict__ z, char* __restrict__ vis_ch,
                                       int32_t* __restrict__ w_sb, const uint8_t* __restrict__ fl_sb,
                                       int N, int Na, int S, int ti, int tj, bool write_weights,
-                                      char* lds_raw, int tid, bool off) {
+                                      char* lds_raw, int tid, bool off, uint32_t rows, uint32_t cols) {
     using Tr = XT<DT>;
     constexpr int RB = Tr::RB, PLANES = Tr::PLANES, kStg = stage_blocks<DT, TILE>();
     constexpr int WT = TILE / 2, MB = WT / 32;
@@ -1138,7 +1157,9 @@ __device__ __forceinline__ void xtile_f32(const char* __restrict__ z, char* __re
     const int wr = wid >> 1, wc = wid & 1;
     const int i0 = ti * TILE, j0 = tj * TILE;
     const bool diag = ti == tj;
-    const bool wave_on = !off && wid < 4 && !(diag && wr < wc);
+    static_assert(TILE == 64, "32 antennas a panel, 16 a wave's rows and columns");
+    const bool wave_on = !off && wid < 4 && !(diag && wr < wc) &&
+                         ((rows >> (16 * wr) | cols >> (16 * wc)) & 0xFFFFu) != 0;
     const int nb = (S + kSBlk - 1) / kSBlk;
     const int tail_valid = S - (nb - 1) * kSBlk;             // spectra in the last block
     const int n_stages = (nb + kStg - 1) / kStg;
@@ -1346,7 +1367,7 @@ __device__ __forceinline__ void xtile_f32(const char* __restrict__ z, char* __re
                 const int I = i0 + wr * WT + m * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
                 if (I >= N) continue;
                 const int a = I >> 1, p = I & 1;
-                if (a < b) continue;
+                if (a < b || ((rows >> ((I - i0) >> 1) | cols >> ((J - j0) >> 1)) & 1u) == 0) continue;
                 const bool flagged = fb || frow[m][((r >> 2) << 1) | ((r >> 1) & 1)];
                 const int64_t bl = (int64_t)a * (a + 1) / 2 + b;
                 const int64_t e = bl * 4 + p * 2 + qq;
@@ -1368,16 +1389,19 @@ __device__ __forceinline__ void xtile(const char* __restrict__ z, char* __restri
                                       int32_t* __restrict__ w_sb, const uint8_t* __restrict__ fl_sb,
                                       int N, int Na, int S, int ti, int tj, bool write_weights, char* lds_raw) {
     if constexpr (DT == AFC_F32) {
-        static_assert(4 * split_panel<TILE>() + 16 <= lds_bytes<DT, TILE>(), "two buffers of two panels and the flag");
+        static_assert(4 * split_panel<TILE>() + 4 * TILE <= lds_bytes<DT, TILE>(), "two buffers of two panels and the flags");
+        uint64_t rows = ~0ull, cols = ~0ull;
         const bool full = ti != tj && (ti + 1) * TILE <= N;
         // (one spectrum: the fp32 products round less often than the split's
         // six parts, 3.1e-8 against 3.4e-8 of the result)
-        if (S > 1 && (full ? xtile_split<TILE, true>(z, vis_ch, w_sb, fl_sb, N, S, ti, tj, write_weights, lds_raw)
-                           : xtile_split<TILE, false>(z, vis_ch, w_sb, fl_sb, N, S, ti, tj, write_weights, lds_raw)))
+        if (S > 1 &&
+            (full ? xtile_split<TILE, true>(z, vis_ch, w_sb, fl_sb, N, S, ti, tj, write_weights, lds_raw, rows, cols)
+                  : xtile_split<TILE, false>(z, vis_ch, w_sb, fl_sb, N, S, ti, tj, write_weights, lds_raw, rows, cols)))
             return;
         __syncthreads();
         if constexpr (TILE == 64) {
-            xtile_f32<DT, 64, 512>(z, vis_ch, w_sb, fl_sb, N, Na, S, ti, tj, write_weights, lds_raw, threadIdx.x, false);
+            xtile_f32<DT, 64, 512>(z, vis_ch, w_sb, fl_sb, N, Na, S, ti, tj, write_weights, lds_raw, threadIdx.x, false,
+                                   (uint32_t)rows, (uint32_t)cols);
         } else {
             // the 64-wide quarters, two at a time: waves 0-3 the left ones,
             // waves 4-7 the right ones (above the diagonal on a diagonal
@@ -1385,10 +1409,12 @@ __device__ __forceinline__ void xtile(const char* __restrict__ z, char* __restri
             const int half = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
 #pragma unroll 1
             for (int r = 0; r < 2; ++r) {
+                const uint32_t qr = (uint32_t)(rows >> (32 * r)), qc = (uint32_t)(cols >> (32 * half));
+                if (qr == 0 && cols == 0) continue;
                 const int qi = 2 * ti + r, qj = 2 * tj + half;
                 const bool off = qi < qj || qi * 64 >= N || qj * 64 >= N;
                 xtile_f32<DT, 64, 256>(z, vis_ch, w_sb, fl_sb, N, Na, S, qi, qj, write_weights,
-                                  lds_raw + half * lds_f32_bytes<64>(), threadIdx.x & 255, off);
+                                       lds_raw + half * lds_f32_bytes<64>(), threadIdx.x & 255, off, qr, qc);
             }
         }
     } else {

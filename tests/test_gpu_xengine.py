@@ -342,3 +342,38 @@ def test_f32_split_goes_by_the_receivers_scale(afc, dev, B, Na, S, power):
     ref, _ = afc.correlate(z, n_spectra=S)
     got, _ = afc.correlate(z * 2.0 ** power, n_spectra=S)
     assert torch.equal(got, ref * 2.0 ** (2 * power))
+
+
+# fp32 tiles of one subband alone and of all together: 64 and 128 wide at 48
+# antennas, 128 (with a tile off the diagonal) and 64 at 100
+@pytest.mark.parametrize("B,Na,S", [(4, 48, 300), (2, 100, 200), (2, 100, 33)])
+@pytest.mark.parametrize("case", ["inf", "large", "late", "small", "all"])
+def test_f32_out_of_range_antennas_leave_the_others_alone(afc, dev, B, Na, S, case):
+    """A baseline's bits depend on the samples of its own two antennas: one that
+    the bf16 split cannot hold changes no bit of the others' visibilities, and
+    its own are the same in tiles of either width, weights and flags too."""
+    log(f"xengine f32 out-of-range antennas B={B} Na={Na} S={S} {case}")
+    z = W.make_channelised(B, 64, S, 2 * Na, "f32", seed=Na, device=dev)
+    fl = torch.zeros((B, Na), dtype=torch.uint8, device=dev)
+    fl[:, 5] = 1
+    ref, wref = afc.correlate(z, n_spectra=S, flags=fl)
+    y, ants = z.clone(), [3, Na - 2]
+    for a in ants if case != "all" else range(Na):
+        if case == "inf":
+            y[:, :, 0, 2 * a + 1, 2, 1] = np.inf
+        elif case == "large":
+            y[:, :, :, 2 * a] *= 2.0 ** 55
+        elif case == "late":
+            y[:, :, (S - 1) // 8, 2 * a, (S - 1) % 8, 0] = 2.0 ** 51
+        else:
+            y[:, :, :, 2 * a:2 * a + 2] *= 2.0 ** -56
+    got, w = afc.correlate(y, n_spectra=S, flags=fl)
+    assert torch.equal(w, wref)
+    if case != "all":
+        a, c = np.tril_indices(Na)
+        rest = torch.from_numpy(~(np.isin(a, ants) | np.isin(c, ants))).to(dev)
+        assert torch.equal(got[:, :, rest], ref[:, :, rest])
+    for b in range(B):
+        v1, w1 = afc.correlate(y[b:b + 1].contiguous(), n_spectra=S, flags=fl[b:b + 1])
+        assert torch.equal(v1[0].view(torch.int32), got[b].view(torch.int32)), b
+        assert torch.equal(w1[0], w[b])
