@@ -574,8 +574,9 @@ size_t imaging_workspace_bytes(int Na, int B, int N) {
     const int64_t n_cross = (int64_t)Na * (Na - 1) / 2;
     const int64_t n_part = ceil_div(std::max<int64_t>(1, n_cross * B), 256);
     return (size_t)N * N * 16                      // fixed-point grid
-           + (size_t)N * N * 8 * 2                 // the imager's plane, partial sums of the gridding
-           + (size_t)N / 2 * 8
+           + (size_t)N * N * 8                     // the imager's plane
+           + (size_t)N * N * 8 + (size_t)N / 2 * 8 // partial sums of the gridding, and room that callers' workspaces
+                                                   // have held besides (the size is part of the interface)
            + (size_t)n_part * 16 + 64;             // partial sums, two scales
 }
 
@@ -586,8 +587,10 @@ hipError_t launch_grid(const float2* vis, const int32_t* weights, const double* 
     const int64_t n_part = ceil_div(n_thr, 256);              // pairs of doubles the workspace holds
     char* w = reinterpret_cast<char*>(ws);
     unsigned long long* fixed = reinterpret_cast<unsigned long long*>(w);
-    char* planes = w + (size_t)N * N * 16;                    // the imager's, free here
-    Sums* tail = reinterpret_cast<Sums*>(planes + (size_t)N * N * 16 + (size_t)N / 2 * 8);
+    // partial sums: behind the imager's plane (an image may be formed from the
+    // last grid in the same workspace meanwhile) and in the workspace's tail
+    Sums* est = reinterpret_cast<Sums*>(w + (size_t)N * N * 24);
+    Sums* tail = reinterpret_cast<Sums*>(w + (size_t)N * N * 32 + (size_t)N / 2 * 8);
     Scale* scale = reinterpret_cast<Scale*>(tail + n_part);
     GridArgs g{vis, weights, pos, freq, Na, B, N, 1.0 / (kC * du), 1.0 / du};
     const int64_t n_words = (int64_t)N * N * 2;
@@ -597,12 +600,11 @@ hipError_t launch_grid(const float2* vis, const int32_t* weights, const double* 
     // 128 23 us.
     const int stride = (int)std::min<int64_t>(64, std::max<int64_t>(1, n_thr >> 13));
     const int64_t n_sample = ceil_div(n_thr, 4 * stride) * 4;
-    // workgroups: enough to clear the grid as well; their partial sums lie in
-    // the first half of the planes
-    const int64_t half = (int64_t)N * N / 2;
+    // workgroups: enough to clear the grid as well; their partial sums take the
+    // first half of the room behind the plane
+    const int64_t half = (int64_t)N * N / 4;
     const int n_est = (int)std::min<int64_t>(std::max<int64_t>(ceil_div(n_sample * (kP / kBatch), 256), n_words / 1024),
                                              std::min<int64_t>(half, 2048));
-    Sums* est = reinterpret_cast<Sums*>(planes);
     hipLaunchKernelGGL(grid_estimate_kernel, dim3(n_est), dim3(256), 0, stream, g, n_cross, n_sample, stride, est, fixed,
                        n_words);
     const int n_blk = (int)ceil_div(Na, kGB);
@@ -613,8 +615,8 @@ hipError_t launch_grid(const float2* vis, const int32_t* weights, const double* 
     // grid, so no more parts than that.
     const int64_t n_pair = (int64_t)n_blk * (n_blk + 1) / 2;
     // (the sums of the parts lie in the tail of the workspace, or, more than it
-    // holds, in the second half of the planes: without a split at most one per
-    // subband, that is)
+    // holds, in the second half of the room behind the plane, 256 or more:
+    // without a split at most one per subband, that is)
     const int64_t cap = std::max<int64_t>(n_part, half);
     int n_split = 1;
     while (n_split < 4 && n_pair * B * n_split < 768 && n_pair * B * n_split * 2 <= cap) n_split *= 2;

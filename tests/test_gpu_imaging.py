@@ -278,6 +278,29 @@ def test_points_on_the_edge_of_the_grid(afc, dev, du, waves):
     assert np.abs(_cg(grid) - G).max() <= 1e-6 * np.abs(G).max()
 
 
+@pytest.mark.parametrize("Na,B,N", [(9, 1, 32), (2, 256, 32), (97, 8, 64), (300, 1, 128)])
+def test_gridding_and_imaging_share_no_workspace(afc, dev, Na, B, N):
+    """A snapshot may be imaged while the next is gridded in the same workspace
+    on another stream: neither writes where the other does."""
+    rng = np.random.default_rng(Na)
+    pos = torch.from_numpy(rng.uniform(-12, 12, size=(Na, 2))).to(dev)
+    V = torch.randn((B, 64, Na * (Na + 1) // 2, 2, 2, 2), device=dev)
+    log(f"imaging workspace Na={Na} B={B} N={N}")
+    im = afc.Imager(pos, B, N, 1.0)
+
+    def written(call):
+        im.ws.fill_(0xA5)
+        call()
+        once = im.ws != 0xA5
+        im.ws.fill_(0x5A)
+        out = call()
+        return once | (im.ws != 0x5A), out
+
+    by_grid, grid = written(lambda: im.grid(V, torch.from_numpy(_freqs(B)).to(dev)))
+    by_image, _ = written(lambda: im.image(grid))
+    assert by_grid.any() and by_image.any() and not (by_grid & by_image).any()
+
+
 @pytest.mark.parametrize("N", [32, 64, 128, 256, 512, 1024, 2048, 4096])
 def test_image_every_size_matches_fft(afc, dev, N):
     """Every transform size against numpy's float64 FFT of the same grid:
