@@ -556,6 +556,7 @@ struct afc_plan {
         bool used = false;
         int tile = 128;
         int groups = 1;
+        bool i8_only = true;
         int n_wg = 0;
         int n_items = 0;
         XWork* d_work = nullptr;
@@ -658,10 +659,10 @@ int upload_mode(afc_plan* p, int m, int tile) {
     md.ranges = ranges;
     md.n_wg = xengine_list_grid(ranges);
     md.n_items = (int)work.size();
-    bool i8_only = true;
+    md.i8_only = true;
     for (int b = 0; b < p->d.n_subbands; ++b)
-        if (in_mode(*p, m, p->dt[b])) i8_only &= p->dt[b] == AFC_I8;
-    md.groups = i8_only && tile == 64 ? xengine_i8_groups(md.n_items) : 1;
+        if (in_mode(*p, m, p->dt[b])) md.i8_only &= p->dt[b] == AFC_I8;
+    md.groups = md.i8_only && tile == 64 ? xengine_i8_groups(md.n_items) : 1;
     if (!md.used) return AFC_OK;
     hipError_t e = hipMalloc(&md.d_work, work.size() * sizeof(XWork));
     if (e == hipSuccess) e = hipMemcpy(md.d_work, work.data(), work.size() * sizeof(XWork), hipMemcpyHostToDevice);
@@ -776,7 +777,7 @@ int tune_mode0(afc_plan* p, TuneChoice& out) {
                 const afc_plan::Mode& md = p->mode[m];
                 if (e == hipSuccess && md.used)
                     e = launch_xengine_list(z, vis, nullptr, nullptr, p->d_sbs, md.d_work, md.ranges, p->N, p->Na, 0,
-                                            md.tile, md.groups, nullptr);
+                                            md.tile, md.groups, md.i8_only, nullptr);
             }
             if (e == hipSuccess) e = hipEventRecord(e1, nullptr);
             if (e == hipSuccess) e = hipEventSynchronize(e1);
@@ -857,7 +858,7 @@ int capture_plan(afc_plan* p, const int16_t* x, const float* taps, const std::ve
         const afc_plan::Mode& md = p->mode[m];
         if (!md.used) continue;
         le = launch_xengine_list(z_workspace, vis, weights, flags, p->d_sbs, md.d_work, md.ranges, p->N, p->Na,
-                                 m == 1 ? 1 : 0, md.tile, md.groups, p->cap_stream);
+                                 m == 1 ? 1 : 0, md.tile, md.groups, md.i8_only, p->cap_stream);
     }
     e = hipStreamEndCapture(p->cap_stream, &c->graph);
     if (le != hipSuccess || e != hipSuccess) {

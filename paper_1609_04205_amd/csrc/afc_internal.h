@@ -124,10 +124,11 @@ struct XcdRanges {
 // One workgroup per work item (workgroup ids go round-robin over the 8
 // XCDs); mode 0: int8 / fp16 subbands with tile-wide tiles (128 or 64),
 // mode 1: fp32 subbands (128 or 64).  groups > 1 (xengine_i8_groups) only for
-// 64-wide tiles of int8 subbands.
+// 64-wide tiles of a list of int8 subbands (i8_only): the kernels of several
+// groups hold no other type, and any other call is refused.
 hipError_t launch_xengine_list(const void* z_ws, void* vis, int32_t* weights, const uint8_t* flags,
                                const XSubband* sbs_dev, const XWork* work_dev, const XcdRanges& ranges,
-                               int N, int Na, int mode, int tile, int groups, hipStream_t stream);
+                               int N, int Na, int mode, int tile, int groups, bool i8_only, hipStream_t stream);
 int xengine_list_grid(const XcdRanges& ranges);
 // tile width of the int8 / fp16 correlator for N receivers and subbands of
 // types dt and lengths S

@@ -1674,7 +1674,8 @@ int xengine_list_grid(const XcdRanges& r) {
 
 hipError_t launch_xengine_list(const void* z_ws, void* vis, int32_t* weights, const uint8_t* flags,
                                const XSubband* sbs_dev, const XWork* work_dev, const XcdRanges& ranges, int N,
-                               int Na, int mode, int tile, int groups, hipStream_t stream) {
+                               int Na, int mode, int tile, int groups, bool i8_only, hipStream_t stream) {
+    if (groups > 1 && !(mode == 0 && tile == 64 && i8_only)) return hipErrorInvalidValue;
     const char* z = reinterpret_cast<const char*>(z_ws);
     char* v = reinterpret_cast<char*>(vis);
     const int g = xengine_list_grid(ranges);

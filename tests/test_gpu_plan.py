@@ -118,6 +118,15 @@ def test_plan_small_int8(afc, dev, S_list):
     assert info.tile == 64 and info.n_work_items == 192 * len(S_list)
 
 
+@pytest.mark.parametrize("dtypes", [["i8", "f16"], ["f16"], ["i8", "f32"], ["f32"]])
+def test_plan_small_without_groups(afc, dev, dtypes):
+    """Small lists that hold another type than int8 take one group of waves per
+    tile (the kernels of several hold int8 alone), and those of int8 beside a
+    list of fp32 several."""
+    log(f"plan small {dtypes}")
+    _run_plan(afc, dev, 40, [300, 47][:len(dtypes)], dtypes, np.zeros((len(dtypes), 40), np.uint8))
+
+
 def test_plan_f32_subbands(afc, dev):
     log("plan fp32 + int8")
     Na = 24

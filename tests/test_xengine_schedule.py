@@ -60,6 +60,40 @@ def test_every_stage_once_and_unclamped_loads_in_the_data(k_stg, depth, ring):
         assert issued == list(range(n_st))
 
 
+@pytest.mark.parametrize("groups", [1, 2, 4])
+@pytest.mark.parametrize("depth", [1, 2, 3])
+@pytest.mark.parametrize("k_stg", [2, 4])
+@pytest.mark.parametrize("last_block", [1, 8])
+def test_groups_of_waves_share_the_stages(groups, depth, k_stg, last_block):
+    """Groups of waves (tiles without the column-register ring): stage st of
+    group kg is stage st * groups + kg of the integration, and all groups run
+    the same number of stages (their barriers are the workgroup's).  Each stage
+    of the integration is multiplied by one group, every stage before a group's
+    last, whose operands are not masked, holds whole blocks of whole spectra
+    only, and clamped loads lie inside the data."""
+    for nb in range(1, 400):
+        n_st = -(-nb // (k_stg * groups))
+        whole = []
+        for kg in range(groups):
+            issued = [s for s in range(min(depth + 1, n_st))]             # the prologue
+            for st in range(n_st):
+                if st + 1 < n_st and st + 1 + depth < n_st:
+                    issued.append(st + 1 + depth)
+            assert issued == list(range(n_st))
+            for st in range(n_st):
+                ws = st * groups + kg
+                whole.append(ws)
+                if st < n_st - 1:
+                    assert (ws + 1) * k_stg <= (nb if last_block == 8 else nb - 1)
+                for bl in range(k_stg):                      # offset of block bl after the clamp
+                    voff, soff = bl, ws * k_stg
+                    if (ws + 1) * k_stg > nb:
+                        voff, soff = bl + min(ws * k_stg + bl, nb - 1) - bl, 0
+                    assert 0 <= voff + soff < nb
+        assert sorted(whole) == list(range(n_st * groups))
+        assert n_st * groups * k_stg >= nb
+
+
 def test_unclamped_last_stage_is_caught():
     """The check itself: a ring-less tile that skipped the clamp in its main
     loop would issue the last stage unclamped."""
