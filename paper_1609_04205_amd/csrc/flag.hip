@@ -16,12 +16,10 @@ namespace afc {
 namespace {
 
 constexpr int kClipChunk = 4096;   // baselines per partial sum of stage 1
-constexpr int kClipBl = 64;         // baselines per workgroup of the flagging pass
-constexpr int kClipG = 8;           // channel groups per workgroup of the flagging pass
-constexpr int kClipHeld = 8;        // channels a thread can hold: 64 channels in all
+constexpr int kClipThreads = 512;   // of the flagging pass
 
-// whether bl = a(a+1)/2 + b has a = b, bl = a(a+3)/2 (bl < 2^23: 4096 antennas;
-// the float32 root is within one of a)
+// whether bl = a(a+1)/2 + b has a = b, bl = a(a+3)/2 (bl < 4096 * 4097 / 2; the
+// float32 root is within one of a)
 __device__ __forceinline__ bool is_auto(int bl) {
     const int r = (int)((sqrtf(8.0f * (float)bl + 9.0f) - 3.0f) * 0.5f);
     bool hit = false;
@@ -32,6 +30,9 @@ __device__ __forceinline__ bool is_auto(int bl) {
 
 __device__ __forceinline__ double abs2(float2 v) { return (double)v.x * v.x + (double)v.y * v.y; }
 
+// Partial sums of stage 1: a workgroup per chunk and channel.  kAll: all loads
+// of a thread in flight (baselines past the last repeat it and are not added).
+template <bool kAll>
 __global__ __launch_bounds__(256) void clip_partial_kernel(int nbl, const float2* __restrict__ V,
                                                            double* __restrict__ part, int n_chunks) {
     __shared__ double red[2][256];
@@ -39,13 +40,27 @@ __global__ __launch_bounds__(256) void clip_partial_kernel(int nbl, const float2
     const int bl0 = c * kClipChunk, bl1 = min(nbl, bl0 + kClipChunk);
     const float2* v = V + (int64_t)ch * nbl * 4;
     double xx = 0.0, yy = 0.0;
-#pragma unroll 4
-    for (int bl = bl0 + tid; bl < bl1; bl += 256) {
-        const float2 x = v[(int64_t)bl * 4], y = v[(int64_t)bl * 4 + 3];
+    auto add = [&](int bl, float2 x, float2 y) {
         if (!is_auto(bl)) {
             xx += abs2(x);
             yy += abs2(y);
         }
+    };
+    if constexpr (kAll) {
+        constexpr int kPer = kClipChunk / 256;
+        float2 x[kPer], y[kPer];
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const int64_t bl = min(bl0 + k * 256 + tid, bl1 - 1);
+            x[k] = v[bl * 4];
+            y[k] = v[bl * 4 + 3];
+        }
+#pragma unroll
+        for (int k = 0; k < kPer; ++k)
+            if (bl0 + k * 256 + tid < bl1) add(bl0 + k * 256 + tid, x[k], y[k]);
+    } else {
+#pragma unroll 4
+        for (int bl = bl0 + tid; bl < bl1; bl += 256) add(bl, v[(int64_t)bl * 4], v[(int64_t)bl * 4 + 3]);
     }
     red[0][tid] = xx;
     red[1][tid] = yy;
@@ -70,21 +85,23 @@ __global__ void clip_mean_kernel(int P, int n_chunks, int64_t n_cross, const dou
     mean[e] = n_cross > 0 ? s / (double)n_cross : 0.0;
 }
 
-// Both stages for 64 baselines: thread (baseline, group g) takes the channels
-// g, g + 8, ..., both polarisations; stage 1 as they are read, the baseline's
-// mean over the channels that pass it by a sum over the groups, stage 2 and the
-// flags.  kHeld (up to 64 channels): the |V|^2 stay in registers, so that V is
-// read once (a flag pass, and one thread per baseline and polarisation that
-// read V and the flags twice, took 14 + 60 us at 288 antennas x 64 channels
-// against 25 us); otherwise V is read again for stage 2.
-template <bool kHeld>
-__global__ __launch_bounds__(kClipBl* kClipG) void clip_flags_kernel(int P, int nbl, const float2* __restrict__ V,
-                                                                     const double* __restrict__ mean, double k2,
-                                                                     uint8_t* __restrict__ flags) {
-    __shared__ double sum[kClipG][2][kClipBl];
-    __shared__ int cnt[kClipG][2][kClipBl];
-    const int lane = threadIdx.x % kClipBl, g = threadIdx.x / kClipBl;
-    const int bl = blockIdx.x * kClipBl + lane;
+// Both stages for kBl baselines: thread (baseline, group g of kG) takes the
+// channels g, g + kG, ..., both polarisations; stage 1 as they are read, the
+// baseline's mean over the channels that pass it by a sum over the groups, stage
+// 2 and the flags.  kH: channels a thread holds, so that V is read once (a flag
+// pass, and one thread per baseline and polarisation that read V and the flags
+// twice, took 14 + 60 us at 288 antennas x 64 channels against 25 us); 0: V is
+// read again for stage 2.
+template <int kG, int kH>
+__global__ __launch_bounds__(kClipThreads) void clip_flags_kernel(int P, int nbl, const float2* __restrict__ V,
+                                                                  const double* __restrict__ mean, double k2,
+                                                                  uint8_t* __restrict__ flags) {
+    constexpr int kBl = kClipThreads / kG;
+    constexpr bool kHeld = kH > 0;
+    __shared__ double sum[kG][2][kBl];
+    __shared__ int cnt[kG][2][kBl];
+    const int lane = threadIdx.x % kBl, g = threadIdx.x / kBl;
+    const int bl = blockIdx.x * kBl + lane;
     const bool live = bl < nbl;
     const float2* v = V + (int64_t)(live ? bl : 0) * 4;
     const int64_t ch_stride = (int64_t)nbl * 4;
@@ -105,11 +122,11 @@ __global__ __launch_bounds__(kClipBl* kClipG) void clip_flags_kernel(int P, int 
             f[(int64_t)ch * nbl * 2 + 1] = y ? 1 : 0;
         }
     };
-    double a2[kHeld ? kClipHeld : 1][2];
-    bool hit[kHeld ? kClipHeld : 1][2];
+    double a2[kHeld ? kH : 1][2];
+    bool hit[kHeld ? kH : 1][2];
     if constexpr (kHeld) {
 #pragma unroll
-        for (int c = 0; c < kClipHeld; ++c) first(min(g + c * kClipG, P - 1), a2[c], hit[c]);
+        for (int c = 0; c < kH; ++c) first(min(g + c * kG, P - 1), a2[c], hit[c]);
     }
     auto add = [&](const double (&a)[2], const bool (&h)[2]) {
 #pragma unroll
@@ -121,10 +138,10 @@ __global__ __launch_bounds__(kClipBl* kClipG) void clip_flags_kernel(int P, int 
     };
     if constexpr (kHeld) {
 #pragma unroll
-        for (int c = 0; c < kClipHeld; ++c)
-            if (g + c * kClipG < P) add(a2[c], hit[c]);
+        for (int c = 0; c < kH; ++c)
+            if (g + c * kG < P) add(a2[c], hit[c]);
     } else {
-        for (int ch = g; ch < P; ch += kClipG) {
+        for (int ch = g; ch < P; ch += kG) {
             first(ch, a2[0], hit[0]);
             add(a2[0], hit[0]);
         }
@@ -142,7 +159,7 @@ __global__ __launch_bounds__(kClipBl* kClipG) void clip_flags_kernel(int P, int 
         double t = 0.0;
         int m = 0;
 #pragma unroll
-        for (int q = 0; q < kClipG; ++q) {
+        for (int q = 0; q < kG; ++q) {
             t += sum[q][p][lane];
             m += cnt[q][p][lane];
         }
@@ -151,12 +168,12 @@ __global__ __launch_bounds__(kClipBl* kClipG) void clip_flags_kernel(int P, int 
     }
     if constexpr (kHeld) {
 #pragma unroll
-        for (int c = 0; c < kClipHeld; ++c)
-            if (g + c * kClipG < P)
-                store(g + c * kClipG, hit[c][0] || (any[0] && a2[c][0] > limit[0]),
+        for (int c = 0; c < kH; ++c)
+            if (g + c * kG < P)
+                store(g + c * kG, hit[c][0] || (any[0] && a2[c][0] > limit[0]),
                       hit[c][1] || (any[1] && a2[c][1] > limit[1]));
     } else {
-        for (int ch = g; ch < P; ch += kClipG) {
+        for (int ch = g; ch < P; ch += kG) {
             first(ch, a2[0], hit[0]);
             store(ch, hit[0][0] || (any[0] && a2[0][0] > limit[0]), hit[0][1] || (any[1] && a2[0][1] > limit[1]));
         }
@@ -190,14 +207,32 @@ hipError_t launch_sigma_clip(int Na, int P, const float2* V, float k, uint8_t* f
     double* part = reinterpret_cast<double*>(ws);
     double* mean = part + (size_t)P * 2 * nc;
     const double k2 = (double)k * (double)k;
-    hipLaunchKernelGGL(clip_partial_kernel, dim3(nc, P), dim3(256), 0, stream, (int)nbl, V, part, nc);
+    // A workgroup or two per CU: a thread's 16 loads all in flight (1000 antennas
+    // x 4 channels, 492 workgroups, 36 us for all three launches); more of them
+    // hide the latency of four at a time and fit a CU then (576 x 16, 656
+    // workgroups: 38.5 us with all, 37.0 with four); nor does a chunk of less
+    // than half its size gain.
+    if ((int64_t)nc * P <= 512 && nbl > 2048)
+        hipLaunchKernelGGL(clip_partial_kernel<true>, dim3(nc, P), dim3(256), 0, stream, (int)nbl, V, part, nc);
+    else
+        hipLaunchKernelGGL(clip_partial_kernel<false>, dim3(nc, P), dim3(256), 0, stream, (int)nbl, V, part, nc);
     hipLaunchKernelGGL(clip_mean_kernel, dim3((unsigned)ceil_div(P * 2, 64)), dim3(64), 0, stream, P, nc,
                        nbl - Na, part, mean);
-    const dim3 grid((unsigned)ceil_div(nbl, kClipBl)), block(kClipBl * kClipG);
-    if (P <= kClipG * kClipHeld)
-        hipLaunchKernelGGL(clip_flags_kernel<true>, grid, block, 0, stream, P, (int)nbl, V, mean, k2, flags);
-    else
-        hipLaunchKernelGGL(clip_flags_kernel<false>, grid, block, 0, stream, P, (int)nbl, V, mean, k2, flags);
+    // groups and held channels by the number of channels: with eight and eight
+    // for any up to 64, few channels were read several times over (1500 antennas
+    // x 2 channels 169 us for all three launches, 42 now; a pass per stage 83)
+#define AFC_CLIP(G, H)                                                                                          \
+    hipLaunchKernelGGL((clip_flags_kernel<G, H>), dim3((unsigned)ceil_div(nbl, kClipThreads / (G))),            \
+                       dim3(kClipThreads), 0, stream, P, (int)nbl, V, mean, k2, flags)
+    if (P == 1) AFC_CLIP(1, 1);
+    else if (P == 2) AFC_CLIP(2, 1);
+    else if (P <= 4) AFC_CLIP(4, 1);
+    else if (P <= 8) AFC_CLIP(8, 1);
+    else if (P <= 16) AFC_CLIP(8, 2);
+    else if (P <= 32) AFC_CLIP(8, 4);
+    else if (P <= 64) AFC_CLIP(8, 8);
+    else AFC_CLIP(8, 0);
+#undef AFC_CLIP
     return hipGetLastError();
 }
 

@@ -281,3 +281,15 @@ def test_sigma_clip_channel_and_baseline_edges(afc, dev, Na, P):
     log(f"sigma clip edges Na={Na} P={P}")
     f = afc.sigma_clip(torch.from_numpy(V).to(dev), 3.0).cpu().numpy()
     _compare_flags(f, oracle.sigma_clip(V, 3.0), V, 3.0)
+
+
+# groups and channels per thread of the flagging pass change at 1, 2, 4, 8, 16,
+# 32 and 64 channels (512 baselines a workgroup down to 64); all loads of a
+# partial sum in flight from 2049 baselines on (64 antennas) to 512 workgroups
+@pytest.mark.parametrize("P", [1, 2, 3, 4, 5, 8, 9, 16, 17, 32, 33, 64, 65])
+@pytest.mark.parametrize("Na", [3, 32, 64, 128])
+def test_sigma_clip_by_the_number_of_channels(afc, dev, Na, P):
+    V = _rfi_vis(P, Na, seed=Na * 1000 + P)
+    log(f"sigma clip by channels Na={Na} P={P}")
+    f = afc.sigma_clip(torch.from_numpy(V).to(dev), 3.0).cpu().numpy()
+    _compare_flags(f, oracle.sigma_clip(V, 3.0), V, 3.0)
