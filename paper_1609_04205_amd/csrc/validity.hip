@@ -38,8 +38,9 @@ __global__ void validity_kernel(const uint8_t* __restrict__ pkt, uint32_t* __res
     const int n = min(32, S - s0);
     uint32_t bits = n == 32 ? 0xFFFFFFFFu : ((1u << n) - 1u);
     // packets touched by the windows of spectra s0 .. s0+n-1
-    const int64_t k_lo = ((int64_t)s0 << log2Ps) / Q;
-    const int64_t k_hi = (((int64_t)(s0 + n - 1 + kT) << log2Ps) - 1) / Q;
+    // (samples fit 32 bits: a subband's input is below 2^31 values)
+    const int64_t k_lo = ((unsigned)s0 << log2Ps) / (unsigned)Q;
+    const int64_t k_hi = (((unsigned)(s0 + n - 1 + kT) << log2Ps) - 1u) / (unsigned)Q;
     const uint8_t* pb = pkt + (int64_t)b * n_pk * Na + a;
     // clears the spectra whose window [s Ps, (s+T) Ps - 1] meets packet k,
     // samples [k Q, (k+1) Q - 1]: floor(k Q / Ps) - T + 1 to floor(((k+1) Q - 1)
@@ -63,50 +64,65 @@ __global__ void validity_kernel(const uint8_t* __restrict__ pkt, uint32_t* __res
                 if (f[e] == 0) lost(k + e);
         }
     }
-    for (; bits != 0 && k <= k_hi; ++k)
-        if (k >= n_pk || pb[k * Na] == 0) lost(k);           // packets past the last are lost
+    // the rest, and all of it where packets are long, four at a time (one by one
+    // is a chain of loads); packets past the last are lost
+    const int64_t last = min(k_hi, n_pk - 1);
+    for (; bits != 0 && k <= k_hi; k += 4) {
+        uint8_t f[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f[e] = pb[min(k + e, last) * Na];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (k + e <= k_hi && (k + e >= n_pk || f[e] == 0)) lost(k + e);
+    }
     v[((int64_t)b * Wd + wd) * Na + a] = bits;
 }
 
-// One thread = one antenna, one word of 32 spectra and kZeroCh channels; it
-// writes zeros only where a spectrum is invalid (lost data is rare), over both
-// receivers of the antenna: 8, 2 or 1 spectra at a time (kWide: z is 16-byte
-// aligned, and with it every block).  A thread that took all 64 channels,
-// spectrum by spectrum, made a dead station's words a chain of 4096 stores: 311
-// us for 576 antennas x 4 subbands with one station of 48 dead, now 43 us (4
-// channels per thread the same, 16 51 us).
-constexpr int kZeroCh = 8;
-template <typename SampleT, bool kWide>
-__global__ void zero_kernel(const uint32_t* __restrict__ v, SampleT* __restrict__ z, int Na, int S, int Wd,
-                            int Sb) {
-    const int a = blockIdx.x * blockDim.x + threadIdx.x;
-    const int wd = blockIdx.y;
-    const int b = blockIdx.z / (kP / kZeroCh), k0 = blockIdx.z % (kP / kZeroCh) * kZeroCh;
-    if (a >= Na) return;
-    const int s0 = wd * 32;
-    const int n = min(32, S - s0);
-    const uint32_t all = n == 32 ? 0xFFFFFFFFu : ((1u << n) - 1u);
-    const uint32_t bad = ~v[((int64_t)b * Wd + wd) * Na + a] & all;
-    if (bad == 0) return;
+// A workgroup looks at four words of 32 spectra of 64 antennas, a word per
+// wave; losses are rare, and it ends there if it has none.  Else the waves share
+// the channels and take the four words one after the other, an antenna per lane:
+// zeros over both receivers, 8, 2 or 1 spectra at a time (kWide: z is 16-byte
+// aligned, and with it every block).  kSplit workgroups share the channels of
+// the words, as many as still start quickly: losses are bursts of whole stations
+// or a dead one, the work of few words.  576 antennas x 4 subbands, int8: 3.6 us
+// without a loss, 48 us with bursts (0.6% of the packets) and a dead station; a
+// thread per antenna and word that took all channels, spectrum by spectrum, 2.8
+// and 363 us, a thread for every eight of the channels 5.9 and 56 us.
+constexpr int kZeroWords = 4;
+template <typename SampleT, bool kWide, int kSplit>
+__global__ __launch_bounds__(64 * kZeroWords) void zero_kernel(const uint32_t* __restrict__ v, SampleT* __restrict__ z,
+                                                               int Na, int S, int Wd, int Sb) {
+    constexpr int kCh = kP / kSplit / kZeroWords;             // channels of a thread
+    __shared__ uint32_t words[kZeroWords][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int a = blockIdx.x * 64 + lane, wd0 = blockIdx.y * kZeroWords, b = blockIdx.z / kSplit;
+    uint32_t own = 0u;
+    if (a < Na && wd0 + wv < Wd) {
+        const int n = min(32, S - (wd0 + wv) * 32);
+        const uint32_t all = n == 32 ? 0xFFFFFFFFu : ((1u << n) - 1u);
+        own = ~v[((int64_t)b * Wd + wd0 + wv) * Na + a] & all;
+    }
+    words[wv][lane] = own;
+    if (!__syncthreads_or(own != 0)) return;
     const int N = 2 * Na;
     const int64_t ch_stride = (int64_t)Sb * N * kSBlk;
-    SampleT* zb = z + ((int64_t)b * kP + k0) * ch_stride;
-    // zeros of 2^E samples at p of both receivers in every channel
+    SampleT* zb = z + ((int64_t)b * kP + (blockIdx.z % kSplit * kZeroWords + wv) * kCh) * ch_stride;
+    // zeros of 2^E samples at p of both receivers in every channel of the thread
     auto put = [&](SampleT* p, auto e_tag) {
         constexpr size_t kRun = sizeof(SampleT) << decltype(e_tag)::value;
         struct alignas(kRun < 16 ? kRun : 16) Run {
             SampleT s[1 << decltype(e_tag)::value];
         };
 #pragma unroll
-        for (int k = 0; k < kZeroCh; ++k) {
+        for (int k = 0; k < kCh; ++k) {
             *reinterpret_cast<Run*>(p + k * ch_stride) = Run{};
             *reinterpret_cast<Run*>(p + k * ch_stride + kSBlk) = Run{};
         }
     };
-    for (int q = 0; q < 4; ++q) {
-        const unsigned m8 = (bad >> (8 * q)) & 0xFFu;
+    for (int e = 0; e < 4 * kZeroWords; ++e) {                // blocks of 8 spectra
+        const unsigned m8 = (words[e >> 2][lane] >> (8 * (e & 3))) & 0xFFu;
         if (m8 == 0) continue;
-        SampleT* p = zb + ((int64_t)(wd * 4 + q) * N + 2 * a) * kSBlk;
+        SampleT* p = zb + ((int64_t)(wd0 * 4 + e) * N + 2 * a) * kSBlk;
         if (kWide && m8 == 0xFFu) {
             put(p, std::integral_constant<int, 3>{});
             continue;
@@ -236,18 +252,26 @@ hipError_t launch_validity(const uint8_t* pkt, uint32_t* v, int B, int Na, int S
 hipError_t launch_zero_invalid(const uint32_t* v, void* z, afc_dtype dt, int B, int Na, int S, hipStream_t stream) {
     const int Wd = (int)ceil_div(S, 32);
     const int Sb = (int)ceil_div(S, kSBlk);
-    const dim3 grid((unsigned)ceil_div(Na, 256), (unsigned)Wd, (unsigned)(B * (kP / kZeroCh)));
     const bool wide = reinterpret_cast<uintptr_t>(z) % 16 == 0;
+    const int64_t n_wg = ceil_div(Na, 64) * ceil_div(Wd, kZeroWords) * B;
+    const int split = n_wg * 8 <= 2048 ? 8 : n_wg * 4 <= 4096 ? 4 : 2;
+    const dim3 grid((unsigned)ceil_div(Na, 64), (unsigned)ceil_div(Wd, kZeroWords), (unsigned)(B * split));
+#define AFC_ZERO_N(T, W, N)                                                                                     \
+    hipLaunchKernelGGL((zero_kernel<T, W, N>), grid, dim3(64 * kZeroWords), 0, stream, v, reinterpret_cast<T*>(z), Na, \
+                       S, Wd, Sb)
+#define AFC_ZERO_W(T, W)                                                                                        \
+    if (split == 8) AFC_ZERO_N(T, W, 8);                                                                        \
+    else if (split == 4) AFC_ZERO_N(T, W, 4);                                                                   \
+    else AFC_ZERO_N(T, W, 2);
 #define AFC_ZERO(T)                                                                                             \
-    if (wide)                                                                                                   \
-        hipLaunchKernelGGL((zero_kernel<T, true>), grid, dim3(256), 0, stream, v, reinterpret_cast<T*>(z), Na, S, Wd, Sb); \
-    else                                                                                                        \
-        hipLaunchKernelGGL((zero_kernel<T, false>), grid, dim3(256), 0, stream, v, reinterpret_cast<T*>(z), Na, S, Wd, Sb);
+    if (wide) { AFC_ZERO_W(T, true) } else { AFC_ZERO_W(T, false) }
     switch (dt) {
         case AFC_F32: AFC_ZERO(float2) break;
         case AFC_F16: AFC_ZERO(Half2Raw) break;
         default: AFC_ZERO(I8x2) break;
     }
+#undef AFC_ZERO_N
+#undef AFC_ZERO_W
 #undef AFC_ZERO
     return hipGetLastError();
 }

@@ -206,3 +206,30 @@ def test_validity_packet_sizes(afc, dev, Na, S, Q, Ps, n_extra):
         full = np.zeros((max(n_pk, -(-(S + 15) * Ps // Q)), Na), np.uint8)
         full[:n_pk] = pkt[b]
         np.testing.assert_array_equal(got[b], oracle.spectrum_validity(full, Q, Ps, 16, S))
+
+
+# a workgroup takes four words of 64 antennas, whole and partial; eight share the
+# channels up to 256 such workgroups, four up to 1024, two above
+@pytest.mark.parametrize("Na,B,S", [(9, 2, 77), (65, 1, 321), (64, 1, 32 * 1030 - 5), (17, 2, 32 * 2060 - 31)])
+@pytest.mark.parametrize("dtype", [torch.int8, torch.float16, torch.float32])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_zeros_of_every_word_pattern(afc, dev, Na, B, S, dtype, offset):
+    """Words with no invalid spectrum, all, whole blocks of 8, pairs and single
+    ones, one antenna of a group or several: exactly the samples of invalid
+    spectra become zero, at 16-byte aligned z (offset 0) and one sample on."""
+    log(f"zero patterns {dtype} Na={Na} B={B} S={S} offset={offset}")
+    g = torch.Generator(device=dev)
+    g.manual_seed(Na + S)
+    Wd, Sb = -(-S // 32), -(-S // 8)
+    words = torch.tensor([-1, 0, 0xFF, 0x7FFF00FF, -4, 0x55555555, -256, 1], dtype=torch.int64, device=dev).to(torch.int32)
+    v = words[torch.randint(0, len(words), (B, Wd, Na), generator=g, device=dev)]
+    v = torch.where(torch.rand((B, Wd, Na), generator=g, device=dev) < 0.7, torch.full_like(v, -1), v).contiguous()
+    shape = (B, 64, Sb, 2 * Na, 8, 2)
+    n = int(np.prod(shape))
+    z = torch.ones(n + 8, dtype=dtype, device=dev)[2 * offset:2 * offset + n].view(shape)
+    bits = (v[:, :, None, :] >> torch.arange(32, device=dev)[None, None, :, None]) & 1          # [B][Wd][32][Na]
+    keep = bits.reshape(B, Wd * 32, Na)[:, :Sb * 8].clone()
+    keep[:, S:] = 1                                         # slots past the last spectrum stay
+    want = keep.view(B, Sb, 8, Na).permute(0, 1, 3, 2).repeat_interleave(2, dim=2)             # [B][Sb][N][8]
+    afc.zero_invalid(z, v, S)
+    assert torch.equal(z, want[:, None, ..., None].to(dtype).expand(shape))
