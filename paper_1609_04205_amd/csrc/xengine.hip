@@ -76,9 +76,6 @@ template <int DT, int TILE>
 constexpr int stage_blocks() {
     return DT == AFC_F32 ? 4 : 64 / XT<DT>::RB;
 }
-// fp32: stages of register-staged loads in flight
-template <int DT, int TILE>
-constexpr int prefetch_depth() { return 2; }
 // int8 and fp16 stage through direct global-to-LDS loads, fp32 through registers
 template <int DT>
 constexpr bool uses_dma() { return DT != AFC_F32; }
@@ -972,6 +969,9 @@ __device__ __forceinline__ bool xtile_split(const char* __restrict__ z, char* __
             split2(v.x, v.y, h.z, m.z, l.z);
             split2(v.z, v.w, h.w, m.w, l.w);
             mx[pn] = max3_abs(u.x, u.y, max3_abs(u.z, u.w, max3_abs(v.x, v.y, max3_abs(v.z, v.w, mx[pn]))));
+            // (taken here: sunk past the next loads, it would keep their registers
+            // and wait for them, 20% of the time at 80 receivers)
+            __asm__ volatile("" : "+v"(mx[pn]));
             char* p = base + pn * kSplitPanel;
             *reinterpret_cast<uint4*>(p) = h;
             *reinterpret_cast<uint4*>(p + kSplitPlane) = m;
@@ -1106,6 +1106,7 @@ __device__ __forceinline__ bool xtile_split(const char* __restrict__ z, char* __
 
     const StorePair<float> st{vis_ch, w_sb, N, S, write_weights, (lc & 1) != 0};
     auto flag_of = [&](int rcv) { return fl_sb && fl_sb[min(rcv, N - 1) >> 1] != 0; };
+    const uint32_t skip_r = (uint32_t)(bad_rows >> (8 * NR * rh)) >> (2 * lg);       // antennas 8 i + r / 2
     bool fr[NR][2];
 #pragma unroll
     for (int i = 0; i < NR; ++i)
@@ -1114,74 +1115,59 @@ __device__ __forceinline__ bool xtile_split(const char* __restrict__ z, char* __
 #pragma unroll
     for (int x = 0; x < NC; ++x) {
         const int Jc = j0 + bn[x] * 16 + lc;
-        const bool fc = flag_of(Jc), skip_c = bad_cols >> ((Jc - j0) >> 1) & 1;
+        const bool fc = flag_of(Jc), skip_c = (uint32_t)(bad_cols >> (8 * bn[x])) >> (lc >> 1) & 1;
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
             if (!on[i][x]) continue;
 #pragma unroll
             for (int r = 0; r < 4; r += 2) {
-                const int row = (NR * rh + i) * 16 + 4 * lg + r;
-                st(outR[i][x][r], outI[i][x][r], outR[i][x][r + 1], outI[i][x][r + 1], i0 + row, Jc,
-                   fc || fr[i][r >> 1], skip_c || (bad_rows >> (row >> 1) & 1));
+                st(outR[i][x][r], outI[i][x][r], outR[i][x][r + 1], outI[i][x][r + 1],
+                   i0 + (NR * rh + i) * 16 + 4 * lg + r, Jc, fc || fr[i][r >> 1],
+                   skip_c || (skip_r >> (8 * i + (r >> 1)) & 1));
             }
         }
     }
     return (bad_rows | bad_cols) == 0;
 }
 
-// One fp32 tile on the fp32 matrix cores: 2 x 2 waves of one 32 x 32 block
-// each (threads tid 0..255), samples staged through the registers of kStagers
-// threads (512: four more waves that only stage; all loads in flight then fit
-// in 128 registers), sums in two levels of 64 spectra.  The baselines of
-// antennas whose samples the bf16 split cannot hold take it (see out_of_split):
-// bits of rows and cols, the 32 antennas of either panel; the others are not
-// stored.  `z` points at channel ch of subband sb; off: the tile is only
-// stepped through (its barriers), neither multiplied nor stored.
-template <int DT, int TILE, int kStagers>
+// One 64-wide fp32 tile on the fp32 matrix cores: 2 x 2 waves of one 32 x 32
+// block each (threads tid 0..255), samples staged through the registers of
+// kStagers threads (512: four more waves that only stage; all loads in flight
+// then fit in 128 registers), sums in two levels of 64 spectra.  The baselines
+// of antennas whose samples the bf16 split cannot hold take it (see
+// out_of_split): bits of rows and cols, the 32 antennas of either panel; the
+// others are not stored.  `z` points at channel ch of subband sb; off: the tile
+// is only stepped through (its barriers), neither multiplied nor stored.
+template <int kStagers>
 __device__ __forceinline__ void xtile_f32(const char* __restrict__ z, char* __restrict__ vis_ch,
-                                      int32_t* __restrict__ w_sb, const uint8_t* __restrict__ fl_sb,
-                                      int N, int Na, int S, int ti, int tj, bool write_weights,
-                                      char* lds_raw, int tid, bool off, uint32_t rows, uint32_t cols) {
-    using Tr = XT<DT>;
-    constexpr int RB = Tr::RB, PLANES = Tr::PLANES, kStg = stage_blocks<DT, TILE>();
-    constexpr int WT = TILE / 2, MB = WT / 32;
+                                          int32_t* __restrict__ w_sb, const uint8_t* __restrict__ fl_sb, int N, int S,
+                                          int ti, int tj, bool write_weights, char* lds_raw, int tid, bool off,
+                                          uint32_t rows, uint32_t cols) {
+    constexpr int TILE = 64, RB = XT<AFC_F32>::RB, PLANES = XT<AFC_F32>::PLANES, kStg = stage_blocks<AFC_F32, TILE>();
     constexpr int PANEL = kStg * TILE * RB;                  // bytes of one panel in one stage
     constexpr int CHUNKS = kStg * TILE * PLANES;             // 16-byte chunks per panel per stage
     constexpr int CPT = CHUNKS / kStagers;
     static_assert(CHUNKS % kStagers == 0, "a stage must split evenly over the threads");
-    static_assert(DT == AFC_F32, "fp32 only");
-    using acc_t = typename Tr::acc_t;
 
     const int lane = tid & 63;
     const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wr = wid >> 1, wc = wid & 1;
     const int i0 = ti * TILE, j0 = tj * TILE;
     const bool diag = ti == tj;
-    static_assert(TILE == 64, "32 antennas a panel, 16 a wave's rows and columns");
     const bool wave_on = !off && wid < 4 && !(diag && wr < wc) &&
                          ((rows >> (16 * wr) | cols >> (16 * wc)) & 0xFFFFu) != 0;
     const int nb = (S + kSBlk - 1) / kSBlk;
     const int tail_valid = S - (nb - 1) * kSBlk;             // spectra in the last block
     const int n_stages = (nb + kStg - 1) / kStg;
 
-    acc_t accR[MB][MB], accI[MB][MB];
-    acc_t outR[MB][MB], outI[MB][MB];                        // fp32 only: outer level
-#pragma unroll
-    for (int m = 0; m < MB; ++m)
-#pragma unroll
-        for (int n = 0; n < MB; ++n) {
-            accR[m][n] = acc_t{};
-            accI[m][n] = acc_t{};
-            outR[m][n] = acc_t{};
-            outI[m][n] = acc_t{};
-        }
+    v16f accR{}, accI{}, outR{}, outI{};                     // inner and outer level
 
     // Loads are issued unconditionally from clamped addresses (always in
     // bounds) so that none of them waits on another; rows beyond N, blocks
     // beyond the subband's spectra and the tail spectra of the last block are
     // zeroed when the staged registers are written to LDS, after the compute
     // of the current stage has hidden the load latency.
-    constexpr int DEPTH = prefetch_depth<DT, TILE>();   // stages of loads in flight
+    constexpr int DEPTH = 2;                                 // stages of loads in flight
     uint4 pre[DEPTH][2][CPT];
     auto load_stage = [&](int st, auto slot_tag) {
         constexpr int slot = decltype(slot_tag)::value;
@@ -1197,9 +1183,9 @@ __device__ __forceinline__ void xtile_f32(const char* __restrict__ z, char* __re
                 const int row = rem / PLANES, q = rem % PLANES;
                 const int blk = min(st * kStg + bl, nb - 1);
                 const int rg = min(r0 + row, N - 1);
-                // (a channel of samples is below 2^27 bytes)
-                const unsigned off = ((unsigned)blk * (unsigned)N + (unsigned)rg) * RB + q * 16;
-                pre[slot][pn][c] = *reinterpret_cast<const uint4*>(z + off);
+                // (a channel of samples is at most 2^27 bytes)
+                const unsigned off_z = ((unsigned)blk * (unsigned)N + (unsigned)rg) * RB + q * 16;
+                pre[slot][pn][c] = *reinterpret_cast<const uint4*>(z + off_z);
             }
         }
     };
@@ -1225,14 +1211,14 @@ __device__ __forceinline__ void xtile_f32(const char* __restrict__ z, char* __re
                 uint4 v = pre[slot][pn][c];
                 if (!clean) {
                     if (blk >= nb || r0 + row >= N) v = make_uint4(0u, 0u, 0u, 0u);
-                    else if (blk == nb - 1 && tail_valid < kSBlk) v = mask_tail<DT>(v, q, tail_valid);
+                    else if (blk == nb - 1 && tail_valid < kSBlk) v = mask_tail<AFC_F32>(v, q, tail_valid);
                 }
                 *reinterpret_cast<uint4*>(base + bl * TILE * RB + row * RB + ((q ^ swz<RB, PLANES>(row)) * 16)) = v;
             }
         }
     };
-    auto rd = [&](const char* panel, int bl, int row, int q) -> uint4 {
-        return *reinterpret_cast<const uint4*>(panel + bl * TILE * RB + row * RB + ((q ^ swz<RB, PLANES>(row)) * 16));
+    auto rd = [&](const char* panel, int bl, int row, int q) -> float4 {
+        return *reinterpret_cast<const float4*>(panel + bl * TILE * RB + row * RB + ((q ^ swz<RB, PLANES>(row)) * 16));
     };
 
     const int lr = lane & 31, lh = lane >> 5;
@@ -1240,144 +1226,79 @@ __device__ __forceinline__ void xtile_f32(const char* __restrict__ z, char* __re
 
     // MFMAs of one stage from the panels PA (rows) and PB (columns)
     auto compute = [&](const char* PA, const char* PB) {
-        if (wave_on) {
-            {
+        if (!wave_on) return;
 #pragma unroll
-                for (int kk = 0; kk < kStg; ++kk) {
+        for (int kk = 0; kk < kStg; ++kk) {
 #pragma unroll
-                    for (int r2 = 0; r2 < 2; ++r2) {
-                        float4 a[MB], b[MB];
-#pragma unroll
-                        for (int m = 0; m < MB; ++m) {
-                            a[m] = __builtin_bit_cast(float4, rd(PA, kk, wr * WT + m * 32 + lr, 2 * r2 + lh));
-                            b[m] = __builtin_bit_cast(float4, rd(PB, kk, wc * WT + m * 32 + lr, 2 * r2 + lh));
-                        }
-#pragma unroll
-                        for (int m = 0; m < MB; ++m)
-#pragma unroll
-                            for (int n = 0; n < MB; ++n) {
-                                if (diag && wr == wc && m < n) continue;
-                                acc_t R = accR[m][n], I = accI[m][n];
-                                R = __builtin_amdgcn_mfma_f32_32x32x2f32(a[m].x, b[n].x, R, 0, 0, 0);
-                                R = __builtin_amdgcn_mfma_f32_32x32x2f32(a[m].y, b[n].y, R, 0, 0, 0);
-                                I = __builtin_amdgcn_mfma_f32_32x32x2f32(a[m].y, b[n].x, I, 0, 0, 0);
-                                I = __builtin_amdgcn_mfma_f32_32x32x2f32(a[m].x, -b[n].y, I, 0, 0, 0);
-                                R = __builtin_amdgcn_mfma_f32_32x32x2f32(a[m].z, b[n].z, R, 0, 0, 0);
-                                R = __builtin_amdgcn_mfma_f32_32x32x2f32(a[m].w, b[n].w, R, 0, 0, 0);
-                                I = __builtin_amdgcn_mfma_f32_32x32x2f32(a[m].w, b[n].z, I, 0, 0, 0);
-                                I = __builtin_amdgcn_mfma_f32_32x32x2f32(a[m].z, -b[n].w, I, 0, 0, 0);
-                                accR[m][n] = R;
-                                accI[m][n] = I;
-                            }
-                    }
-                    if (++fold == kF32Inner) {
-                        fold = 0;
-#pragma unroll
-                        for (int m = 0; m < MB; ++m)
-#pragma unroll
-                            for (int n = 0; n < MB; ++n) {
-                                outR[m][n] += accR[m][n];
-                                outI[m][n] += accI[m][n];
-                                accR[m][n] = acc_t{};
-                                accI[m][n] = acc_t{};
-                            }
-                    }
-                }
+            for (int r2 = 0; r2 < 2; ++r2) {
+                const float4 a = rd(PA, kk, wr * 32 + lr, 2 * r2 + lh), b = rd(PB, kk, wc * 32 + lr, 2 * r2 + lh);
+                accR = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, accR, 0, 0, 0);
+                accR = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, accR, 0, 0, 0);
+                accI = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.x, accI, 0, 0, 0);
+                accI = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, -b.y, accI, 0, 0, 0);
+                accR = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, accR, 0, 0, 0);
+                accR = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, accR, 0, 0, 0);
+                accI = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.z, accI, 0, 0, 0);
+                accI = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, -b.w, accI, 0, 0, 0);
+            }
+            if (++fold == kF32Inner) {
+                fold = 0;
+                outR += accR;
+                outI += accI;
+                accR = accI = v16f{};
             }
         }
     };
 
-    {
-        // Register staging with one barrier per stage: at stage st the
-        // registers hold the samples of the next DEPTH stages; stage st+1 goes
-        // to the other LDS buffer first, its register slot is refilled with
-        // stage st+1+DEPTH, then stage st is multiplied from its buffer.  The
-        // barrier at the end of the stage orders both the buffer just written
-        // (read at st+1) and the buffer just read (written at st+1).  Stage k
-        // lives in register slot k % DEPTH; the loop is unrolled by DEPTH so
-        // that every slot index is a constant.
-        using S0 = std::integral_constant<int, 0>;
-        using S1 = std::integral_constant<int, (DEPTH > 1 ? 1 : 0)>;
-        load_stage(0, S0{});
-        store_stage(0, 0, S0{});
-        if (n_stages > 1) load_stage(1, S1{});
-        if (DEPTH > 1 && n_stages > 2) load_stage(2, S0{});
+    // Register staging with one barrier per stage: at stage st the registers
+    // hold the samples of the next DEPTH stages; stage st+1 goes to the other LDS
+    // buffer first, its register slot is refilled with stage st+1+DEPTH, then
+    // stage st is multiplied from its buffer.  The barrier at the end of the stage
+    // orders both the buffer just written (read at st+1) and the buffer just read
+    // (written at st+1).  Stage k lives in register slot k % DEPTH; the loop is
+    // unrolled by DEPTH so that every slot index is a constant.
+    using S0 = std::integral_constant<int, 0>;
+    using S1 = std::integral_constant<int, 1>;
+    load_stage(0, S0{});
+    store_stage(0, 0, S0{});
+    if (n_stages > 1) load_stage(1, S1{});
+    if (n_stages > 2) load_stage(2, S0{});
+    lds_barrier();
+    auto step = [&](int st, auto slot_tag) {
+        const int buf = st & 1;
+        if (st + 1 < n_stages) {
+            store_stage(st + 1, buf ^ 1, slot_tag);
+            if (st + 1 + DEPTH < n_stages) load_stage(st + 1 + DEPTH, slot_tag);
+        }
+        compute(lds_raw + (buf * 2 + 0) * PANEL, lds_raw + (buf * 2 + (diag ? 0 : 1)) * PANEL);
         lds_barrier();
-        auto step = [&](int st, auto slot_tag) {
-            const int buf = st & 1;
-            if (st + 1 < n_stages) {
-                store_stage(st + 1, buf ^ 1, slot_tag);
-                if (st + 1 + DEPTH < n_stages) load_stage(st + 1 + DEPTH, slot_tag);
-            }
-            compute(lds_raw + (buf * 2 + 0) * PANEL, lds_raw + (buf * 2 + (diag ? 0 : 1)) * PANEL);
-            lds_barrier();
-        };
-        // stage st consumes slot (st + 1) % DEPTH
-        for (int st = 0; st < n_stages; st += 2) {
-            step(st, S1{});
-            if (st + 1 < n_stages) step(st + 1, S0{});
-        }
+    };
+    // stage st consumes slot (st + 1) % DEPTH
+    for (int st = 0; st < n_stages; st += 2) {
+        step(st, S1{});
+        if (st + 1 < n_stages) step(st + 1, S0{});
     }
-#pragma unroll
-    for (int m = 0; m < MB; ++m)
-#pragma unroll
-        for (int n = 0; n < MB; ++n) {
-            accR[m][n] += outR[m][n];
-            accI[m][n] += outI[m][n];
-        }
+    accR += outR;
+    accI += outI;
     if (!wave_on) return;
 
-    // ---- epilogue: 2x2 polarisation blocks of antennas a >= b
-    // flags of this lane's row antennas (8 per 32-row block) and column
-    // antennas, fetched together before the stores
-    bool frow[MB][8], fcol[MB];
+    // ---- epilogue: 2 x 2 polarisation blocks of antennas a >= b.  Rows r, r + 1
+    // (r even) of a lane are the two polarisations of an antenna, 8 antennas
+    // 4 (r / 4) + r / 2 % 2 in all, lanes lr, lr ^ 1 the two of one antenna b.
+    // Their flags are fetched together before the stores.
+    const int J = j0 + wc * 32 + lr;
+    auto row_of = [&](int r) { return i0 + wr * 32 + 8 * (r >> 2) + 4 * lh + (r & 3); };
+    auto flag_of = [&](int rcv) { return fl_sb && fl_sb[min(rcv, N - 1) >> 1] != 0; };
+    const bool fcol = flag_of(J), mine_c = cols >> (16 * wc + (lr >> 1)) & 1;
+    const uint32_t mine_r = rows >> (16 * wr + 2 * lh);
+    bool frow[8];
 #pragma unroll
-    for (int m = 0; m < MB; ++m) {
-        fcol[m] = false;
+    for (int k = 0; k < 8; ++k) frow[k] = flag_of(row_of(2 * k));
+    const StorePair<float> st{vis_ch, w_sb, N, S, write_weights, (lr & 1) != 0};
 #pragma unroll
-        for (int k = 0; k < 8; ++k) frow[m][k] = false;
-    }
-    if (fl_sb) {
-        uint8_t fc[MB], fr[MB][8];
-#pragma unroll
-        for (int m = 0; m < MB; ++m) {
-            fc[m] = fl_sb[min(j0 + wc * WT + m * 32 + lr, N - 1) >> 1];
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                fr[m][k] = fl_sb[min(i0 + wr * WT + m * 32 + 8 * (k >> 1) + 4 * lh + 2 * (k & 1), N - 1) >> 1];
-        }
-#pragma unroll
-        for (int m = 0; m < MB; ++m) {
-            fcol[m] = fc[m] != 0;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) frow[m][k] = fr[m][k] != 0;
-        }
-    }
-#pragma unroll
-    for (int m = 0; m < MB; ++m)
-#pragma unroll
-        for (int n = 0; n < MB; ++n) {
-            if (diag && wr == wc && m < n) continue;
-            const int J = j0 + wc * WT + n * 32 + lr;
-            if (J >= N) continue;
-            const int b = J >> 1, qq = J & 1;
-            const bool fb = fcol[n];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int I = i0 + wr * WT + m * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
-                if (I >= N) continue;
-                const int a = I >> 1, p = I & 1;
-                if (a < b || ((rows >> ((I - i0) >> 1) | cols >> ((J - j0) >> 1)) & 1u) == 0) continue;
-                const bool flagged = fb || frow[m][((r >> 2) << 1) | ((r >> 1) & 1)];
-                const int64_t bl = (int64_t)a * (a + 1) / 2 + b;
-                const int64_t e = bl * 4 + p * 2 + qq;
-                float re = accR[m][n][r], im = accI[m][n][r];
-                if (I == J) im = 0.0f;
-                if (flagged) re = im = 0.0f;
-                reinterpret_cast<float2*>(vis_ch)[e] = make_float2(re, im);
-                if (write_weights && p == 0 && qq == 0) w_sb[bl] = flagged ? 0 : S;
-            }
-        }
+    for (int r = 0; r < 16; r += 2)
+        st(accR[r], accI[r], accR[r + 1], accI[r + 1], row_of(r), J, fcol || frow[r >> 1],
+           !(mine_c || (mine_r >> (4 * (r >> 2) + ((r >> 1) & 1)) & 1)));
 }
 
 // One tile of one (subband, channel).  int8 / fp16: each wave computes its
@@ -1400,8 +1321,8 @@ __device__ __forceinline__ void xtile(const char* __restrict__ z, char* __restri
             return;
         __syncthreads();
         if constexpr (TILE == 64) {
-            xtile_f32<DT, 64, 512>(z, vis_ch, w_sb, fl_sb, N, Na, S, ti, tj, write_weights, lds_raw, threadIdx.x, false,
-                                   (uint32_t)rows, (uint32_t)cols);
+            xtile_f32<512>(z, vis_ch, w_sb, fl_sb, N, S, ti, tj, write_weights, lds_raw, threadIdx.x, false,
+                           (uint32_t)rows, (uint32_t)cols);
         } else {
             // the 64-wide quarters, two at a time: waves 0-3 the left ones,
             // waves 4-7 the right ones (above the diagonal on a diagonal
@@ -1413,8 +1334,8 @@ __device__ __forceinline__ void xtile(const char* __restrict__ z, char* __restri
                 if (qr == 0 && cols == 0) continue;
                 const int qi = 2 * ti + r, qj = 2 * tj + half;
                 const bool off = qi < qj || qi * 64 >= N || qj * 64 >= N;
-                xtile_f32<DT, 64, 256>(z, vis_ch, w_sb, fl_sb, N, Na, S, qi, qj, write_weights,
-                                       lds_raw + half * lds_f32_bytes<64>(), threadIdx.x & 255, off, qr, qc);
+                xtile_f32<256>(z, vis_ch, w_sb, fl_sb, N, S, qi, qj, write_weights,
+                               lds_raw + half * lds_f32_bytes<64>(), threadIdx.x & 255, off, qr, qc);
             }
         }
     } else {
