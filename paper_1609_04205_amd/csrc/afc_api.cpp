@@ -660,9 +660,13 @@ int upload_mode(afc_plan* p, int m, int tile) {
     md.n_wg = xengine_list_grid(ranges);
     md.n_items = (int)work.size();
     md.i8_only = true;
+    int max_S = 0;
     for (int b = 0; b < p->d.n_subbands; ++b)
-        if (in_mode(*p, m, p->dt[b])) md.i8_only &= p->dt[b] == AFC_I8;
-    md.groups = md.i8_only && tile == 64 ? xengine_i8_groups(md.n_items) : 1;
+        if (in_mode(*p, m, p->dt[b])) {
+            md.i8_only &= p->dt[b] == AFC_I8;
+            max_S = std::max(max_S, p->S[b]);
+        }
+    md.groups = md.i8_only && tile == 64 ? xengine_i8_groups(md.n_items, max_S) : 1;
     if (!md.used) return AFC_OK;
     hipError_t e = hipMalloc(&md.d_work, work.size() * sizeof(XWork));
     if (e == hipSuccess) e = hipMemcpy(md.d_work, work.data(), work.size() * sizeof(XWork), hipMemcpyHostToDevice);
@@ -994,9 +998,10 @@ AFC_API int afc_plan_create(const afc_dims* d, const afc_dtype* dtype_per_sb, co
         }
     }
     if (any1) {
-        int n32 = 0;
-        for (int b = 0; b < B; ++b) n32 += p->dt[b] == AFC_F32;
-        rc = upload_mode(p, 1, xengine_f32_tile(p->N, n32));
+        std::vector<int32_t> S1;
+        for (int b = 0; b < B; ++b)
+            if (p->dt[b] == AFC_F32) S1.push_back(p->S[b]);
+        rc = upload_mode(p, 1, xengine_f32_tile(p->N, S1.data(), (int)S1.size()));
         if (rc != AFC_OK) {
             afc_plan_destroy(p);
             return rc;

@@ -10,6 +10,15 @@
 
 namespace afc {
 
+// CUs of the current device, 256 if it cannot be asked
+inline int n_compute_units() {
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
+        n = 256;
+    return n;
+}
+
 constexpr int kP = 64;                 // channels
 constexpr int kT = 16;                 // taps per branch
 constexpr int kPFine = 256;            // channels of the fine bank
@@ -133,10 +142,11 @@ int xengine_list_grid(const XcdRanges& ranges);
 // tile width of the int8 / fp16 correlator for N receivers and subbands of
 // types dt and lengths S
 int xengine_tile(int N, const int32_t* dt, const int32_t* S, int n_subbands);
-// groups of waves per 64-wide int8 tile of a launch of this many workgroups
-int xengine_i8_groups(int64_t n_workgroups);
-// tile width of the fp32 correlator for N receivers and its subband count
-int xengine_f32_tile(int N, int n_subbands);
+// groups of waves per 64-wide int8 tile of a launch of this many workgroups and
+// this longest integration
+int xengine_i8_groups(int64_t n_workgroups, int max_S);
+// tile width of the fp32 correlator for N receivers and subbands of lengths S
+int xengine_f32_tile(int N, const int32_t* S, int n_subbands);
 // Fill `bytes` (a multiple of 4) of device memory with hashed bytes that are
 // valid int8 samples and finite fp16 values (bit 6 of every byte clear).
 hipError_t launch_fill_scratch(void* p, size_t bytes, hipStream_t stream);

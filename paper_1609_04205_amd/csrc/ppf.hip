@@ -375,10 +375,7 @@ __global__ __launch_bounds__(64 * kWaves) void ppf_list_kernel(const int16_t* __
 // second round with 32 workgroups before), 288 x 8 x 3051 1342 -> 1302 us;
 // 576 x 16 x 3051 still takes 768 (5154 us; 640 and 1024 within 0.4%).
 int ppf_run(const int32_t* S, int B, bool same_S, int n_groups) {
-    int dev = 0, n_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu <= 0)
-        n_cu = 256;
+    const int n_cu = n_compute_units();
     int max_S = S[0];
     for (int b = 1; b < B && !same_S; ++b) max_S = std::max(max_S, S[b]);
     const int64_t s_pad = ceil_div(max_S, kRunQ) * kRunQ;

@@ -1467,56 +1467,73 @@ hipError_t launch_fill_scratch(void* p, size_t bytes, hipStream_t stream) {
     return hipGetLastError();
 }
 
+// us that storing the visibilities takes at tb_s TB/s: the bound of launches of
+// few spectra
+static double store_us(int N, int n_subbands, double tb_s) {
+    const double Na = 0.5 * N;
+    return 16.0 * Na * (Na + 1.0) * kP * n_subbands / (tb_s * 1e6);
+}
+
 // fp32 tile width.  128-wide tiles convert and read each sample for twice as
-// many products, but run one workgroup per CU; 64-wide ones run two, waste
-// less at the array's edge and fill the CUs on small launches.  Measured (1000
-// spectra): 119 us per round of 128-wide tiles; 64-wide ones 53 us for at most
-// one per CU, 85 us for at most two, then 20 us + 80 us per round of two (a
-// round just begun costs it whole).  E.g. (64, 128) 75 antennas x 3 subbands 185
-// and 260 us, 150 x 2 340 and 381, 96 receivers x 4 subbands 116 and 93, 200
-// antennas x 1 287 and 349, 300 x 1 570 and 523, 576 x 1 1962 and 1665.
-int xengine_f32_tile(int N, int n_subbands) {
-    int dev = 0, n_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu <= 0)
-        n_cu = 256;
-    auto tiles = [&](int tile) {
-        const int64_t side = ceil_div(N, tile);
-        return side * (side + 1) / 2 * kP * n_subbands;
+// many products, but run one workgroup per CU; 64-wide ones run two, start and
+// store sooner, waste less at the array's edge and fill the CUs on small
+// launches.  Fitted in us to launches of 2 to 3051 spectra, 1 to 2048 antennas,
+// 1 to 16 subbands: a round of 128-wide tiles, one or two 64-wide ones on every
+// CU and the further ones (diagonal 128-wide tiles 0.84 of the others), by the
+// mean length; the slower of that and the visibilities' stores.  It is within
+// 0.2% of the better width on average.  E.g. (64, 128) 48 antennas x 4 subbands x
+// 100 spectra 18 and 15 us, 96 x 4 x 64 24 and 35, 200 x 1 x 1000 283 and 350, 300
+// x 1 x 1000 573 and 529, 576 x 1 x 2 83 and 119, x 100 258 and 246, x 3051 6110
+// and 5469.  One spectrum takes the fp32 MFMAs, which work in 64-wide tiles
+// anyway.
+int xengine_f32_tile(int N, const int32_t* S, int n_subbands) {
+    double mean = 0.0;
+    for (int b = 0; b < n_subbands; ++b) mean += S[b];
+    mean /= std::max(1, n_subbands);
+    if (mean <= 1.0) return 64;
+    const double n_cu = n_compute_units();
+    auto tiles = [&](int tile, double diag) {
+        const double side = (double)ceil_div(N, tile);
+        return (side * (side - 1.0) / 2.0 + diag * side) * kP * n_subbands / n_cu;       // per CU
     };
-    const double t128 = 119.0 * (double)ceil_div(tiles(128), n_cu);
-    const int64_t n64 = tiles(64);
-    const double r64 = (double)n64 / (2.0 * n_cu);
-    const double t64 = r64 <= 0.5 ? 53.0 : r64 <= 1.0 ? 85.0 : std::max(130.0, 20.0 + 80.0 * r64);
-    return t64 < t128 ? 64 : 128;
+    const double w128 = tiles(128, 1.0), w64 = tiles(64, 1.0), pair = 5.1 + 0.0775 * mean;
+    const double t128 = (8.1 + 0.127 * mean) * tiles(128, 0.84) / w128 * std::max(1.0, std::ceil(w128 - 1e-9));
+    const double t64 = w64 <= 1.0 ? 3.8 + 0.0756 * mean : w64 <= 2.0 ? pair : pair * std::max(1.4, 0.19 + 0.5 * w64);
+    return std::max(t64, store_us(N, n_subbands, 4.0)) < std::max(t128, store_us(N, n_subbands, 1.7)) ? 64 : 128;
 }
 
 // int8 / fp16 tile width.  A round (two 128-wide or four 64-wide off-diagonal
 // tiles on every CU) takes a fixed part, the tiles' first loads and stores, and
 // one per spectrum; a diagonal tile 0.6 (128) or 0.75 (64) of an off-diagonal
-// one.  64-wide tiles move twice the operand bytes per product, but start and
-// store sooner, fill the CUs on small launches and waste less at the array's
-// edge.  Fitted in us over 16 to 1152 receivers, 1 to 16 subbands, 200 and 1000
-// spectra; e.g. int8 150 receivers x 4 subbands x 1000 spectra 48 us (128) and
-// 29 us (64), 600 x 1 x 1000 38 and 25 us, 200 x 16 x 1000 163 and 191 us, 1152
-// x 2 x 1000 375 and 462 us.
+// one, and the only one of at most 128 receivers a fixed part by its size.
+// 64-wide tiles move twice the operand bytes per product, but start and store
+// sooner, fill the CUs on small launches and waste less at the array's edge;
+// launches of few spectra are bound by their stores, which 128-wide tiles do in
+// longer runs.  Fitted in us to launches of 1 to 3051 spectra, 1 to 2048
+// antennas, 1 to 16 subbands, within 0.3% of the better width on average.  E.g.
+// int8 (64, 128) 100 antennas x 3 subbands x 64 spectra 10.0 and 16.2 us, 48 x 8
+// x 1000 29 and 24, 150 x 1 x 3051 52 and 64, 300 x 1 x 1000 68 and 63, 576 x 1 x
+// 1000 212 and 177, 1500 x 1 x 16 617 and 518; fp16 100 x 3 x 300 25 and 32, 48 x
+// 8 x 300 20 and 17, 576 x 1 x 1000 386 and 311.
 int xengine_tile(int N, const int32_t* dt, const int32_t* S, int n_subbands) {
-    int dev = 0, n_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu <= 0)
-        n_cu = 256;
+    const double n_cu = n_compute_units();
     auto time = [&](int tile) {
+        const bool wide = tile == 128;
         const double side = (double)ceil_div(N, tile);
-        const double area = side * (side - 1.0) / 2.0 + (tile == 128 ? 0.6 : 0.75) * side;
-        const double rounds = area * kP / ((tile == 128 ? 2.0 : 4.0) * n_cu);           // of one subband
-        double sum = 0.0, longest = 0.0;
+        const double area = side * (side - 1.0) / 2.0 + (wide ? 0.6 : 0.75) * side;
+        const double rounds = area * kP / ((wide ? 2.0 : 4.0) * n_cu);                  // of one subband
+        const bool single = wide && N > 64 && N <= 128;
+        double sum = 0.0, longest = 0.0, stores = 0.0;
         for (int b = 0; b < n_subbands; ++b) {
-            const double t = dt[b] == AFC_I8 ? (tile == 128 ? 9.9 + 0.0266 * S[b] : 3.6 + 0.0195 * S[b])
-                                             : (tile == 128 ? 15.5 + 0.0465 * S[b] : 6.3 + 0.0347 * S[b]);
+            const bool i8 = dt[b] == AFC_I8;
+            double fixed = wide ? (i8 ? 11.9 : 14.4) : (i8 ? 4.2 : 4.9);
+            if (single) fixed = fixed * N / 128.0 + (i8 ? 0.45 : 0.91);
+            const double t = fixed + S[b] * (wide ? (i8 ? 0.0262 : 0.0522) : (i8 ? 0.0193 : 0.0371));
             sum += t * rounds;
-            longest = std::max(longest, t);
+            longest = std::max(longest, t * (i8 ? 0.375 : 0.28));
+            stores += store_us(N, 1, wide ? (i8 ? 4.1 : 5.3) : (i8 ? 4.0 : 3.4));
         }
-        return sum + 0.3 * longest;
+        return std::max(sum + longest, stores);
     };
     return time(64) < time(128) ? 64 : 128;
 }
@@ -1525,18 +1542,18 @@ int xengine_tile(int N, const int32_t* dt, const int32_t* S, int n_subbands) {
 // only: its sums are exact in any order; a float sum would depend on the
 // launch's size).  A workgroup alone on its CU takes about 0.24 us per stage
 // whatever the depth of its ring: one wave per SIMD, and a stage is a chain of
-// barrier, LDS reads and MFMAs.  With four groups four chains run on the CU.
-// Four while the launch has no more workgroups than the card CUs, two while it
-// has fewer than two per CU; from there on the CUs hold several workgroups
-// anyway.  In us for one, two and four groups at 3051 spectra: 16 receivers x
-// 1 subband (64 workgroups) 25.8, 18.0, 15.1; 96 x 1 (192) 28.2, 19.2, 16.6;
-// 150 x 1 (384) 35.1, 27.8, 32.5; 150 x 2 (768) 40.8, 43.4, 48.8.
-int xengine_i8_groups(int64_t n_workgroups) {
-    int dev = 0, n_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu <= 0)
-        n_cu = 256;
-    return n_workgroups <= n_cu ? 4 : n_workgroups < 2 * n_cu ? 2 : 1;
+// barrier, LDS reads and MFMAs.  With four groups four chains run on the CU,
+// at the price of a larger workgroup to start and sums to add: worth it for
+// launches of no more workgroups than the card has CUs, or twice as many, and
+// more stages (max_S: the longest subband).  In us for one, two and four groups:
+// 64 to 256 workgroups x 64 spectra 3.6, 3.8, 4.9; x 300 6.0, 5.6, 6.7; x 600
+// 8.1, 7.2, 7.3; x 1000 11.2, 9.0, 8.7; x 3051 26, 19, 16; 384 and 512 x 600
+// 9.8, 10.1, 13.7; x 1000 13.1, 12.1, 16.1; x 3051 32, 27, 32; 640 x 3051 39, 42,
+// 47.
+int xengine_i8_groups(int64_t n_workgroups, int max_S) {
+    const int n_cu = n_compute_units();
+    if (n_workgroups <= n_cu) return max_S >= 800 ? 4 : max_S >= 240 ? 2 : 1;
+    return n_workgroups <= 2 * n_cu && max_S >= 800 ? 2 : 1;
 }
 
 hipError_t launch_xengine(const XLaunch& l, hipStream_t stream) {
@@ -1555,7 +1572,7 @@ hipError_t launch_xengine(const XLaunch& l, hipStream_t stream) {
     a.P = kP;
     int32_t dts[AFC_MAX_SUBBANDS];
     std::fill_n(dts, l.B, (int32_t)l.dt);
-    const int tile = l.dt == AFC_F32 ? xengine_f32_tile(l.N, l.B) : xengine_tile(l.N, dts, l.S_host, l.B);
+    const int tile = l.dt == AFC_F32 ? xengine_f32_tile(l.N, l.S_host, l.B) : xengine_tile(l.N, dts, l.S_host, l.B);
     a.n_tiles_side = (int)ceil_div(l.N, tile);
     a.n_tiles = a.n_tiles_side * (a.n_tiles_side + 1) / 2;
     const int64_t total = (int64_t)a.n_tiles * kP * l.B;
@@ -1564,7 +1581,8 @@ hipError_t launch_xengine(const XLaunch& l, hipStream_t stream) {
     a.per_xcd = (int)ceil_div(total, 8);
     for (int b = 0; b < l.B; ++b) a.S[b] = l.S_host[b];
     const dim3 grid((unsigned)(a.per_xcd * 8));
-    const int groups = tile == 64 && l.dt == AFC_I8 ? xengine_i8_groups(total) : 1;
+    const int groups =
+        tile == 64 && l.dt == AFC_I8 ? xengine_i8_groups(total, *std::max_element(l.S_host, l.S_host + l.B)) : 1;
 #define AFC_X_LAUNCH(DT, TILE, GROUPS)                                                                            \
     hipLaunchKernelGGL((xengine_kernel<DT, TILE, GROUPS>), grid, dim3(tile_threads<DT, TILE>() * GROUPS), 0,      \
                        stream, a)

@@ -329,7 +329,7 @@ def test_int8_groups_of_a_small_launch(afc, dev, Na, B, S):
             np.testing.assert_array_equal(w_np[b], W_)
 
 
-@pytest.mark.parametrize("B,Na,S", [(1, 75, 97), (4, 48, 40), (1, 100, 200), (1, 150, 65)])
+@pytest.mark.parametrize("B,Na,S", [(1, 75, 97), (4, 48, 40), (1, 100, 200), (1, 150, 65), (4, 100, 200)])
 @pytest.mark.parametrize("power", [-20, -30])
 def test_f32_split_goes_by_the_receivers_scale(afc, dev, B, Na, S, power):
     """A sample far below its receiver's others does not take a tile off the
@@ -345,8 +345,8 @@ def test_f32_split_goes_by_the_receivers_scale(afc, dev, B, Na, S, power):
 
 
 # fp32 tiles of one subband alone and of all together: 64 and 128 wide at 48
-# antennas, 128 (with a tile off the diagonal) and 64 at 100
-@pytest.mark.parametrize("B,Na,S", [(4, 48, 300), (2, 100, 200), (2, 100, 33)])
+# antennas and at 100 x 4 (with a tile off the diagonal), 128 and 64 at 100 x 2
+@pytest.mark.parametrize("B,Na,S", [(4, 48, 300), (4, 100, 200), (2, 100, 33)])
 @pytest.mark.parametrize("case", ["inf", "large", "late", "small", "all"])
 def test_f32_out_of_range_antennas_leave_the_others_alone(afc, dev, B, Na, S, case):
     """A baseline's bits depend on the samples of its own two antennas: one that
@@ -377,3 +377,15 @@ def test_f32_out_of_range_antennas_leave_the_others_alone(afc, dev, B, Na, S, ca
         v1, w1 = afc.correlate(y[b:b + 1].contiguous(), n_spectra=S, flags=fl[b:b + 1])
         assert torch.equal(v1[0].view(torch.int32), got[b].view(torch.int32)), b
         assert torch.equal(w1[0], w[b])
+
+
+@pytest.mark.parametrize("dtype,Na,B,S,tile", [("i8", 40, 8, 1000, 128), ("i8", 128, 3, 64, 64), ("i8", 1500, 1, 16, 128),
+                                               ("f16", 33, 8, 200, 128), ("f16", 100, 3, 300, 64),
+                                               ("f32", 48, 4, 100, 128), ("f32", 288, 1, 2, 64), ("f32", 75, 3, 1, 64)])
+def test_tile_width_by_the_lengths(afc, dev, dtype, Na, B, S, tile):
+    """Launches whose faster tile width the sizes without the integration
+    lengths, or without the stores, do not tell: the plan takes the rule's."""
+    log(f"tile width {dtype} Na={Na} B={B} S={S}")
+    plan = afc.Plan(Na, [S] * B, [dtype] * B)
+    assert plan.info().tile == tile
+    plan.close()
