@@ -76,9 +76,6 @@ template <int DT, int TILE>
 constexpr int stage_blocks() {
     return DT == AFC_F32 ? 4 : 64 / XT<DT>::RB;
 }
-// int8 and fp16 stage through direct global-to-LDS loads, fp32 through registers
-template <int DT>
-constexpr bool uses_dma() { return DT != AFC_F32; }
 // stages of global-to-LDS loads in flight beyond the next one: one stage is
 // 32 spectra for int8 and 16 for fp16
 #ifndef AFC_I8_DMA_DEPTH
@@ -841,7 +838,7 @@ __device__ __forceinline__ void xtile_mm16(const char* __restrict__ z, char* __r
 // one float32 multiply.  The bf16 rate is 16 times the fp32 matrix rate, so
 // the six take 3/8 of the time of the fp32 MFMAs.
 // Bound by the matrix cores' power: 1152 receivers x 2 subbands x 3051 spectra
-// take 10.4 ms, 1.2 PFLOP/s of bf16 MFMA (a large bf16 product reaches 1.26 on
+// take 10.2 ms, 1.2 PFLOP/s of bf16 MFMA (a large bf16 product reaches 1.26 on
 // the same card), against 17.9 ms on the fp32 MFMAs; converting while the
 // SIMD's other wave multiplies is worth 2% of it.
 //
@@ -969,9 +966,9 @@ __device__ __forceinline__ bool xtile_split(const char* __restrict__ z, char* __
             split2(v.x, v.y, h.z, m.z, l.z);
             split2(v.z, v.w, h.w, m.w, l.w);
             mx[pn] = max3_abs(u.x, u.y, max3_abs(u.z, u.w, max3_abs(v.x, v.y, max3_abs(v.z, v.w, mx[pn]))));
-            // (taken here: sunk past the next loads, it would keep their registers
-            // and wait for them, 20% of the time at 80 receivers)
-            __asm__ volatile("" : "+v"(mx[pn]));
+            // (partial tiles: taken here; sunk past the next loads, it would keep
+            // their registers and wait for them, 20% of the time at 80 receivers)
+            if constexpr (!kFull) __asm__ volatile("" : "+v"(mx[pn]));
             char* p = base + pn * kSplitPanel;
             *reinterpret_cast<uint4*>(p) = h;
             *reinterpret_cast<uint4*>(p + kSplitPlane) = m;
