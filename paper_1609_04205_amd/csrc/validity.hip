@@ -83,11 +83,12 @@ __global__ void validity_kernel(const uint8_t* __restrict__ pkt, uint32_t* __res
 // the channels and take the four words one after the other, an antenna per lane:
 // zeros over both receivers, 8, 2 or 1 spectra at a time (kWide: z is 16-byte
 // aligned, and with it every block).  kSplit workgroups share the channels of
-// the words, up to 16 and as many as still start quickly: losses are bursts of
-// whole stations or a dead one, the work of few words.  576 antennas x 4 subbands, int8: 3.6 us
+// the words, four or, on small launches, eight or 16: losses are bursts of whole
+// stations or a dead one, the work of few words.  576 antennas x 4 subbands, int8: 3.6 us
 // without a loss, 48 us with bursts (0.6% of the packets) and a dead station; a
 // thread per antenna and word that took all channels, spectrum by spectrum, 2.8
-// and 363 us, a thread for every eight of the channels 5.9 and 56 us.
+// and 363 us, a thread for every eight of the channels 5.9 and 56 us (16 subbands
+// 8.6 and 160 us; 4.9 and 786, 18 and 156).
 constexpr int kZeroWords = 4;
 template <typename SampleT, bool kWide, int kSplit>
 __global__ __launch_bounds__(64 * kZeroWords) void zero_kernel(const uint32_t* __restrict__ v, SampleT* __restrict__ z,
@@ -254,7 +255,7 @@ hipError_t launch_zero_invalid(const uint32_t* v, void* z, afc_dtype dt, int B, 
     const int Sb = (int)ceil_div(S, kSBlk);
     const bool wide = reinterpret_cast<uintptr_t>(z) % 16 == 0;
     const int64_t n_wg = ceil_div(Na, 64) * ceil_div(Wd, kZeroWords) * B;
-    const int split = n_wg * 16 <= 2048 ? 16 : n_wg * 8 <= 2048 ? 8 : n_wg * 4 <= 4096 ? 4 : 2;
+    const int split = n_wg * 16 <= 2048 ? 16 : n_wg * 8 <= 2048 ? 8 : 4;
     const dim3 grid((unsigned)ceil_div(Na, 64), (unsigned)ceil_div(Wd, kZeroWords), (unsigned)(B * split));
 #define AFC_ZERO_N(T, W, N)                                                                                     \
     hipLaunchKernelGGL((zero_kernel<T, W, N>), grid, dim3(64 * kZeroWords), 0, stream, v, reinterpret_cast<T*>(z), Na, \
@@ -262,8 +263,7 @@ hipError_t launch_zero_invalid(const uint32_t* v, void* z, afc_dtype dt, int B, 
 #define AFC_ZERO_W(T, W)                                                                                        \
     if (split == 16) AFC_ZERO_N(T, W, 16);                                                                      \
     else if (split == 8) AFC_ZERO_N(T, W, 8);                                                                   \
-    else if (split == 4) AFC_ZERO_N(T, W, 4);                                                                   \
-    else AFC_ZERO_N(T, W, 2);
+    else AFC_ZERO_N(T, W, 4);
 #define AFC_ZERO(T)                                                                                             \
     if (wide) { AFC_ZERO_W(T, true) } else { AFC_ZERO_W(T, false) }
     switch (dt) {

@@ -209,10 +209,9 @@ def test_validity_packet_sizes(afc, dev, Na, S, Q, Ps, n_extra):
 
 
 # a workgroup takes four words of 64 antennas, whole and partial; sixteen share
-# the channels up to 128 such workgroups, eight up to 256, four up to 1024, two
-# above
+# the channels up to 128 such workgroups, eight up to 256, four above
 @pytest.mark.parametrize("Na,B,S", [(9, 2, 77), (65, 1, 321), (64, 1, 32 * 600 - 7), (64, 1, 32 * 1030 - 5),
-                                    (17, 2, 32 * 2060 - 31)])
+                                    (17, 2, 32 * 520 - 31)])
 @pytest.mark.parametrize("dtype", [torch.int8, torch.float16, torch.float32])
 @pytest.mark.parametrize("offset", [0, 1])
 def test_zeros_of_every_word_pattern(afc, dev, Na, B, S, dtype, offset):
