@@ -457,7 +457,7 @@ __device__ __forceinline__ void dft(float2 (&x)[R]) {
 }
 
 // Rows per workgroup of the N-point transform: enough that the transposed
-// store writes 64 bytes (2048 points; 128 KB of LDS) and a workgroup has at
+// store writes 64 bytes (2048 points; 156 KB of LDS) and a workgroup has at
 // least one wave, few enough that 256 workgroups result where N allows.
 template <int N>
 constexpr int fft_rows() { return N >= 4096 ? 2 : N >= 2048 ? 8 : N >= 512 ? 4 : N >= 128 ? 1024 / N : 32; }
@@ -470,7 +470,7 @@ constexpr int kFftPer = 16;                      // points per thread
 // ns) / (R ns)) and writes its outputs to (j / ns) R ns + j mod ns + r ns.
 // kFirst: input the gridding's grid, modulated by (-1)^(row + column), output
 // float2; otherwise output float, (-1)^(row + k) Re(.) / norm.  Bound by the
-// memory traffic and by latency: 2048^2 takes 40 us for both transforms (five
+// memory traffic and by latency: 2048^2 takes 44 us for both transforms (five
 // passes over 32 MB); radix-2 passes, twiddles, transposes and a copy in
 // launches of their own took 111 us.
 template <int N, bool kFirst>

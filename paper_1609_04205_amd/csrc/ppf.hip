@@ -344,7 +344,7 @@ __global__ __launch_bounds__(64 * kWaves) void ppf_kernel(const int16_t* __restr
 // Batched form: one launch per sample type over the runs of its subbands,
 // which have their own integration length and gain (a body that holds the
 // three types needs 256 registers per lane, 8 waves: 4.6 ms for 16 subbands of
-// 576 antennas, 508 to 3051 spectra, int8 and fp16, against 3.6 ms).
+// 576 antennas, 508 to 3051 spectra, int8 and fp16, against 3.8 ms).
 template <int DT, bool kOne>
 __global__ __launch_bounds__(64 * kWaves) void ppf_list_kernel(const int16_t* __restrict__ x,
                                                               const float* __restrict__ taps, void* __restrict__ z,
